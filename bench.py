@@ -32,7 +32,7 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBPS = 8000.0
 METRIC = "exchange pair-solves/s + ACE build s, FP32-batched vs FP64 at <=2e-5 err"
-PASS_NAMES = ["pass1_fwd_xy", "pass2_z_kernel", "pass3_inv_xy_acc", "pass4_transpose_acc"]
+PASS_NAMES = ["pass1_z", "pass2_xy", "pass3_z", "pass4_rows"]
 # Time step 50 as in atomic units of time times the hybrid mixing fraction 0.25.
 DT_ALPHA = 50.0 / 24.188843265857 * 0.25
 
@@ -208,9 +208,9 @@ def roofline_fields(prof, ace, steps, pairs_phys, ng, b, copy_gbps):
     pipe_ms = sum(p["ms"] for p in prof)
     model_bytes = pairs_phys * 6.0 * ng * b * steps
     pipe_gbps = model_bytes / (pipe_ms * 1e-3) / 1e9
-    # bytes the Hermitian-pair mode moves beyond the model: the kept v_ij,
-    # written by pass 3 and read back by pass 4
-    extra_bytes = pairs_phys * ng * b * steps + prof[3]["bytes"]
+    # bytes the Hermitian-pair mode moves beyond the model, at least: the outputs
+    # that pass 4 adds the row sums to
+    extra_bytes = prof[3]["bytes"]
     passes = {}
     for k in range(4):
         if prof[k]["launches"] == 0:
@@ -226,15 +226,14 @@ def roofline_fields(prof, ace, steps, pairs_phys, ng, b, copy_gbps):
         "per_unit_bytes": per_launch,
         "unit_desc": "algorithmic bytes per launch of the dominant pass: 2*N_g*b per pair "
                      "solved in the launch (its share of the 6*N_g*b pair model), b = 8 B "
-                     "(complex64); the kept v_ij of the Hermitian-pair mode is not counted",
+                     "(complex64); the row sums of the Hermitian-pair mode are not counted",
     }
     pipeline = dict(ms_per_step=pipe_ms / steps, model_GBps=pipe_gbps,
                     model_frac=pipe_gbps / HBM_PEAK_GBPS,
-                    model_plus_kept_v_GBps=(model_bytes + extra_bytes) / (pipe_ms * 1e-3) / 1e9,
+                    model_plus_rows_GBps=(model_bytes + extra_bytes) / (pipe_ms * 1e-3) / 1e9,
                     copy_kernel_GBps=copy_gbps,
                     desc="physical pair solves x 6*N_g*b over the summed pass times of the "
-                         "pair pipeline; model_plus_kept_v adds the v_ij that the Hermitian-pair "
-                         "mode writes in pass 3 and reads in pass 4")
+                         "pair pipeline; model_plus_rows adds the outputs that pass 4 updates")
     stages = dict(pair_pipeline_ms=pipe_ms / max(1, ace["calls"]),
                   M_contraction_ms=ace["M"] / max(1, ace["calls"]),
                   factorization_ms=ace["factor"] / max(1, ace["calls"]),

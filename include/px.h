@@ -128,7 +128,7 @@ px_status px_set_workspace(px_context* ctx, void* dev_ptr, size_t bytes);
 
 /* Pair-chunk tuning: a chunk is ic output orbitals x jc density orbitals whose
  * pair slabs are in flight together (Sec. III-B(b) batches 16 pairs on its
- * GPU).  0 restores the default.  Changes px_workspace_bytes.  The pass-2
+ * GPU).  0 restores the default.  Changes px_workspace_bytes.  The tile
  * configuration that px_autotune chose for the grid is kept. */
 px_status px_set_tuning(px_context* ctx, const px_cell* cell, px_precision prec, int32_t ic,
                         int32_t jc);
@@ -338,28 +338,29 @@ px_status px_ptim_step(px_context* ctx, const px_cell* cell, px_precision prec, 
 /* Hermitian pair symmetry of the ACE build (default on).  With Phi = Psi and a
  * real even kernel, v_ji = conj(v_ij): the orbitals are cut into square blocks,
  * only blocks J <= I are transformed, and a diagonal block only for its pairs
- * j <= i; the real-space v_ij is kept and a streaming pass adds the transposed
- * contribution -f_i psi_i conj(v_ij) to W_j for j < i.  Every unordered pair
+ * j <= i; the transposed contribution -f_i psi_i conj(v_ij) to W_j for j < i is
+ * summed while v_ij is at hand (see px_profile_read).  Every unordered pair
  * is solved once (N (N + 1) / 2 pair solves instead of N^2). */
 px_status px_set_symmetry(px_context* ctx, int32_t enable);
 
 /* Measurement mode.  When enabled, px_exchange_apply and px_ace_build record
- * HIP events on their stream around pass 1 (pair product + forward xy
- * transforms), pass 2 (z transforms + kernel multiply) and pass 3 (inverse xy
- * transforms + weighted accumulation) of every pair chunk, and synchronise on
+ * HIP events on their stream around pass 1 (pair product + forward z
+ * transform), pass 2 (xy transforms + kernel multiply) and pass 3 (inverse z
+ * transform + weighted accumulation) of every pair chunk, and synchronise on
  * the last event before returning (the only host synchronisation outside
  * px_sync).  Off by default. */
 px_status px_set_profiling(px_context* ctx, int32_t enable);
 
 /* Totals since the last reset, per pass k = 0..3 (arrays of 4): ms[k] summed
  * event time (pass 4: the time from the end of pass 3 to the end of the
- * chunk, which is the transposed accumulation), bytes[k] algorithmic HBM
+ * chunk, in which the row sums are added), bytes[k] algorithmic HBM
  * bytes of the 6 * N_g * b pair model (b = element size), 2 * N_g * b per
  * solved pair in each of passes 1-3: pass 1 reads psi_j and writes the pair
  * slab, pass 2 reads and rewrites it, pass 3 reads it and psi_j.  The
- * Hermitian-pair mode keeps v_ij outside that model: pass 3 also writes it
- * (N_g * b per solved pair, not counted in bytes[2]) and pass 4 reads it back,
- * bytes[3] = N_g * b per pair below the diagonal.  launches[k] kernel
+ * Hermitian-pair mode adds row sums outside that model: pass 3 writes one slab
+ * of them per row and group of up to 8 pairs (not counted in bytes[2]), and
+ * pass 4 reads them back and adds them to the outputs; bytes[3] = 2 * N_g * b
+ * per row (the outputs alone).  launches[k] kernel
  * launches.  reset != 0 zeroes the totals. */
 px_status px_profile_read(px_context* ctx, double* ms, double* bytes, int64_t* launches,
                           int32_t reset);
@@ -421,12 +422,9 @@ px_status px_set_graph(px_context* ctx, int32_t enable);
 /* Autotuner: times the Hermitian-pair pipeline on this instance (Phi = Psi)
  * for square pair blocks B in {16, 24, 32, 48, 64, 96, 128, 192, 256} (up to
  * the first B >= n, which solves the instance as one triangular block) that
- * fit the attached workspace, each with both compiled
- * configurations of pass 2 (the z transforms: its workgroup shape, x-sections
- * per plane and threads, fixed per grid size at compile time; one
- * configuration on the non-cubic grids), keeps the
- * fastest pair as the context's tuning for this grid and precision, writes B
- * to *best_block (nullable) and appends a JSON line (block, "p2"
+ * fit the attached workspace, each with both compiled tile configurations of
+ * passes 1 and 3 (tile rows of 256 and of 512 bytes), keeps the fastest pair as the context's tuning for this grid and precision, writes B
+ * to *best_block (nullable) and appends a JSON line (block, "p2": the tile
  * configuration, per-candidate times) to cache_path (nullable).
  * Synchronises `stream`; `out` receives Vx psi. */
 px_status px_autotune(px_context* ctx, const px_cell* cell, px_precision prec, int32_t n,

@@ -3,7 +3,7 @@
     python -m paper_2501_03061_amd.csrc.build      # or build() from Python
 
 Every .hip translation unit is compiled with hipcc for gfx950 only; the pair
-pipeline is compiled once per grid size (-DPX_N=n) so the sizes build in
+pipeline is compiled once per grid (-DPX_S0, PX_S1, PX_S2) so the grids build in
 parallel.  Packed FP32 instructions are disabled for all device code.
 """
 from __future__ import annotations
@@ -38,12 +38,10 @@ def _hipcc() -> str:
 
 def _units():
     units = []
-    for n in SIZES:
-        units.append(("exchange_inst.hip", f"exchange_n{n}.o", [f"-DPX_N={n}"]))
-    for n0, n1, n2 in SHAPES:
-        units.append(("exchange_shape.hip", f"exchange_s{n0}x{n1}x{n2}.o",
+    for n0, n1, n2 in SHAPES + tuple((n, n, n) for n in reversed(SIZES)):
+        units.append(("exchange_inst.hip", f"exchange_{n0}x{n1}x{n2}.o",
                       [f"-DPX_S0={n0}", f"-DPX_S1={n1}", f"-DPX_S2={n2}"]))
-    for src in ("exchange_dispatch.cpp", "pair_transpose.hip", "misc_kernels.hip", "gemm_kernels.hip",
+    for src in ("exchange_dispatch.cpp", "pair_rows.hip", "misc_kernels.hip", "gemm_kernels.hip",
                 "chol_kernels.hip", "eig_kernels.hip", "density_fine.hip", "px_api.cpp"):
         units.append((src, os.path.splitext(src)[0] + ".o", []))
     return units

@@ -1,68 +1,43 @@
-// Size dispatch of the pair pipeline: the cubic grids with compiled plans
-// (per-size tuned configurations) and the non-cubic grids (configurations
-// from the plans alone).
+// Size dispatch of the pair pipeline: the grids with compiled plans.
 #include "px_internal.hpp"
 
 namespace px {
 
-template <int N>
-hipError_t launch_chunk_n(bool fp32, const ChunkArgs& a, int npairs, bool ex, bool store_v,
-                          int p2cfg, hipStream_t s, hipEvent_t* ev, const ChunkArgs* tasks,
-                          int ntasks, int max_ic);
 template <int N0, int N1, int N2>
-hipError_t launch_chunk_shape(bool fp32, const ChunkArgs& a, int npairs, bool ex, bool store_v,
-                              hipStream_t s, hipEvent_t* ev, const ChunkArgs* tasks, int ntasks,
-                              int max_ic);
+hipError_t launch_chunk_t(bool fp32, const ChunkArgs& a, const ChunkDims& d, bool ex, int cfg,
+                          hipStream_t s, hipEvent_t* ev, const ChunkArgs* tasks);
 
-#define PX_SIZES(X) X(16) X(24) X(32) X(40) X(48) X(60) X(64) X(72) X(80) X(96)
-#define PX_SHAPES(X) X(60, 60, 90) X(60, 90, 120)
+#define PX_CUBE(X, N) X(N, N, N)
+#define PX_GRIDS(X)                                                                             \
+  PX_CUBE(X, 16) PX_CUBE(X, 24) PX_CUBE(X, 32) PX_CUBE(X, 40) PX_CUBE(X, 48) PX_CUBE(X, 60)     \
+  PX_CUBE(X, 64) PX_CUBE(X, 72) PX_CUBE(X, 80) PX_CUBE(X, 96) X(60, 60, 90) X(60, 90, 120)
 
 bool grid_supported(int n0, int n1, int n2) {
-#define PX_SHAPE_CASE(A, B, C) if (n0 == A && n1 == B && n2 == C) return true;
-  PX_SHAPES(PX_SHAPE_CASE)
-#undef PX_SHAPE_CASE
-  if (n0 != n1 || n1 != n2) return false;
-#define PX_CASE(N) if (n0 == N) return true;
-  PX_SIZES(PX_CASE)
+#define PX_CASE(A, B, C) if (n0 == A && n1 == B && n2 == C) return true;
+  PX_GRIDS(PX_CASE)
 #undef PX_CASE
   return false;
 }
 
-bool grid_cubic(int n0, int n1, int n2) { return n0 == n1 && n1 == n2; }
-
-hipError_t launch_chunk(bool fp32, const int* n, const ChunkArgs& a, int npairs, bool ex, int p2cfg,
-                        hipStream_t s, hipEvent_t* ev) {
-#define PX_SHAPE_CASE(A, B, C)                   \
+static hipError_t dispatch(bool fp32, const int* n, const ChunkArgs& a, const ChunkDims& d, bool ex,
+                           int cfg, hipStream_t s, hipEvent_t* ev, const ChunkArgs* tasks) {
+#define PX_CASE(A, B, C)                         \
   if (n[0] == A && n[1] == B && n[2] == C)       \
-    return launch_chunk_shape<A, B, C>(fp32, a, npairs, ex, a.store_v != 0, s, ev, nullptr, 1, 0);
-  PX_SHAPES(PX_SHAPE_CASE)
-#undef PX_SHAPE_CASE
-  if (!grid_cubic(n[0], n[1], n[2])) return hipErrorInvalidValue;
-#define PX_CASE(N) \
-  if (n[0] == N)   \
-    return launch_chunk_n<N>(fp32, a, npairs, ex, a.store_v != 0, p2cfg, s, ev, nullptr, 1, 0);
-  PX_SIZES(PX_CASE)
+    return launch_chunk_t<A, B, C>(fp32, a, d, ex, cfg, s, ev, tasks);
+  PX_GRIDS(PX_CASE)
 #undef PX_CASE
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_chunk_tasks(bool fp32, const int* n, const ChunkArgs* tasks, int ntasks, int max_ic,
-                              int max_pairs, bool ex, bool store_v, int p2cfg, hipStream_t s) {
-  ChunkArgs dummy{};
-#define PX_SHAPE_CASE(A, B, C)                                                                    \
-  if (n[0] == A && n[1] == B && n[2] == C)                                                        \
-    return launch_chunk_shape<A, B, C>(fp32, dummy, max_pairs, ex, store_v, s, nullptr, tasks, ntasks, \
-                                       max_ic);
-  PX_SHAPES(PX_SHAPE_CASE)
-#undef PX_SHAPE_CASE
-  if (!grid_cubic(n[0], n[1], n[2])) return hipErrorInvalidValue;
-#define PX_CASE(N)                                                                                  \
-  if (n[0] == N)                                                                                    \
-    return launch_chunk_n<N>(fp32, dummy, max_pairs, ex, store_v, p2cfg, s, nullptr, tasks, ntasks, \
-                             max_ic);
-  PX_SIZES(PX_CASE)
-#undef PX_CASE
-  return hipErrorInvalidValue;
+hipError_t launch_chunk(bool fp32, const int* n, const ChunkArgs& a, bool ex, int cfg, hipStream_t s,
+                        hipEvent_t* ev) {
+  const ChunkDims d{1, a.ic, a.jc, chunk_pairs(a), a.store_v};
+  return dispatch(fp32, n, a, d, ex, cfg, s, ev, nullptr);
+}
+
+hipError_t launch_chunk_tasks(bool fp32, const int* n, const ChunkArgs* tasks, const ChunkDims& d, bool ex,
+                              int cfg, hipStream_t s) {
+  return dispatch(fp32, n, ChunkArgs{}, d, ex, cfg, s, nullptr, tasks);
 }
 
 }  // namespace px

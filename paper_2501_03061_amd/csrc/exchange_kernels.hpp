@@ -2,33 +2,39 @@
 //
 //   (Vx phi_i)(r) = -sum_j f_j psi_j(r) * IFFT[ K(G) * FFT(conj(psi_j) * phi_i) ](r)
 //
-// split into three passes over a chunk of orbital pairs (i, j), each pass a
-// kernel that keeps one 2D section of the grid in LDS:
+// over a chunk of orbital pairs (i, j) in passes that each keep a piece of a
+// pair's grid in LDS:
 //
-//   pass 1  (z-slab, i) : pair product conj(psi_j)*phi_i, forward x and y
-//                         transforms, slab written to the pair buffer T.
-//   pass 2  (y-plane, pair): forward z transform, multiply by K(G) (and, in
-//                         FP32 form, the G = 0 coefficient taken from FP64
-//                         slab sums), FP64 partial of sum_G K |rho(G)|^2 for
-//                         the exchange energy, inverse z transform; in place.
-//   pass 3  (z-slab, i) : inverse x and y transforms, then the weighted sum
-//                         over the chunk's j of f_j/N_g * psi_j * v_ij kept in
-//                         registers and subtracted from the output slab once.
+//   pass 1  (z tile, i) : pair product conj(psi_j)*phi_i, forward z transform,
+//                         written to the pair buffer T.
+//   pass 2  (xy slab, pair): forward y and x transforms, multiply by K(G) (and,
+//                         in FP32 form, the G = 0 coefficient taken from FP64
+//                         tile sums), FP64 partial of sum_G K |rho(G)|^2 for
+//                         the exchange energy, inverse x and y transforms; in
+//                         place.
+//   pass 3  (z tile)    : inverse z transform, then the weighted sums over the
+//                         chunk's pairs, kept in registers: per output orbital
+//                         i, sum_j f_j/N_g psi_j v_ij, and in the Hermitian-pair
+//                         mode for the transposed pairs (v_ji = conj v_ij) also
+//                         sum_i f_i/N_g psi_i conj(v_ij) for every j.
+//   pass 4  (Hermitian-pair mode): adds the sums over groups of j that pass 3
+//                         left in the pair buffer to the output orbitals i.
+//
+// A z tile is W consecutive points of the xy plane times all z: small enough
+// that the sums of several orbitals fit the registers of one workgroup, which
+// is why z is the axis of the first and the last transform.  The pair slab
+// makes four trips to memory (written by pass 1, read and written by pass 2,
+// read by pass 3), and v_ij itself is never stored: pass 3 writes one sum per
+// group of GJ pairs of a row, which pass 4 reads back (2/GJ of a slab per pair
+// instead of two).
 //
 // Layout of every grid array: [n2][n1][n0] with x = n0 fastest; orbital blocks
 // are orbital-major.  T is float (complex64 data) or double (complex128).
 #pragma once
-#include <type_traits>
 #include "fft_core.hpp"
 #include "px_internal.hpp"
 
 namespace px {
-
-typedef double vd2 __attribute__((ext_vector_type(2)));
-typedef float vf2 __attribute__((ext_vector_type(2)));
-template <typename T> struct Vec;
-template <> struct Vec<double> { using t = vd2; };
-template <> struct Vec<float> { using t = vf2; };
 
 // Global-memory access through address-space-1 pointers.  The chunk
 // arguments arrive in a struct (or a task table), so the compiler cannot
@@ -43,51 +49,48 @@ template <typename V> __device__ __forceinline__ void gst(V* p, V v) {
   *(PX_GLOBAL V*)p = v;
 }
 
-template <typename T> __device__ __forceinline__ cpx<T> ldg(const cpx<T>* p) {  // streaming load
-  using V = typename Vec<T>::t;
-  V v = __builtin_nontemporal_load((const PX_GLOBAL V*)p);
-  return {v.x, v.y};
+// Element at lane byte offset `off` plus the constant `step` elements from a
+// wave-uniform base, as a raw buffer access: base, size and step are scalar
+// operands and the lane offset has 32 bits, so that a load or store needs no
+// vector address arithmetic (global accesses with such a base took two 64-bit
+// vector additions each, once the compiler had moved the offset's extension
+// out of the loop).
+template <typename T> struct Raw;
+template <> struct Raw<float> { typedef unsigned v __attribute__((ext_vector_type(2))); };
+template <> struct Raw<double> { typedef unsigned v __attribute__((ext_vector_type(4))); };
+template <typename T> __device__ __forceinline__ __amdgpu_buffer_rsrc_t view(const cpx<T>* base) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<cpx<T>*>(base), 0, -1, 0x00020000);
 }
-template <typename T> __device__ __forceinline__ cpx<T> ldc(const cpx<T>* p) {  // cached load
-  using V = typename Vec<T>::t;
-  V v = gld(reinterpret_cast<const V*>(p));
-  return {v.x, v.y};
+template <typename T, int AUX>
+__device__ __forceinline__ cpx<T> ld_raw(__amdgpu_buffer_rsrc_t b, unsigned off, int step) {
+  const int so = step * int(sizeof(cpx<T>));
+  if constexpr (sizeof(T) == 4) return __builtin_bit_cast(cpx<T>, __builtin_amdgcn_raw_buffer_load_b64(b, off, so, AUX));
+  else return __builtin_bit_cast(cpx<T>, __builtin_amdgcn_raw_buffer_load_b128(b, off, so, AUX));
 }
-template <typename T> __device__ __forceinline__ void stg(cpx<T>* p, cpx<T> a) {
-  using V = typename Vec<T>::t;
-  V v;
-  v.x = a.x;
-  v.y = a.y;
-  gst(reinterpret_cast<V*>(p), v);
+template <typename T, int AUX>
+__device__ __forceinline__ void st_raw(__amdgpu_buffer_rsrc_t b, unsigned off, int step, cpx<T> x) {
+  const int so = step * int(sizeof(cpx<T>));
+  using R = typename Raw<T>::v;
+  if constexpr (sizeof(T) == 4) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(R, x), b, off, so, AUX);
+  else __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(R, x), b, off, so, AUX);
 }
-// Streaming store for the pair buffer: the slab is read back only by the
-// next pass, so it should not displace the orbital slabs that the current
-// pass re-reads from the caches.
-template <typename T> __device__ __forceinline__ void stn(cpx<T>* p, cpx<T> a) {
-  using V = typename Vec<T>::t;
-  V v;
-  v.x = a.x;
-  v.y = a.y;
-  __builtin_nontemporal_store(v, (PX_GLOBAL V*)p);
-}
+// Cached, and with the streaming (non-temporal) policy: a pair slab is read
+// once by the next pass, so it should not displace the orbital tiles that the
+// current pass re-reads from the caches.
+template <typename T> __device__ __forceinline__ cpx<T> ldc(__amdgpu_buffer_rsrc_t b, unsigned off, int step) { return ld_raw<T, 0>(b, off, step); }
+template <typename T> __device__ __forceinline__ cpx<T> ldg(__amdgpu_buffer_rsrc_t b, unsigned off, int step) { return ld_raw<T, 2>(b, off, step); }
+template <typename T> __device__ __forceinline__ void stg(__amdgpu_buffer_rsrc_t b, unsigned off, int step, cpx<T> x) { st_raw<T, 0>(b, off, step, x); }
+template <typename T> __device__ __forceinline__ void stn(__amdgpu_buffer_rsrc_t b, unsigned off, int step, cpx<T> x) { st_raw<T, 2>(b, off, step, x); }
 
-// Pair-slab loads of pass 2: each element is read once, so they take the
-// streaming (non-temporal) policy (pass 2 -4.5 % at 96^3 and -5 % at 72^3 in
-// the FP32 form against cached loads; a build may set PX_P2_NT=0 to time
-// those).
-#ifndef PX_P2_NT
-#define PX_P2_NT 1
-#endif
-template <typename T> __device__ __forceinline__ cpx<T> ld_pair2(const cpx<T>* p) {
-  if constexpr (PX_P2_NT != 0) return ldg(p);
-  else return ldc(p);
-}
-
-// Twiddle table: tw[m] = exp(-2 pi i m / N) from the compile-time roots
-// (FP64, about one ulp) rounded to T; copied into LDS by each workgroup.
-template <typename T, int N, int NT> __device__ __forceinline__ void fill_twiddles(cpx<T>* tw) {
+// Twiddle table of a second stage of span NS: t[r NS + k] = exp(-2 pi i r k / N)
+// from the compile-time roots (FP64, about one ulp) rounded to T; written into
+// LDS by each workgroup.
+template <typename T, int N, int NS, int NT> __device__ __forceinline__ void fill_stage_table(cpx<T>* t) {
   constexpr const RootTable<N>& tab = kRoots<N>;
-  for (int m = threadIdx.x; m < N; m += NT) tw[m] = {T(tab.c[m]), T(-tab.s[m])};
+  for (int m = threadIdx.x; m < N; m += NT) {
+    const int e = (m / NS) * (m % NS);  // < N
+    t[m] = {T(tab.c[e]), T(-tab.s[e])};
+  }
 }
 
 // One DPP step on an FP64 value (both 32-bit halves moved with the same
@@ -124,757 +127,23 @@ __device__ __forceinline__ double wave_sum(double v) {
   return __builtin_bit_cast(double, (static_cast<unsigned long long>(hi) << 32) | lo);
 }
 
-// Waves per SIMD that a CU could hold given the LDS of one workgroup (and at
-// most `cap`): used as the kernel's occupancy target, so that the register
-// allocation does not become the tighter limit.  Pass 2 in the FP32 form at
-// 40^3 and 64^3 gains from it (-22 %, -7 %; cap 6 keeps it free of spills);
-// elsewhere it did not help (32^3 got slower) and the cap is 1 (no target).
-template <typename T, int N> constexpr int pass2_wave_cap() {
-#if defined(PX_SH_CAP2)
-  if (N == 90 || N == 120) return PX_SH_CAP2;
-#endif
-  // 90 and 120 occur as z lengths of the non-cubic grids only: FP32 pass 2 at
-  // 60 x 90 x 120 with two 768-thread workgroups per CU instead of one,
-  // 3.42 -> 2.88 ms per 1,024-pair launch
-  return sizeof(T) == 4 && (N == 40 || N == 64 || N == 90 || N == 120) ? 6 : 1;
-}
+
+// Occupancy target of a kernel: the waves per SIMD of a CU that holds as many
+// workgroups of nt threads and lds_bytes of LDS as fit, at most cap, so that
+// the register allocation does not become the tighter limit.  A workgroup
+// takes ceil(waves / 4) wave slots on every SIMD (counters: six-wave
+// workgroups with registers for five waves per SIMD ran two per CU, not three).
 constexpr int lds_waves_per_simd(int lds_bytes, int nt, int cap) {
-  const int waves = (nt + 63) / 64;
+  const int per = (nt + 255) / 256;
   int wgs = (160 * 1024) / lds_bytes;
-  if (wgs * waves > 32) wgs = 32 / waves;
-  const int w = (wgs * waves + 3) / 4;
-  return w < 1 ? 1 : (w > cap ? cap : w);
+  while (wgs > 1 && wgs * per > cap) --wgs;
+  const int w = wgs * per;
+  return w > 8 ? 8 : w;
 }
+constexpr int round64(int n) { return (n + 63) / 64 * 64; }
+// Workgroup size for the register allocation: whole waves on every SIMD.
+constexpr int round256(int n) { return (n + 255) / 256 * 256; }
 
-// Whether two slab buffers (ping-pong) fit in LDS next to the small tables.
-template <typename T, int N0, int N1> constexpr bool pingpong_fits() {
-  return 2 * N1 * (N0 + 1) * int(sizeof(cpx<T>)) <= 150 * 1024;
-}
-
-// Workgroups of nt threads and lds bytes that a CU can hold (LDS and waves).
-constexpr int wgs_per_cu(int lds_bytes, int nt) {
-  const int cap = 32 / ((nt + 63) / 64);
-  const int w = (160 * 1024) / lds_bytes;
-  return w < cap ? w : cap;
-}
-// Whether a workgroup's LDS can grow from `base` to `with` bytes without
-// lowering the number of workgroups that a CU can hold.  Used for the
-// per-thread partial sums that a few waves add up after a barrier (one wave
-// per sum instead of a wave reduction in every wave).
-constexpr bool lds_growth_free(int base, int with, int nt) {
-  return with <= 160 * 1024 && wgs_per_cu(with, nt) >= wgs_per_cu(base, nt);
-}
-template <typename T, int N0, int N1, int NT> constexpr bool g0_lds_fits() {
-  constexpr int nw = (NT + 63) / 64;
-  constexpr int sl = N1 * (N0 + 1) * int(sizeof(cpx<T>));
-  constexpr int base = (pingpong_fits<T, N0, N1>() ? 2 : 1) * sl + (N0 + N1) * int(sizeof(cpx<T>)) + 3 * nw * 8;
-  return lds_growth_free(base, base - 3 * nw * 8 + 3 * NT * int(sizeof(T)), NT);
-}
-template <typename T, int N0, int N2, int NT, bool G0> constexpr bool ex_lds_fits() {
-  constexpr int nw = (NT + 63) / 64;
-  constexpr int base = (N2 * (N0 + 1) + N2) * int(sizeof(cpx<T>)) + 2 * nw * 8;
-  return lds_growth_free(base, base - 2 * nw * 8 + (G0 ? 2 : 1) * NT * 8, NT);
-}
-
-// Branch-free gather of the R inputs of every butterfly slot of a stage whose
-// reads are x[j + r*N/R] along the lines of geometry G: slot indices past the
-// last butterfly are clamped to it (loaded, never stored), so all loads of a
-// slab issue back to back and stay in flight across the LDS stages that follow.
-template <typename T, class G, int R, int NT, int BPT, class F>
-__device__ __forceinline__ void gather(cpx<T> (&v)[BPT][R], F&& load) {
-  constexpr int NB = G::nl * (G::n / R);
-#pragma unroll
-  for (int k = 0; k < BPT; ++k) {
-    int b = threadIdx.x + k * NT;
-    if (NB % NT != 0) b = b < NB ? b : NB - 1;
-    int line, j;
-    decode<G, R>(b, line, j);
-#pragma unroll
-    for (int r = 0; r < R; ++r) v[k][r] = load(line, j + r * (G::n / R));
-  }
-}
-
-// The same for kernels without prefetch: a wave whose slots all lie past the
-// last butterfly issues no loads at all (the address unit is the bottleneck
-// of such kernels; their slots are never used).
-template <typename T, class G, int R, int NT, int BPT, class F>
-__device__ __forceinline__ void gather_live(cpx<T> (&v)[BPT][R], F&& load) {
-  constexpr int NB = G::nl * (G::n / R);
-  const int wave0 = __builtin_amdgcn_readfirstlane(threadIdx.x & ~63);
-#pragma unroll
-  for (int k = 0; k < BPT; ++k) {
-    if (NB % NT != 0 && wave0 + k * NT >= NB) continue;
-    int b = threadIdx.x + k * NT;
-    if (NB % NT != 0) b = b < NB ? b : NB - 1;
-    int line, j;
-    decode<G, R>(b, line, j);
-#pragma unroll
-    for (int r = 0; r < R; ++r) v[k][r] = load(line, j + r * (G::n / R));
-  }
-}
-
-// ============================================================== pass 1
-// PF: prefetch the next density orbital's slab while the current one is
-// transformed.  With two slab buffers in LDS (ping-pong, PP) every stage is
-// out of place and the buffers swap roles each pair, so a slab costs three
-// barriers; otherwise the middle stages run in place (two barriers each).
-template <typename T, int N0, int N1, int NT, bool G0, bool PF, bool PP>
-__global__ __launch_bounds__(NT) void pass1_fwd_xy(ChunkArgs a0, const ChunkArgs* tasks) {
-  static_assert(!PP || pingpong_fits<T, N0, N1>(), "two slabs do not fit in LDS");
-  const ChunkArgs a = chunk_args(a0, tasks);
-  if (int(blockIdx.y) >= a.ic) return;
-  constexpr int P0 = N0 + 1;  // odd row pitch: no bank conflicts on stride-R writes
-  constexpr int SL = N1 * P0;
-  __shared__ cpx<T> lds[PP ? 2 * SL : SL];
-  __shared__ cpx<T> tw0[N0];
-  __shared__ cpx<T> tw1[N1];
-  using GX = Lines<N0, N1, P0, 1, false>;  // rows: contiguous lines
-  using GY = Lines<N1, N0, 1, P0, true>;   // columns: strided lines
-  constexpr int NSX = Plan<N0>::nst, NSY = Plan<N1>::nst;
-  static_assert(!PP || (NSX == 2 && NSY == 2), "ping-pong path assumes two-stage plans");
-  // x stages in the reversed radix order: the first stage writes LDS at a
-  // stride of its radix along a line, and the plans' later radices are the
-  // ones that spread such writes over the banks (9 before 8 at 72^3)
-  using X0 = StageOf<N0, 0, true>;
-  using X1 = StageOf<N0, 1, true>;
-  using Y0 = StageOf<N1, 0, false>;
-  using YL = StageOf<N1, NSY - 1, false>;
-  constexpr int NB0 = N1 * (N0 / X0::R), BPT0 = (NB0 + NT - 1) / NT;
-  constexpr int NBL = N0 * (N1 / YL::R), BPTL = (NBL + NT - 1) / NT;
-  // G = 0 sums: with GL every thread leaves its FP32 partials in LDS and a
-  // few waves add them in FP64 after the barrier that follows the first
-  // stage (one wave per sum instead of a wave reduction in every wave: -6 %
-  // pass time at 72^3); otherwise each wave reduces its own partials
-  constexpr int NW = NT / 64;
-  constexpr bool GL = G0 && BPT0 == 1 && NT % 64 == 0 && g0_lds_fits<T, N0, N1, NT>();
-  __shared__ T gpart[GL ? 3 * NT : 1];
-  __shared__ double red[GL || !G0 ? 1 : 3][NW];
-
-  fill_twiddles<T, N0, NT>(tw0);
-  fill_twiddles<T, N1, NT>(tw1);
-  const int z = blockIdx.x, ii = blockIdx.y;
-  const int jend = a.tri ? ii + 1 : a.jc;  // pairs jj < jend of row ii
-  const size_t slab = size_t(N0) * N1;
-  const size_t ng = slab * a.n2;
-  const cpx<T>* phi = reinterpret_cast<const cpx<T>*>(a.phi) + size_t(a.i0 + ii) * ng + z * slab;
-  const cpx<T>* psi0 = reinterpret_cast<const cpx<T>*>(a.psi) + size_t(a.j0) * ng + z * slab;
-  const int tid = threadIdx.x;
-
-  cpx<T> ph[BPT0][X0::R], nx[BPT0][X0::R];
-  if constexpr (PF) {
-    gather<T, GX, X0::R, NT>(ph, [&](int line, int e) { return ldc(phi + unsigned(line * N0 + e)); });
-    gather<T, GX, X0::R, NT>(nx, [&](int line, int e) { return ldc(psi0 + unsigned(line * N0 + e)); });
-  }
-  __syncthreads();
-
-  for (int jj = 0; jj < jend; ++jj) {
-    cpx<T>* A = lds + (PP ? (jj & 1) * SL : 0);
-    cpx<T>* B = lds + (PP ? (1 - (jj & 1)) * SL : 0);
-    cpx<T> cu[BPT0][X0::R];
-    if constexpr (PF) {
-#pragma unroll
-      for (int k = 0; k < BPT0; ++k)
-#pragma unroll
-        for (int r = 0; r < X0::R; ++r) cu[k][r] = nx[k][r];
-      if (jj + 1 < jend) {
-        const cpx<T>* pn = psi0 + size_t(jj + 1) * ng;
-        gather<T, GX, X0::R, NT>(nx, [&](int line, int e) { return ldc(pn + unsigned(line * N0 + e)); });
-      }
-    } else {
-      const cpx<T>* pc = psi0 + size_t(jj) * ng;
-      gather<T, GX, X0::R, NT>(cu, [&](int line, int e) { return ldc(pc + unsigned(line * N0 + e)); });
-      gather<T, GX, X0::R, NT>(ph, [&](int line, int e) { return ldc(phi + unsigned(line * N0 + e)); });
-    }
-    const int p = ii * a.jc + jj;
-    double sre = 0.0, sim = 0.0, sen = 0.0;
-    T gre = T(0), gim = T(0), gen = T(0);
-    // first x stage from registers: product, radix butterfly, LDS
-#pragma unroll
-    for (int k = 0; k < BPT0; ++k) {
-      const int b = tid + k * NT;
-      const bool valid = NB0 % NT == 0 || b < NB0;
-      int line, j;
-      decode<GX, X0::R>(valid ? b : 0, line, j);
-      cpx<T> v[X0::R];
-      // G = 0 slab sums (FP32 form): the thread's few products are summed in
-      // FP32, the partials in FP64.  These are the transform's own inputs;
-      // with random rounding the partial sums add about 1e-10 relative to the
-      // coefficient of a diagonal pair, far below the FP32 transform's error.
-      T fen = T(0);
-#pragma unroll
-      for (int r = 0; r < X0::R; ++r) {
-        v[r] = cmulc(cu[k][r], ph[k][r]);
-        if (G0) fen += v[r].x * v[r].x + v[r].y * v[r].y;
-      }
-      dft<T, X0::R, false>(v);
-      // the butterfly's DC output is the FP32 sum of its R inputs
-      const T fre = v[0].x, fim = v[0].y;
-      if (G0 && valid) {
-        if constexpr (GL) {
-          gre = fre;
-          gim = fim;
-          gen = fen;
-        } else {
-          sre += double(fre);
-          sim += double(fim);
-          sen += double(fen);
-        }
-      }
-      if (valid) {
-#pragma unroll
-        for (int r = 0; r < X0::R; ++r) A[line * P0 + out_pos<X0::R, 1>(j, r)] = v[r];
-      }
-    }
-    if constexpr (GL) {
-      gpart[tid] = gre;
-      gpart[NT + tid] = gim;
-      gpart[2 * NT + tid] = gen;
-    } else if constexpr (G0) {
-      sre = wave_sum(sre);
-      sim = wave_sum(sim);
-      sen = wave_sum(sen);
-      if ((tid & 63) == 0) {
-        red[0][tid >> 6] = sre;
-        red[1][tid >> 6] = sim;
-        red[2][tid >> 6] = sen;
-      }
-    }
-    __syncthreads();
-    if constexpr (GL) {
-      // sum c (re, im, energy) is added by wave c mod NW; the partials are
-      // read before this wave reaches the next barrier, so the next pair
-      // cannot overwrite them earlier
-      const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-      double* g = reinterpret_cast<double*>(a.g0 + size_t(p) * a.n2 + z);
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        if (w == c % NW) {
-          double sc = 0.0;
-#pragma unroll
-          for (int q = 0; q < NW; ++q) sc += double(gpart[c * NT + q * 64 + (tid & 63)]);
-          sc = wave_sum(sc);
-          if ((tid & 63) == 0) gst(g + c, sc);
-        }
-      }
-    } else if constexpr (G0) {
-      if (tid == 0) {
-        double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-#pragma unroll
-        for (int w = 0; w < NW; ++w) {
-          s0 += red[0][w];
-          s1 += red[1][w];
-          s2 += red[2][w];
-        }
-        double* g = reinterpret_cast<double*>(a.g0 + size_t(p) * a.n2 + z);
-        gst(g, s0);
-        gst(g + 1, s1);
-        gst(g + 2, s2);
-      }
-    }
-    if constexpr (PP) {
-      stage_pp<T, GX, X1::R, X1::NS, false, NT>(A, B, tw0);
-      __syncthreads();
-      stage_pp<T, GY, Y0::R, Y0::NS, false, NT>(B, A, tw1);
-      __syncthreads();
-    } else {
-      stages_lds<T, GX, false, NT, 1, NSX, true>(A, tw0);
-      stages_lds<T, GY, false, NT, 0, NSY - 1>(A, tw1);
-    }
-    // last y stage: LDS -> global pair buffer
-    cpx<T>* out = reinterpret_cast<cpx<T>*>(a.t) + size_t(p) * ng + z * slab;
-#pragma unroll
-    for (int k = 0; k < BPTL; ++k) {
-      const int b = tid + k * NT;
-      if (NBL % NT == 0 || b < NBL) {
-        int line, j;
-        decode<GY, YL::R>(b, line, j);
-        cpx<T> v[YL::R];
-#pragma unroll
-        for (int r = 0; r < YL::R; ++r) v[r] = A[line + (j + r * (N1 / YL::R)) * P0];
-        twiddle<T, N1, YL::R, YL::NS, false>(v, j, tw1);
-        dft<T, YL::R, false>(v);
-#pragma unroll
-        for (int r = 0; r < YL::R; ++r) stn(out + unsigned(line + (j + r * (N1 / YL::R)) * N0), v[r]);
-      }
-    }
-    if constexpr (!PP) __syncthreads();
-  }
-}
-
-// ============================================================== pass 2
-// Plane tile (y, pair group) of a pass-2 workgroup in a grid of n1 x groups
-// (with XS x-sections per plane, "y" here is y * XS + section).  Workgroups
-// go to the 8 XCDs in turn by linear id; for n1 a multiple of 8, XCD x takes
-// the contiguous tiles [x n1/8, (x+1) n1/8), so that the cache lines that
-// neighbouring tiles share at the ends of their rows are fetched through one
-// L2 instead of two.  The set of tiles in flight is unchanged.  Otherwise,
-// when n1 x groups is a multiple of 8, XCD x takes the contiguous eighth
-// [x T, (x+1) T) of the tiles in pair-major order (T = n1 x groups / 8): every
-// pair's planes then go through one L2, and the XCDs work on different pairs.
-// (The plane-major form stays where both apply: pair-major was no faster at
-// 72^3 and 96^3 and 6 % slower in pass 2 at 64^3.)
-#ifndef PX_PLANE_MAP
-#define PX_PLANE_MAP 1
-#endif
-__device__ __forceinline__ void plane_tile(int& y, int& g) {
-  const int ny = int(gridDim.x);
-  const int b = int(blockIdx.x) + ny * int(blockIdx.y);
-  if (ny % 8 == 0) {
-    const int k = b >> 3, per = ny >> 3;
-    y = (b & 7) * per + k % per;
-    g = k / per;
-  } else if (PX_PLANE_MAP && (ny * int(gridDim.y)) % 8 == 0) {
-    const int t = (ny * int(gridDim.y)) >> 3;
-    const int idx = (b & 7) * t + (b >> 3);
-    y = idx % ny;
-    g = idx / ny;
-  } else {
-    y = blockIdx.x;
-    g = blockIdx.y;
-  }
-}
-
-// One workgroup takes the same tile of a y-plane of PQ consecutive pairs:
-// the kernel values of the tile are loaded once and, with PF, the next pair's
-// tile is in flight while the current one is transformed.  A tile is x-section
-// xs of XS: the NX = N0/XS z-lines x in [xs NX, (xs+1) NX) of the plane (XS > 1
-// gives more, smaller workgroups per CU).  Energy partials go to slot
-// y * XS + xs of the pair (N1 * XS slots per pair).
-template <typename T, int N0, int N1, int N2, int NT, bool G0, bool EX, int PQ, bool PF, int XS>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(
-    lds_waves_per_simd(N2 * (N0 / XS + 1) * int(sizeof(cpx<T>)) + 1024, NT, pass2_wave_cap<T, N2>()))))
-void pass2_z_kernel(ChunkArgs a0, const ChunkArgs* tasks) {
-  static_assert(N0 % XS == 0, "x-sections must divide the plane");
-  constexpr int NX = N0 / XS;
-  const ChunkArgs a = chunk_args(a0, tasks);
-  // pairs q in [qbeg, qend) of the chunk; pair q owns slot pair_slot(a, q)
-  const int np = chunk_pairs(a);
-  int yt, grp;
-  plane_tile(yt, grp);
-  const int y = yt / XS, xs = yt % XS, x0 = xs * NX;
-  const int qbeg = grp * PQ;
-  if (qbeg >= np) return;
-  const int qend = qbeg + PQ < np ? qbeg + PQ : np;
-  constexpr int P0 = NX + 1;
-  // energy partials: as the G = 0 sums of pass 1 (EL: per thread in LDS, one
-  // wave per sum), else a wave reduction in every wave
-  constexpr int NW = NT / 64, NE = G0 ? 2 : 1;
-  constexpr bool EL = EX && NT % 64 == 0 && ex_lds_fits<T, NX, N2, NT, G0>();
-  __shared__ cpx<T> lds[N2 * P0];
-  __shared__ cpx<T> tw2[N2];
-  __shared__ double red[EL ? 1 : 2][NW];
-  __shared__ double epart[EL ? NE * NT : 1];
-  using GZ = Lines<N2, NX, 1, P0, true>;  // tile [z][x], lines along z
-  constexpr int NS = Plan<N2>::nst;
-  using F0 = StageOf<N2, 0, false>;
-  using FL = StageOf<N2, NS - 1, false>;
-  using I0 = StageOf<N2, 0, true>;
-  using IL = StageOf<N2, NS - 1, true>;
-  static_assert(I0::R == FL::R, "inverse must start with the forward's last radix");
-  constexpr int NB0 = NX * (N2 / F0::R), BPT0 = (NB0 + NT - 1) / NT;
-  constexpr int NBL = NX * (N2 / FL::R), BPTL = (NBL + NT - 1) / NT;
-  constexpr int NBI = NX * (N2 / IL::R), BPTI = (NBI + NT - 1) / NT;
-
-  const size_t slab = size_t(N0) * N1;
-  cpx<T>* const buf0 = reinterpret_cast<cpx<T>*>(a.t) + size_t(y) * N0 + x0;
-  // kernel values: the FP32 copy in the FP32 form (G = 0 comes from kern)
-  using KT = typename std::conditional<G0, float, double>::type;
-  const KT* kern = (G0 ? reinterpret_cast<const KT*>(a.kern32) : reinterpret_cast<const KT*>(a.kern)) +
-                   size_t(y) * N0 + x0;
-  const int tid = threadIdx.x;
-
-  // global loads first: the first plane (at stage-0 positions) and the kernel
-  // values at the positions the last forward stage produces
-  cpx<T> nx[BPT0][F0::R];
-  gather_live<T, GZ, F0::R, NT>(nx, [&](int line, int e) {
-    return ld_pair2(buf0 + size_t(pair_slot(a, qbeg)) * slab * N2 + unsigned(e * int(slab) + line));
-  });
-  KT kv[BPTL][FL::R];
-  const int wave0 = __builtin_amdgcn_readfirstlane(tid & ~63);
-#pragma unroll
-  for (int k = 0; k < BPTL; ++k) {
-    if (NBL % NT != 0 && wave0 + k * NT >= NBL) continue;  // no live slot in this wave
-    int b = tid + k * NT;
-    if (NBL % NT != 0) b = b < NBL ? b : NBL - 1;
-    int line, j;
-    decode<GZ, FL::R>(b, line, j);
-#pragma unroll
-    for (int r = 0; r < FL::R; ++r) kv[k][r] = gld(kern + unsigned((j + r * (N2 / FL::R)) * int(slab) + line));
-  }
-  fill_twiddles<T, N2, NT>(tw2);
-  for (int q = qbeg; q < qend; ++q) {
-  const int p = pair_slot(a, q);
-  cpx<T>* const buf = buf0 + size_t(p) * slab * N2;
-  cpx<T> v0[BPT0][F0::R];
-  if (PQ == 1 || PF || q == qbeg) {
-#pragma unroll
-    for (int k = 0; k < BPT0; ++k)
-#pragma unroll
-      for (int r = 0; r < F0::R; ++r) v0[k][r] = nx[k][r];
-  } else {
-    gather_live<T, GZ, F0::R, NT>(v0, [&](int line, int e) { return ld_pair2(buf + unsigned(e * int(slab) + line)); });
-  }
-  if (PF && q + 1 < qend) {
-    cpx<T>* const bn = buf0 + size_t(pair_slot(a, q + 1)) * slab * N2;
-    gather<T, GZ, F0::R, NT>(nx, [&](int line, int e) { return ld_pair2(bn + unsigned(e * int(slab) + line)); });
-  }
-  if (q > qbeg) __syncthreads();  // the previous pair's last stage has read LDS
-#pragma unroll
-  for (int k = 0; k < BPT0; ++k) {
-    const int b = tid + k * NT;
-    if (NB0 % NT == 0 || b < NB0) {
-      int line, j;
-      decode<GZ, F0::R>(b, line, j);
-      dft<T, F0::R, false>(v0[k]);
-#pragma unroll
-      for (int r = 0; r < F0::R; ++r) lds[out_pos<F0::R, 1>(j, r) * P0 + line] = v0[k][r];
-    }
-  }
-  __syncthreads();
-  stages_lds<T, GZ, false, NT, 1, NS - 1>(lds, tw2);
-  // last forward stage into registers, kernel multiply, first inverse stage
-  cpx<T> v[BPTL][FL::R];
-  double ex = 0.0, en = 0.0, ex0 = 0.0;  // FP32 form: sum_{G!=0} K|rho|^2, sum_{G!=0} |rho|^2, G = 0 term
-#pragma unroll
-  for (int k = 0; k < BPTL; ++k) {
-    const int b = tid + k * NT;
-    if (NBL % NT == 0 || b < NBL) {
-      int line, j;
-      decode<GZ, FL::R>(b, line, j);
-#pragma unroll
-      for (int r = 0; r < FL::R; ++r) v[k][r] = lds[(j + r * (N2 / FL::R)) * P0 + line];
-      twiddle<T, N2, FL::R, FL::NS, false>(v[k], j, tw2);
-      dft<T, FL::R, false>(v[k]);
-      T fex = T(0), fen = T(0);  // FP32 form: the thread's partial energy sums
-#pragma unroll
-      for (int r = 0; r < FL::R; ++r) {
-        const int kz = j + r * (N2 / FL::R);
-        const double kg = kv[k][r];
-        cpx<T> c = v[k][r];
-        if (G0 && y == 0 && x0 + line == 0 && kz == 0) {
-          const double k0 = gld(a.kern);
-          // G = 0 from the FP64 slab sums of pass 1
-          double s0 = 0.0, s1 = 0.0;
-          const G0Part* g = a.g0 + size_t(p) * N2;
-          for (int zz = 0; zz < N2; ++zz) {
-            s0 += gld(&g[zz].re);
-            s1 += gld(&g[zz].im);
-          }
-          if (EX) ex0 = k0 * (s0 * s0 + s1 * s1);
-          v[k][r] = {T(k0 * s0), T(k0 * s1)};
-        } else if constexpr (G0) {
-          // FP32 form: K(G) rounded to FP32; the energy terms of the
-          // thread's few values are summed in FP32, the partials in FP64
-          // (random rounding: about 1e-10 relative on a pair's energy)
-          const T kf = kv[k][r];
-          const T c2 = c.x * c.x + c.y * c.y;
-          if (EX) {
-            fex += kf * c2;
-            fen += c2;
-          }
-          v[k][r] = {kf * c.x, kf * c.y};
-        } else {
-          const double c2 = double(c.x) * double(c.x) + double(c.y) * double(c.y);
-          if (EX) ex += kg * c2;
-          v[k][r] = {T(kg * double(c.x)), T(kg * double(c.y))};
-        }
-      }
-      if constexpr (G0 && EX) {
-        ex += double(fex);
-        en += double(fen);
-      }
-    }
-  }
-  if constexpr (EL) {
-    epart[tid] = ex;
-    if constexpr (G0) epart[NT + tid] = en;
-  } else if constexpr (EX) {
-    ex = wave_sum(ex);
-    if ((tid & 63) == 0) red[0][tid >> 6] = ex;
-    if constexpr (G0) {
-      // the G = 0 term lives in thread 0 (slot 0 holds line 0, kz = 0)
-      en = wave_sum(en);
-      if ((tid & 63) == 0) red[1][tid >> 6] = en;
-    }
-  }
-  __syncthreads();  // every thread is done reading LDS before it is overwritten
-#pragma unroll
-  for (int k = 0; k < BPTL; ++k) {
-    const int b = tid + k * NT;
-    if (NBL % NT == 0 || b < NBL) {
-      int line, j;
-      decode<GZ, I0::R>(b, line, j);
-      dft<T, I0::R, true>(v[k]);
-#pragma unroll
-      for (int r = 0; r < I0::R; ++r) lds[out_pos<I0::R, 1>(j, r) * P0 + line] = v[k][r];
-    }
-  }
-  __syncthreads();
-  if constexpr (EL) {
-    // sum c is added by wave c mod NW, which reads the partials before it
-    // reaches the next barrier; the G = 0 term lives in thread 0
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    double* e = G0 ? a.expart + (size_t(p) * N1 * XS + yt) * 3 : a.expart + size_t(p) * N1 * XS + yt;
-#pragma unroll
-    for (int c = 0; c < NE; ++c) {
-      if (w == c % NW) {
-        double sc = 0.0;
-#pragma unroll
-        for (int q = 0; q < NW; ++q) sc += epart[c * NT + q * 64 + (tid & 63)];
-        sc = wave_sum(sc);
-        if ((tid & 63) == 0) gst(e + c, sc);
-      }
-    }
-    if (G0 && tid == 0) gst(e + 2, ex0);
-  } else if constexpr (EX) {
-    if (tid == 0) {
-      double s2 = 0.0, s3 = 0.0;
-      const double s4 = ex0;
-#pragma unroll
-      for (int w = 0; w < NT / 64; ++w) {
-        s2 += red[0][w];
-        if (G0) s3 += red[1][w];
-      }
-      if constexpr (G0) {
-        double* e = a.expart + (size_t(p) * N1 * XS + yt) * 3;
-        gst(e, s2);
-        gst(e + 1, s3);
-        gst(e + 2, s4);
-      } else {
-        gst(a.expart + size_t(p) * N1 * XS + yt, s2);
-      }
-    }
-  }
-  stages_lds<T, GZ, true, NT, 1, NS - 1>(lds, tw2);
-  // last inverse stage back to global, in place
-#pragma unroll
-  for (int k = 0; k < BPTI; ++k) {
-    const int b = tid + k * NT;
-    if (NBI % NT == 0 || b < NBI) {
-      int line, j;
-      decode<GZ, IL::R>(b, line, j);
-      cpx<T> w[IL::R];
-#pragma unroll
-      for (int r = 0; r < IL::R; ++r) w[r] = lds[(j + r * (N2 / IL::R)) * P0 + line];
-      twiddle<T, N2, IL::R, IL::NS, true>(w, j, tw2);
-      dft<T, IL::R, true>(w);
-#pragma unroll
-      for (int r = 0; r < IL::R; ++r) stn(buf + unsigned((j + r * (N2 / IL::R)) * int(slab) + line), w[r]);
-    }
-  }
-  }  // pairs
-}
-
-// Pass 3 with PF: also prefetch the next psi_j slab (a second register set),
-// FP32 only.  Measured on the same box: 72^3 -4 %, 32^3 and 40^3 -1 to -2 %;
-// 48^3 +11 % and 64^3 +7 % (the larger register set costs occupancy there).
-template <typename T, int N> constexpr bool psi_prefetch3_for() {
-  return sizeof(T) == 4 && (N == 72 || N <= 40);
-}
-
-// ============================================================== pass 3
-// PF: prefetch the next pair slab and the next psi_j slab during the transform.
-// PP as in pass 1.
-// SV: symmetric mode, keep N_g v_ij in the pair slab for pass 4 (a compile-time
-// switch, so that the loop has the same stores on every path).
-template <typename T, int N0, int N1, int NT, bool PF, bool SV, bool PP>
-__global__ __launch_bounds__(NT) void pass3_inv_xy_acc(ChunkArgs a0, const ChunkArgs* tasks) {
-  static_assert(!PP || pingpong_fits<T, N0, N1>(), "two slabs do not fit in LDS");
-  const ChunkArgs a = chunk_args(a0, tasks);
-  if (int(blockIdx.y) >= a.ic) return;
-  constexpr int P0 = N0 + 1;
-  constexpr int SL = N1 * P0;
-  __shared__ cpx<T> lds[PP ? 2 * SL : SL];
-  __shared__ cpx<T> tw0[N0];
-  __shared__ cpx<T> tw1[N1];
-  using GX = Lines<N0, N1, P0, 1, false>;
-  using GY = Lines<N1, N0, 1, P0, true>;
-  constexpr int NSX = Plan<N0>::nst, NSY = Plan<N1>::nst;
-  static_assert(!PP || (NSX == 2 && NSY == 2), "ping-pong path assumes two-stage plans");
-  using X0 = StageOf<N0, 0, true>;
-  using X1 = StageOf<N0, 1, true>;
-  // FP32: y stages in the order whose last radix leaves fewer butterflies
-  // per thread, since the last stage's values stay in registers for the
-  // accumulation (96: 12 last, one butterfly per thread instead of two; 6 %
-  // faster).  Ties, and the FP64 form (slower that way at 96), keep the
-  // reversed order.
-  constexpr int RF = StageOf<N1, NSY - 1, false>::R, RR = StageOf<N1, NSY - 1, true>::R;
-  constexpr bool YREV = sizeof(T) == 8 ||
-                        (N0 * (N1 / RR) + NT - 1) / NT <= (N0 * (N1 / RF) + NT - 1) / NT;
-  using Y0 = StageOf<N1, 0, YREV>;
-  using YL = StageOf<N1, NSY - 1, YREV>;
-  constexpr int NB0 = N1 * (N0 / X0::R), BPT0 = (NB0 + NT - 1) / NT;
-  constexpr int NBL = N0 * (N1 / YL::R), BPTL = (NBL + NT - 1) / NT;
-  constexpr bool PSI = PF && psi_prefetch3_for<T, N0>();
-
-  fill_twiddles<T, N0, NT>(tw0);
-  fill_twiddles<T, N1, NT>(tw1);
-  const int z = blockIdx.x, ii = blockIdx.y;
-  const int jend = a.tri ? ii + 1 : a.jc;  // pairs jj < jend of row ii
-  const size_t slab = size_t(N0) * N1;
-  const size_t ng = slab * a.n2;
-  const int tid = threadIdx.x;
-  const cpx<T>* t0 = reinterpret_cast<const cpx<T>*>(a.t) + size_t(ii * a.jc) * ng + z * slab;
-  const cpx<T>* psi0 = reinterpret_cast<const cpx<T>*>(a.psi) + size_t(a.j0) * ng + z * slab;
-  auto tload = [](const cpx<T>* base) {
-    return [base](int line, int e) { return ldg(base + unsigned(line * N0 + e)); };
-  };
-  auto pload = [](const cpx<T>* base) {
-    return [base](int line, int e) { return ldc(base + unsigned(line + e * N0)); };
-  };
-  cpx<T>* const outz = reinterpret_cast<cpx<T>*>(a.out) + size_t(a.i0 + ii) * ng + z * slab;
-  cpx<T> acc[BPTL][YL::R];
-#pragma unroll
-  for (int k = 0; k < BPTL; ++k)
-#pragma unroll
-    for (int r = 0; r < YL::R; ++r) acc[k][r] = {T(0), T(0)};
-  auto weight = [&](int jj) { return T(gld(a.occ + a.j0 + jj) * a.inv_ng); };
-
-  // One pair: inverse x and y transforms of the pair slab held in tc, then
-  // the psi_j-weighted accumulation with the psi_j slab in pc.  With PF the
-  // next pair slab is requested at the start (into tn).  With PSI the next
-  // psi_j slab is requested too (into pn), after the last stage and before
-  // this pair's stores: memory requests complete in order, so the wait for
-  // psi_j then never waits for stores.  Otherwise psi_j is requested at the
-  // start, before the next pair slab, or without PF in the last stage.
-  auto step = [&](int jj, cpx<T>(&tc)[BPT0][X0::R], cpx<T>(&tn)[BPT0][X0::R],
-                  cpx<T>(&pc)[BPTL][YL::R], cpx<T>(&pn)[BPTL][YL::R]) {
-    cpx<T>* A = lds + (PP ? (jj & 1) * SL : 0);
-    cpx<T>* B = lds + (PP ? (1 - (jj & 1)) * SL : 0);
-    const T wj = weight(jj);  // requested before the slabs: waiting for it waits for nothing else
-    // the last pair re-requests its own slabs: the loop stays branch free
-    const int jn = jj + 1 < jend ? jj + 1 : jj;
-    if constexpr (PF) {
-      if constexpr (!PSI) gather<T, GY, YL::R, NT>(pc, pload(psi0 + size_t(jj) * ng));
-      gather<T, GX, X0::R, NT>(tn, tload(t0 + size_t(jn) * ng));
-    }
-#pragma unroll
-    for (int k = 0; k < BPT0; ++k) {
-      const int b = tid + k * NT;
-      if (NB0 % NT == 0 || b < NB0) {
-        int line, j;
-        decode<GX, X0::R>(b, line, j);
-        dft<T, X0::R, true>(tc[k]);
-#pragma unroll
-        for (int r = 0; r < X0::R; ++r) A[line * P0 + out_pos<X0::R, 1>(j, r)] = tc[k][r];
-      }
-    }
-    __syncthreads();
-    if constexpr (PP) {
-      stage_pp<T, GX, X1::R, X1::NS, true, NT>(A, B, tw0);
-      __syncthreads();
-      stage_pp<T, GY, Y0::R, Y0::NS, true, NT>(B, A, tw1);
-      __syncthreads();
-    } else {
-      stages_lds<T, GX, true, NT, 1, NSX>(A, tw0);
-      stages_lds<T, GY, true, NT, 0, NSY - 1, YREV>(A, tw1);
-    }
-    // last stage: slots past the last butterfly repeat it (same values to the
-    // same addresses), so every thread issues the same loads and stores.
-    // Symmetric mode (SV) keeps N_g * v_ij (real space) for the transposed pass.
-    cpx<T>* tv = reinterpret_cast<cpx<T>*>(a.t) + size_t(ii * a.jc + jj) * ng + z * slab;
-    cpx<T> v[BPTL][YL::R];
-#pragma unroll
-    for (int k = 0; k < BPTL; ++k) {
-      int b = tid + k * NT;
-      if (NBL % NT != 0) b = b < NBL ? b : NBL - 1;
-      int line, j;
-      decode<GY, YL::R>(b, line, j);
-      if constexpr (!PF) {
-        const cpx<T>* pj = psi0 + size_t(jj) * ng;
-#pragma unroll
-        for (int r = 0; r < YL::R; ++r) pc[k][r] = ldc(pj + unsigned(line + (j + r * (N1 / YL::R)) * N0));
-      }
-#pragma unroll
-      for (int r = 0; r < YL::R; ++r) v[k][r] = A[line + (j + r * (N1 / YL::R)) * P0];
-      twiddle<T, N1, YL::R, YL::NS, true>(v[k], j, tw1);
-      dft<T, YL::R, true>(v[k]);
-#pragma unroll
-      for (int r = 0; r < YL::R; ++r) {
-        cpx<T> t = cmul(pc[k][r], v[k][r]);
-        acc[k][r].x += wj * t.x;
-        acc[k][r].y += wj * t.y;
-      }
-      if constexpr (SV && !PSI) {
-#pragma unroll
-        for (int r = 0; r < YL::R; ++r) stn(tv + unsigned(line + (j + r * (N1 / YL::R)) * N0), v[k][r]);
-      }
-    }
-    if constexpr (PSI) {
-      gather<T, GY, YL::R, NT>(pn, pload(psi0 + size_t(jn) * ng));
-      if constexpr (SV) {
-#pragma unroll
-        for (int k = 0; k < BPTL; ++k) {
-          int b = tid + k * NT;
-          if (NBL % NT != 0) b = b < NBL ? b : NBL - 1;
-          int line, j;
-          decode<GY, YL::R>(b, line, j);
-#pragma unroll
-          for (int r = 0; r < YL::R; ++r) stn(tv + unsigned(line + (j + r * (N1 / YL::R)) * N0), v[k][r]);
-        }
-      }
-    }
-    if constexpr (!PP) __syncthreads();
-  };
-
-  if constexpr (PF) {
-    // two register sets for the pair slab, used alternately: the next slab
-    // loads into the idle set while the current one is transformed (no
-    // copies between iterations, so the loads stay in flight)
-    cpx<T> tA[BPT0][X0::R], tB[BPT0][X0::R];
-    cpx<T> pA[BPTL][YL::R], pB[PSI ? BPTL : 1][YL::R];
-    gather<T, GX, X0::R, NT>(tA, tload(t0));
-    if constexpr (PSI) gather<T, GY, YL::R, NT>(pA, pload(psi0));
-    __syncthreads();
-    for (int jj = 0; jj < jend; jj += 2) {
-      if constexpr (PSI) {
-        step(jj, tA, tB, pA, pB);
-        if (jj + 1 < jend) step(jj + 1, tB, tA, pB, pA);
-      } else {
-        step(jj, tA, tB, pA, pA);
-        if (jj + 1 < jend) step(jj + 1, tB, tA, pA, pA);
-      }
-    }
-  } else {
-    __syncthreads();
-    for (int jj = 0; jj < jend; ++jj) {
-      cpx<T> tc[BPT0][X0::R];
-      cpx<T> pc[BPTL][YL::R];
-      gather<T, GX, X0::R, NT>(tc, tload(t0 + size_t(jj) * ng));
-      step(jj, tc, tc, pc, pc);
-    }
-  }
-  // one read-modify-write of the output slab, all loads issued before the
-  // first store
-  cpx<T> po[BPTL][YL::R];
-  if (!a.first) gather<T, GY, YL::R, NT>(po, pload(outz));
-#pragma unroll
-  for (int k = 0; k < BPTL; ++k) {
-    const int b = tid + k * NT;
-    if (NBL % NT == 0 || b < NBL) {
-      int line, j;
-      decode<GY, YL::R>(b, line, j);
-#pragma unroll
-      for (int r = 0; r < YL::R; ++r) {
-        const cpx<T> prev = a.first ? cpx<T>{T(0), T(0)} : po[k][r];
-        stg(outz + unsigned(line + (j + r * (N1 / YL::R)) * N0), csub(prev, acc[k][r]));
-      }
-    }
-  }
-}
-
-// ============================================================== pass 3, staged form
-// A workgroup barrier that waits only for this wave's LDS accesses: global ->
-// LDS transfers in flight stay in flight across it.  (The fence of
-// __syncthreads would wait for every outstanding vector memory operation,
-// those transfers included.)  The signal fences keep the compiler from moving
-// memory accesses across it.
-__device__ __forceinline__ void lds_sync() {
-  __atomic_signal_fence(__ATOMIC_SEQ_CST);
-  __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0); vmcnt and expcnt not waited for
-  __builtin_amdgcn_s_barrier();
-  __atomic_signal_fence(__ATOMIC_SEQ_CST);
-}
 // A workgroup barrier after all of this wave's memory operations, global ->
 // LDS transfers included (vmcnt(0) lgkmcnt(0)).
 __device__ __forceinline__ void dma_sync() {
@@ -884,456 +153,755 @@ __device__ __forceinline__ void dma_sync() {
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
 }
 
-// Copies BYTES contiguous bytes (a multiple of 16) from global memory into LDS
-// with 16-byte global -> LDS transfers: wave w moves the 1 KiB pieces w,
-// w + NW, ..., lane l bytes [16 l, 16 l + 16) of each (the LDS destination of
-// a transfer is wave-uniform, its lanes fill consecutive 16-byte slots).
-// Cache-policy bits of the slab transfers (a build may set PX_DMA_AUX to time
-// alternatives).
-#ifndef PX_DMA_AUX
-#define PX_DMA_AUX 2
-#endif
-template <int BYTES, int NT>
-__device__ __forceinline__ void dma_to_lds(const void* src, void* dst) {
-  static_assert(BYTES % 16 == 0, "16-byte pieces");
-  constexpr int NW = NT / 64, NCH = (BYTES + 1023) / 1024;
+// ============================================================== z tiles
+// Geometry of the z-tile passes on an N0 x N1 x N2 grid: W points of the plane
+// (the last tile is short when W does not divide N0 N1: its lanes past the
+// plane load a valid point and store nothing).  A thread holds RS points of a
+// tile, one butterfly of the stage of that radix: the first of the forward and
+// the last of the inverse transform, where the product (pass 1) and the sums
+// (pass 3) happen.  The other stage has RB = N2 / RS.
+template <int N2> constexpr int ztile_radix() {
+  return Plan<N2>::rad[0] == 8 ? Plan<N2>::rad[1] : Plan<N2>::rad[0];
+}
+// Pass 3 in FP64 takes the plan's smaller radix: its GJ + 1 sums of RS points
+// then fit the registers with more columns (96^3: 8 points with GJ = 3 6.4 us a
+// pair in passes 3 and 4, 12 with GJ = 2 8.9).
+template <typename T, int N2> constexpr int ztile_radix3() {
+  constexpr int a = Plan<N2>::rad[0], b = Plan<N2>::rad[1];
+  return sizeof(T) == 4 ? ztile_radix<N2>() : a < b ? a : b;
+}
+template <typename T, int N0, int N1, int N2, int W, int RS_ = ztile_radix<N2>()> struct ZTile {
+  static constexpr int PL = N0 * N1;
+  static constexpr int NTILE = (PL + W - 1) / W;
+  static constexpr bool RAG = PL % W != 0;
+  static_assert(Plan<N2>::nst == 2, "z tiles assume two-stage plans");
+  static constexpr int RS = RS_, RB = N2 / RS;
+  static constexpr bool FWD = Plan<N2>::rad[0] == RS;  // radix order of the forward transform
+  using F0 = StageOf<N2, 0, !FWD>;
+  using FL = StageOf<N2, 1, !FWD>;
+  using I0 = StageOf<N2, 0, FWD>;
+  using IL = StageOf<N2, 1, FWD>;
+  static_assert(F0::R == RS && FL::R == RB && I0::R == RB && IL::R == RS, "stage order");
+  static constexpr int NBS = W * RB;             // butterflies of the radix-RS stage
+  static constexpr int NBB = W * RS;             // and of the radix-RB stage
+  static constexpr int NT = round64(NBS);
+  static constexpr int SB = (NBB + NT - 1) / NT; // slots of a thread in the radix-RB stage
+};
+
+// Tile and row of a workgroup in a grid of tile_grid(NTILE) x rows.  Workgroups
+// go to the 8 XCDs in turn by linear id; XCD x takes the x-th eighth of the
+// tiles, each with its rows one after the other, so that the rows' workgroups,
+// which read the same tiles of the density orbitals, share one L2.  Against
+// workgroups in launch order: pass 1 at 96^3 FP64 5.6 -> 3.2 us a pair, at 72^3
+// FP32 0.87 -> 0.68 (every eighth tile instead of a run of tiles per XCD: up to
+// 10% slower in pass 3).
+constexpr int tile_grid(int ntile) { return (ntile + 7) / 8 * 8; }
+__device__ __forceinline__ void tile_order(int& tile, int& row) {
+  const int nt = int(gridDim.x), nr = int(gridDim.y);
+  const int id = int(blockIdx.x) + int(blockIdx.y) * nt, k = id >> 3;
+  tile = (id & 7) * (nt / 8) + k / nr;
+  row = k % nr;
+}
+
+// ============================================================== pass 1
+// Workgroup = (tile, output orbital i), looping over the chunk's j; the next
+// density orbital's tile is in flight while the current one is transformed.
+// Four waves per SIMD in FP32 (five gave the same, with spills; 120 planes spill
+// with four), FP64 as the registers come out (two).
+template <typename T, int N0, int N1, int N2, int W, bool G0>
+__global__ __launch_bounds__((round256(ZTile<T, N0, N1, N2, W>::NT))) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 1 : N2 > 96 ? 3 : 4)))
+void pass1_z(ChunkArgs a0, const ChunkArgs* tasks) {
+  using Z = ZTile<T, N0, N1, N2, W>;
+  using FL = typename Z::FL;
+  constexpr int NT = Z::NT, RS = Z::RS, RB = Z::RB, PL = Z::PL, NW = NT / 64;
+  const ChunkArgs a = chunk_args(a0, tasks);
+  int tile, ii;
+  tile_order(tile, ii);
+  if (tile >= Z::NTILE || ii >= a.ic) return;
+  __shared__ cpx<T> lds[N2 * W];
+  __shared__ cpx<T> tw[N2];
+  // G = 0 sums: every thread leaves its FP32 partials in LDS and one wave per
+  // sum adds them in FP64 after the barrier that follows the first stage
+  __shared__ T gpart[G0 ? 3 * NT : 1];
+  fill_stage_table<T, N2, FL::NS, NT>(tw);
+  const int tid = threadIdx.x;
+  // the last SW waves add the three G = 0 sums, GPW each
+  constexpr int SW = NW >= 4 ? 3 : 1, GPW = SW == 3 ? 1 : 3;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int t0 = tile * W;
+  const int jend = a.tri ? ii + 1 : a.jc;  // pairs jj < jend of row ii
+  const size_t ng = size_t(PL) * N2;
+  const cpx<T>* phi = reinterpret_cast<const cpx<T>*>(a.phi) + size_t(a.i0 + ii) * ng;
+  const cpx<T>* psi0 = reinterpret_cast<const cpx<T>*>(a.psi) + size_t(a.j0) * ng;
+
+  const bool live0 = Z::NBS % NT == 0 || tid < Z::NBS;
+  const int b0 = live0 ? tid : Z::NBS - 1;  // (threads past the last butterfly repeat it)
+  const int l0 = b0 % W, j0 = b0 / W;
+  const bool in0 = !Z::RAG || t0 + l0 < PL;
+  const unsigned off0 = unsigned(j0 * PL + (in0 ? t0 + l0 : PL - 1)) * unsigned(sizeof(cpx<T>));
+  cpx<T> ph[RS], nx[RS];
+#pragma unroll
+  for (int r = 0; r < RS; ++r) ph[r] = ldc<T>(view(phi), off0, r * RB * PL);
+#pragma unroll
+  for (int r = 0; r < RS; ++r) nx[r] = ldc<T>(view(psi0), off0, r * RB * PL);
+  __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): nothing outstanding when a loop starts
+  __syncthreads();
+
+  // The waves take one of two loops, so that within each every pair issues the
+  // same memory operations: the compiler's wait for the prefetched tile then
+  // counts the stores issued after it instead of waiting for them too.  The
+  // last waves (the fewest butterflies of the last stage) add the G = 0
+  // partials in FP64; lanes past the last butterfly repeat it (the same values
+  // to the same addresses).
+  auto loop = [&](auto slots_c, auto sums_c) {
+    constexpr int SLOTS = decltype(slots_c)::value;
+    constexpr bool SUMS = decltype(sums_c)::value;
+    for (int jj = 0; jj < jend; ++jj) {
+      const int p = ii * a.jc + jj;
+      cpx<T> v[RS];
+      T fen = T(0);
+      // product and first butterfly.  G = 0 (FP32 form): the thread's few
+      // products are summed in FP32 (the butterfly's DC output is that sum), the
+      // partials in FP64.  These are the transform's own inputs; with random
+      // rounding the partial sums add about 1e-10 relative to the coefficient of
+      // a diagonal pair, far below the FP32 transform's error.
+#pragma unroll
+      for (int r = 0; r < RS; ++r) {
+        v[r] = cmulc(nx[r], ph[r]);
+        if (G0) fen += v[r].x * v[r].x + v[r].y * v[r].y;
+      }
+      // the next density orbital's tile (the last pair requests its own again)
+      const auto pn = view(psi0 + size_t(jj + 1 < jend ? jj + 1 : jj) * ng);
+#pragma unroll
+      for (int r = 0; r < RS; ++r) nx[r] = ldc<T>(pn, off0, r * RB * PL);
+      dft<T, RS, false>(v);
+      if constexpr (G0) {
+        const bool cnt = live0 && in0;
+        gpart[tid] = cnt ? v[0].x : T(0);
+        gpart[NT + tid] = cnt ? v[0].y : T(0);
+        gpart[2 * NT + tid] = cnt ? fen : T(0);
+      }
+#pragma unroll
+      for (int r = 0; r < RS; ++r) lds[out_pos<RS, 1>(j0, r) * W + l0] = v[r];
+      lds_sync();
+      if constexpr (G0 && SUMS) {
+        double* g = reinterpret_cast<double*>(a.g0 + size_t(p) * Z::NTILE + tile);
+#pragma unroll
+        for (int k = 0; k < GPW; ++k) {
+          int c = (wave - (NW - SW)) * GPW + k;
+          c = c < 2 ? c : 2;
+          double sc = 0.0;
+#pragma unroll
+          for (int q = 0; q < NW; ++q) sc += double(gpart[c * NT + q * 64 + (tid & 63)]);
+          gst(g + c, wave_sum(sc));  // (every lane, one address)
+        }
+      }
+      const auto out = view(reinterpret_cast<cpx<T>*>(a.t) + size_t(p) * ng);
+#pragma unroll
+      for (int k = 0; k < SLOTS; ++k) {
+        int b = tid + k * NT;
+        if (Z::NBB % NT != 0) b = b < Z::NBB ? b : Z::NBB - 1;
+        const int l1 = b % W, j1 = b / W;
+        cpx<T> u[RB];
+#pragma unroll
+        for (int r = 0; r < RB; ++r) u[r] = lds[(j1 + r * RS) * W + l1];
+        twiddle<T, N2, RB, FL::NS, false>(u, j1, tw);
+        dft<T, RB, false>(u);
+        if (!Z::RAG || t0 + l1 < PL) {
+          const unsigned off1 = unsigned(j1 * PL + t0 + l1) * unsigned(sizeof(cpx<T>));
+#pragma unroll
+          for (int r = 0; r < RB; ++r) stn<T>(out, off1, r * RS * PL, u[r]);
+        }
+      }
+      lds_sync();
+    }
+  };
+  using std::integral_constant;
+  // slots of the waves before and from NW - SW on
+  constexpr int S0 = Z::SB, S1 = NW > SW ? (Z::NBB - (NW - SW) * 64 + NT - 1) / NT : Z::SB;
+  constexpr int S1C = S1 < 0 ? 0 : S1;
+  if (NW > SW && wave < NW - SW) loop(integral_constant<int, S0>{}, integral_constant<bool, false>{});
+  else loop(integral_constant<int, S1C>{}, integral_constant<bool, true>{});
+}
+
+template <typename T, int CFG> constexpr int tile_width() { return ztile_width(sizeof(T) == 4, CFG); }
+// Pass 3 at 96 planes in FP64 takes 512-byte rows (with 256-byte rows 3% more).
+template <typename T, int N2, int CFG> constexpr int tile_width3() {
+  return N2 == 96 && sizeof(T) == 8 ? 32 : tile_width<T, CFG>();
+}
+
+// ============================================================== pass 2
+// Workgroup = the xy slab at kz = blockIdx.x of pq consecutive pairs; the
+// kernel values of the slab are loaded once.  y first and last: a row of the
+// slab is then one contiguous run of lanes for the global loads and stores,
+// and the x lines are read with the line index across lanes (odd row pitch: no
+// bank conflicts in either direction).  The kernel table is [z][x][y] for the
+// same reason.  The inverse x transform starts with the forward's last radix,
+// so the two meet in registers around the kernel multiply.
+template <typename T, int N0, int N1> struct Slab {
+  static constexpr int P0 = N0 + 1;
+  static constexpr int NSX = 2, NSY = 2;
+  static_assert(Plan<N0>::nst == 2 && Plan<N1>::nst == 2, "slabs assume two-stage plans");
+  using GX = Lines<N0, N1, P0, 1, true>;
+  using GY = Lines<N1, N0, 1, P0, true>;
+};
+template <typename T, int N0, int N1, int NT> constexpr int slab_lds_bytes() {
+  return (N1 * (N0 + 1) + 2 * N0 + (N0 == N1 ? 2 : 2 * N1)) * int(sizeof(cpx<T>)) + (NT / 64) * 16 + 64;
+}
+
+// NA: threads that take butterflies (see slab_threads).
+template <bool FIRST, class A, class B> __device__ __forceinline__ auto& pick(A& a, B& b) {
+  if constexpr (FIRST) return a;
+  else return b;
+}
+template <typename T, int N0, int N1, int N2, int NTILE, int NA, bool G0, bool EX, bool PF>
+__global__ __launch_bounds__(round256(NA)) __attribute__((amdgpu_waves_per_eu(
+    lds_waves_per_simd(slab_lds_bytes<T, N0, N1, round64(NA)>(), NA, 4))))
+void pass2_xy(ChunkArgs a0, const ChunkArgs* tasks, int pq) {
+  using S = Slab<T, N0, N1>;
+  using GX = typename S::GX;
+  using GY = typename S::GY;
+  constexpr int P0 = S::P0, NT = round64(NA), NW = NT / 64, PL = N0 * N1;
+  const ChunkArgs a = chunk_args(a0, tasks);
+  const int np = chunk_pairs(a);
+  const int z = blockIdx.x, qbeg = int(blockIdx.y) * pq;
+  if (qbeg >= np) return;
+  const int qend = qbeg + pq < np ? qbeg + pq : np;
+  __shared__ cpx<T> lds[N1 * P0];
+  // twiddles of the second stages: forward and inverse x, forward and inverse y
+  constexpr bool SQ = N0 == N1;
+  __shared__ cpx<T> tfx[N0], tix[N0], tfy_[SQ ? 1 : N1], tiy_[SQ ? 1 : N1];
+  __shared__ double red[2][NW];
+  __shared__ double gsum[2], red0;
+  __shared__ double esum[EX ? kSlabPairs : 1][3];
+  // forward y in the order whose first stage, which loads, has the fuller slots
+  constexpr int YA = StageOf<N1, 0, false>::R, YB = StageOf<N1, 1, false>::R;
+  constexpr bool YREV = slots<GY, YB, NA>() * YB < slots<GY, YA, NA>() * YA;
+  using Y0 = StageOf<N1, 0, YREV>;
+  using Y1 = StageOf<N1, 1, YREV>;
+  using X0 = StageOf<N0, 0, false>;
+  using X1 = StageOf<N0, 1, false>;
+  using J0 = StageOf<N0, 0, true>;   // inverse x
+  using J1 = StageOf<N0, 1, true>;
+  using V0 = StageOf<N1, 0, !YREV>;  // inverse y
+  using V1 = StageOf<N1, 1, !YREV>;
+  // (equal axes: a table depends on the length and the span only)
+  cpx<T>* const tfy = !SQ ? tfy_ : Y1::NS == X1::NS ? tfx : tix;
+  cpx<T>* const tiy = !SQ ? tiy_ : V1::NS == J1::NS ? tix : tfx;
+  static_assert(J0::R == X1::R, "inverse must start with the forward's last radix");
+  using KT = typename std::conditional<G0, float, double>::type;
+  const int tid = threadIdx.x;
+  cpx<T>* const tz = reinterpret_cast<cpx<T>*>(a.t) + size_t(z) * PL;
+  const size_t ng = size_t(PL) * N2;
+
+  fill_stage_table<T, N0, X1::NS, NT>(tfx);
+  fill_stage_table<T, N0, J1::NS, NT>(tix);
+  if constexpr (!SQ) {
+    fill_stage_table<T, N1, Y1::NS, NT>(tfy);
+    fill_stage_table<T, N1, V1::NS, NT>(tiy);
+  }
+  const auto ktab = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<KT*>(reinterpret_cast<const KT*>(a.kt) + size_t(z) * PL), 0, -1, 0x00020000);
+  auto ld_real = [](__amdgpu_buffer_rsrc_t b, unsigned off, int step) {
+    const int so = step * int(sizeof(KT));
+    if constexpr (sizeof(KT) == 4) return __builtin_bit_cast(KT, __builtin_amdgcn_raw_buffer_load_b32(b, off, so, 0));
+    else return __builtin_bit_cast(KT, __builtin_amdgcn_raw_buffer_load_b64(b, off, so, 0));
+  };
+  // PF: the slab of the next pair is requested after the kernel multiply (its
+  // registers are free then and the kernel loads done) and arrives during the
+  // inverse transforms.  Where LDS holds one workgroup per CU nothing else
+  // covers the latency.
+  constexpr int S0 = slots<GY, Y0::R, NA>();
+  static_assert(!PF || (N1 / Y0::R) % (NA / N0) == 0, "prefetch needs full slots");
+  auto request = [&](__amdgpu_buffer_rsrc_t b, auto& v, int t, auto sc) {
+#pragma unroll
+    for (int k = 0; k < decltype(sc)::value; ++k) {
+      int line, j;
+      slot<GY, Y0::R, NA>(t, k, line, j);
+#pragma unroll
+      for (int r = 0; r < Y0::R; ++r)
+        v[k][r] = ldg<T>(b, unsigned(j * N0 + line) * unsigned(sizeof(cpx<T>)), r * (N1 / Y0::R) * N0);
+    }
+  };
+  cpx<T> nx[PF ? S0 : 1][Y0::R];
+  if constexpr (PF) {
+    request(view(tz + size_t(pair_slot(a, qbeg)) * ng), nx, tid, std::integral_constant<int, S0>{});
+    __builtin_amdgcn_s_waitcnt(0x0f70);
+  }
+  for (int q = qbeg; q < qend; ++q) {
+    const int p = pair_slot(a, q);
+    const auto buf = view(tz + size_t(p) * ng);
+    // the thread index, opaque to the compiler in every iteration: it would
+    // otherwise keep the addresses of all stages in registers across the loop
+    // (and spill them) instead of forming them where they are used
+    int t = tid;
+    __asm__("" : "+v"(t));
+    if (G0 && z == 0 && tid >= NT - 64) {
+      // G = 0 from the FP64 tile sums of pass 1, one wave, fixed order
+      double s0 = 0.0, s1 = 0.0;
+      const G0Part* g = a.g0 + size_t(p) * NTILE;
+      for (int i = tid & 63; i < NTILE; i += 64) {
+        s0 += gld(&g[i].re);
+        s1 += gld(&g[i].im);
+      }
+      s0 = wave_sum(s0);
+      s1 = wave_sum(s1);
+      if ((tid & 63) == 0) {
+        gsum[0] = s0;
+        gsum[1] = s1;
+      }
+    }
+    // first forward y stage from global
+    by_slots<GY, Y0::R, NA>([&](auto sc) {
+      constexpr int SL = decltype(sc)::value;
+      cpx<T> u[PF ? 1 : SL > 0 ? SL : 1][Y0::R];
+      auto& v = pick<PF>(nx, u);
+      if constexpr (!PF) request(buf, v, t, sc);
+      lds_sync();  // twiddles written; the previous pair's last stage has read LDS
+#pragma unroll
+      for (int k = 0; k < SL; ++k) {
+        int line, j;
+        slot<GY, Y0::R, NA>(t, k, line, j);
+        dft<T, Y0::R, false>(v[k]);
+#pragma unroll
+        for (int r = 0; r < Y0::R; ++r) lds[out_pos<Y0::R, 1>(j, r) * P0 + line] = v[k][r];
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      lds_sync();
+    });
+    stage_lds<T, GY, Y1::R, Y1::NS, false, NA>(lds, tfy, t);
+    stage_lds<T, GX, X0::R, X0::NS, false, NA>(lds, tfx, t);
+    // last forward x stage into registers, kernel multiply, first inverse stage
+    by_slots<GX, X1::R, NA>([&](auto sc) {
+      constexpr int SL = decltype(sc)::value;
+      cpx<T> v[SL > 0 ? SL : 1][X1::R];
+      double ex = 0.0, en = 0.0, ex0 = 0.0;  // FP32 form: sum_{G!=0} K|rho|^2, sum_{G!=0} |rho|^2, G = 0 term
+#pragma unroll
+      for (int k = 0; k < SL; ++k) {
+        int line, j;
+        slot<GX, X1::R, NA>(t, k, line, j);
+#pragma unroll
+        for (int r = 0; r < X1::R; ++r) v[k][r] = lds[line * P0 + j + r * (N0 / X1::R)];
+      }
+      lds_sync();  // every thread has read its lines before they are overwritten
+#pragma unroll
+      for (int k = 0; k < SL; ++k) {
+        int line, j;
+        slot<GX, X1::R, NA>(t, k, line, j);
+        KT kv[X1::R];
+        const unsigned off = unsigned(j * N1 + line) * unsigned(sizeof(KT));
+#pragma unroll
+        for (int r = 0; r < X1::R; ++r) kv[r] = ld_real(ktab, off, r * (N0 / X1::R) * N1);
+        twiddle<T, N0, X1::R, X1::NS, false>(v[k], j, tfx);
+        dft<T, X1::R, false>(v[k]);
+        T fex = T(0), fen = T(0);  // the butterfly's partial energy sums
+#pragma unroll
+        for (int r = 0; r < X1::R; ++r) {
+          const cpx<T> c = v[k][r];
+          const KT kg = kv[r];
+          if (G0 && r == 0 && k == 0 && z == 0 && tid == 0) {
+            // G = 0: butterfly 0 of line 0
+            const double k0 = gld(a.kern);
+            const double s0 = gsum[0], s1 = gsum[1];
+            if (EX) ex0 = k0 * (s0 * s0 + s1 * s1);
+            v[k][r] = {T(k0 * s0), T(k0 * s1)};
+          } else {
+            // FP32 form: K(G) rounded to FP32; the energy terms of the
+            // thread's few values are summed in FP32, the partials in FP64
+            // (random rounding: about 1e-10 relative on a pair's energy)
+            if (EX) {
+              const T c2 = c.x * c.x + c.y * c.y;
+              fex += kg * c2;
+              if (G0) fen += c2;
+            }
+            v[k][r] = {kg * c.x, kg * c.y};
+          }
+        }
+        if constexpr (EX) {
+          // lanes that repeat a butterfly do not count
+          constexpr int STEP = NA / N1, NJ = N0 / X1::R;
+          const bool own = (NA % 64 == 0 || tid < NA) && (NJ % STEP == 0 || tid / N1 + k * STEP < NJ);
+          ex += own ? double(fex) : 0.0;
+          if (G0) en += own ? double(fen) : 0.0;
+        }
+        dft<T, J0::R, true>(v[k]);
+#pragma unroll
+        for (int r = 0; r < J0::R; ++r) lds[line * P0 + out_pos<J0::R, 1>(j, r)] = v[k][r];
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if constexpr (EX) {
+        ex = wave_sum(ex);
+        if (G0) en = wave_sum(en);
+        if ((tid & 63) == 0) {
+          red[0][tid >> 6] = ex;
+          if (G0) red[1][tid >> 6] = en;
+        }
+        if (G0 && tid == 0) red0 = ex0;
+      }
+      lds_sync();
+    });
+    if constexpr (EX) {
+      if (tid == 0) {
+        double s2 = 0.0, s3 = 0.0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+          s2 += red[0][w];
+          if (G0) s3 += red[1][w];
+        }
+        esum[q - qbeg][0] = s2;
+        if constexpr (G0) {
+          esum[q - qbeg][1] = s3;
+          esum[q - qbeg][2] = red0;
+        }
+      }
+    }
+    if constexpr (PF)  // the next pair's slab (the last pair requests its own again)
+      request(view(tz + size_t(pair_slot(a, q + 1 < qend ? q + 1 : q)) * ng), nx, t, std::integral_constant<int, S0>{});
+    stage_lds<T, GX, J1::R, J1::NS, true, NA>(lds, tix, t);
+    stage_lds<T, GY, V0::R, V0::NS, true, NA>(lds, tiy, t);
+    // last inverse y stage back to global, in place
+    by_slots<GY, V1::R, NA>([&](auto sc) {
+      constexpr int SL = decltype(sc)::value;
+#pragma unroll
+      for (int k = 0; k < SL; ++k) {
+        int line, j;
+        slot<GY, V1::R, NA>(t, k, line, j);
+        cpx<T> w[V1::R];
+#pragma unroll
+        for (int r = 0; r < V1::R; ++r) w[r] = lds[(j + r * (N1 / V1::R)) * P0 + line];
+        twiddle<T, N1, V1::R, V1::NS, true>(w, j, tiy);
+        dft<T, V1::R, true>(w);
+#pragma unroll
+        for (int r = 0; r < V1::R; ++r)
+          stn<T>(buf, unsigned(j * N0 + line) * unsigned(sizeof(cpx<T>)), r * (N1 / V1::R) * N0, w[r]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    });
+  }
+  if constexpr (EX) {
+    constexpr int NE = G0 ? 3 : 1;
+    lds_sync();
+    if (tid < (qend - qbeg) * NE)
+      gst(a.expart + (size_t(pair_slot(a, qbeg + tid / NE)) * N2 + z) * NE + tid % NE, esum[tid / NE][tid % NE]);
+  }
+}
+
+// ============================================================== pass 3
+// Moves a z tile (N2 rows of W points, rows PL points apart) into LDS with
+// 16-byte global -> LDS transfers: a wave moves 1 KiB pieces of consecutive
+// rows, lane l the l-th 16 bytes (the LDS destination of a transfer is
+// wave-uniform, its lanes fill consecutive 16-byte slots).  lim: bytes of the
+// row that lie inside the plane (ragged last tile; lanes past it re-read its
+// last 16 bytes).  Streaming policy: each slab is read once.
+template <typename T, int N2, int W, int PL, int NT, bool RAG>
+__device__ __forceinline__ void dma_tile(const cpx<T>* src, cpx<T>* dst, int lim) {
+  constexpr int RBYTES = W * int(sizeof(cpx<T>)), LR = RBYTES / 16, RPI = 64 / LR;
+  static_assert(RBYTES % 16 == 0 && 64 % LR == 0, "whole rows per transfer");
+  constexpr int NW = NT / 64, NCH = (N2 + RPI - 1) / RPI;
   const int w = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
   const int lane = int(threadIdx.x) & 63;
+  int col = (lane % LR) * 16;
+  if (RAG) col = col < lim ? col : lim - 16;
   const char PX_GLOBAL* g = (const char PX_GLOBAL*)(src);
   char __attribute__((address_space(3)))* l = (char __attribute__((address_space(3)))*)(dst);
 #pragma unroll
   for (int q0 = 0; q0 < NCH; q0 += NW) {
-    const int q = q0 + w;
-    const int off = q * 1024 + lane * 16;
-    // whole pieces for every wave: no branch (the same transfers on every path)
-    if (NCH % NW == 0 && BYTES % 1024 == 0 ? true : (q < NCH && off < BYTES))
-      __builtin_amdgcn_global_load_lds((const void PX_GLOBAL*)(g + off),
-                                       (void __attribute__((address_space(3)))*)(l + q * 1024), 16, 0,
-                                       PX_DMA_AUX);
+    // every wave issues the same transfers: pieces (and rows) past the tile
+    // repeat its last (the compiler's waits then count them)
+    int q = q0 + w;
+    if (NCH % NW != 0) q = q < NCH ? q : NCH - 1;
+    int row = q * RPI + lane / LR;
+    if (N2 % RPI != 0) row = row < N2 ? row : N2 - 1;
+    __builtin_amdgcn_global_load_lds(
+        (const void PX_GLOBAL*)(g + (unsigned(row) * unsigned(PL * sizeof(cpx<T>)) + unsigned(col))),
+        (void __attribute__((address_space(3)))*)(l + q * 1024), 16, 0, 2);
   }
 }
 
-// One in-place LDS stage like stage_lds, with lds_sync barriers.
-template <typename T, class G, int R, int NS, bool INV, int NT>
-__device__ __forceinline__ void stage_inplace(cpx<T>* lds, const cpx<T>* tw) {
-  constexpr int NB = G::nl * (G::n / R);
-  constexpr int BPT = (NB + NT - 1) / NT;
-  cpx<T> v[BPT][R];
-  const int tid = threadIdx.x;
-#pragma unroll
-  for (int k = 0; k < BPT; ++k) {
-    const int b = tid + k * NT;
-    if (NB % NT == 0 || b < NB) {
-      int line, j;
-      decode<G, R>(b, line, j);
-#pragma unroll
-      for (int r = 0; r < R; ++r) v[k][r] = lds[line * G::ls + (j + r * (G::n / R)) * G::es];
-    }
-  }
-  lds_sync();
-#pragma unroll
-  for (int k = 0; k < BPT; ++k) {
-    const int b = tid + k * NT;
-    if (NB % NT == 0 || b < NB) {
-      int line, j;
-      decode<G, R>(b, line, j);
-      twiddle<T, G::n, R, NS, INV>(v[k], j, tw);
-      dft<T, R, INV>(v[k]);
-#pragma unroll
-      for (int r = 0; r < R; ++r) lds[line * G::ls + out_pos<R, NS>(j, r) * G::es] = v[k][r];
-    }
-  }
-  lds_sync();
-}
-
-// Pass 3 with the pair slab staged through LDS (FP32): one working slab A
-// (padded rows, stages in place) and one staging slab S (the pair slab as
-// stored).  While pair jj is transformed, the next pair's slab moves into S by
-// global -> LDS transfers, so neither the registers of a second slab (which at
-// 96^3 would cost the occupancy of the 12-wave workgroup) nor a wait at the
-// start of each pair are needed.  The psi_j slab of the pair is requested at
-// the start of the pair, before the transfer, so that waiting for it never
-// waits for the transfer.  Same arithmetic and results as pass3_inv_xy_acc.
-template <typename T, int N0, int N1, int NT, bool SV>
-__global__ __launch_bounds__(NT) void pass3_staged(ChunkArgs a0, const ChunkArgs* tasks) {
+// Workgroup = (tile, i) looping over j (SYM = false), or (tile, group of GJ
+// density orbitals j) looping over the rows i and within a row over the
+// group's j (SYM).  One staging tile, filled by global -> LDS transfers while
+// the previous pair is transformed, and one working tile.
+// SYM: the sums over i of the group's GJ columns stay in registers for the
+// whole chunk and end in one read-modify-write of the columns' output tiles;
+// the sum over the group's j of a row goes to the tile of the row's first pair
+// slab of the group (which this workgroup alone has just consumed), for pass 4.
+template <typename T, int N0, int N1, int N2, int W, bool SYM, int GJ>
+__global__ __launch_bounds__((round256(ZTile<T, N0, N1, N2, W, ztile_radix3<T, N2>()>::NT))) __attribute__((amdgpu_waves_per_eu(
+    pass3_waves(sizeof(T) == 4, SYM, ZTile<T, N0, N1, N2, W, ztile_radix3<T, N2>()>::NT))))
+void pass3_z(ChunkArgs a0, const ChunkArgs* tasks) {
+  using Z = ZTile<T, N0, N1, N2, W, ztile_radix3<T, N2>()>;
+  using IL = typename Z::IL;
+  constexpr int NT = Z::NT, RS = Z::RS, RB = Z::RB, PL = Z::PL;
   const ChunkArgs a = chunk_args(a0, tasks);
-  if (int(blockIdx.y) >= a.ic) return;
-  constexpr int P0 = N0 + 1;
-  constexpr int SL = N1 * P0;
-  constexpr int SLAB_BYTES = N0 * N1 * int(sizeof(cpx<T>));
-  __shared__ cpx<T> lds[SL];
-  __shared__ __attribute__((aligned(16))) cpx<T> sbuf[N0 * N1];
-  __shared__ cpx<T> tw0[N0];
-  __shared__ cpx<T> tw1[N1];
-  using GX = Lines<N0, N1, P0, 1, false>;
-  using GY = Lines<N1, N0, 1, P0, true>;
-  constexpr int NSX = Plan<N0>::nst, NSY = Plan<N1>::nst;
-  static_assert(NSX == 2 && NSY == 2, "staged pass 3 assumes two-stage plans");
-  using X0 = StageOf<N0, 0, true>;
-  using X1 = StageOf<N0, 1, true>;
-  constexpr int RF = StageOf<N1, NSY - 1, false>::R, RR = StageOf<N1, NSY - 1, true>::R;
-  constexpr bool YREV = sizeof(T) == 8 ||
-                        (N0 * (N1 / RR) + NT - 1) / NT <= (N0 * (N1 / RF) + NT - 1) / NT;
-  using Y0 = StageOf<N1, 0, YREV>;
-  using YL = StageOf<N1, NSY - 1, YREV>;
-  constexpr int NB0 = N1 * (N0 / X0::R), BPT0 = (NB0 + NT - 1) / NT;
-  constexpr int NBL = N0 * (N1 / YL::R), BPTL = (NBL + NT - 1) / NT;
-
-  fill_twiddles<T, N0, NT>(tw0);
-  fill_twiddles<T, N1, NT>(tw1);
-  const int z = blockIdx.x, ii = blockIdx.y;
-  const int jend = a.tri ? ii + 1 : a.jc;  // pairs jj < jend of row ii
-  const size_t slab = size_t(N0) * N1;
-  const size_t ng = slab * a.n2;
+  int tile, by;
+  tile_order(tile, by);
+  if (tile >= Z::NTILE || by * (SYM ? GJ : 1) >= (SYM ? a.jc : a.ic)) return;
+  // staging: whole 1 KiB pieces (see dma_tile)
+  constexpr int PIECE = 1024 / int(sizeof(cpx<T>));
+  __shared__ __attribute__((aligned(16))) cpx<T> sbuf[(N2 * W + PIECE - 1) / PIECE * PIECE];
+  __shared__ cpx<T> lds[N2 * W];
+  __shared__ cpx<T> tw[N2];
+  fill_stage_table<T, N2, IL::NS, NT>(tw);
   const int tid = threadIdx.x;
-  const cpx<T>* t0 = reinterpret_cast<const cpx<T>*>(a.t) + size_t(ii * a.jc) * ng + z * slab;
-  const cpx<T>* psi0 = reinterpret_cast<const cpx<T>*>(a.psi) + size_t(a.j0) * ng + z * slab;
-  auto pload = [](const cpx<T>* base) {
-    return [base](int line, int e) { return ldc(base + unsigned(line + e * N0)); };
+  const int t0 = tile * W;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const size_t ng = size_t(PL) * N2;
+  const cpx<T>* tb = reinterpret_cast<const cpx<T>*>(a.t) + t0;
+  const int lim = (PL - t0 < W ? PL - t0 : W) * int(sizeof(cpx<T>));
+  // last inverse stage and sums: butterfly (j1, l1)
+  const bool live1 = Z::NBS % NT == 0 || tid < Z::NBS;
+  const int b1 = live1 ? tid : Z::NBS - 1;
+  const int l1 = b1 % W, j1 = b1 / W;
+  const bool in1 = live1 && (!Z::RAG || t0 + l1 < PL);
+  const unsigned o1 = unsigned(j1 * PL + (!Z::RAG || t0 + l1 < PL ? t0 + l1 : PL - 1)) * unsigned(sizeof(cpx<T>));
+  constexpr int RSTEP = RB * PL;  // between a thread's points
+  const cpx<T>* psi = reinterpret_cast<const cpx<T>*>(a.psi);
+  cpx<T>* const out = reinterpret_cast<cpx<T>*>(a.out);
+  auto weight = [&](int orb) {
+    // uniform: a scalar load (counted with the LDS operations, so that waiting
+    // for it never waits for the tile transfer)
+    return T(*(const __attribute__((address_space(4))) double*)(a.occ + orb) * a.inv_ng);
   };
-  cpx<T>* const outz = reinterpret_cast<cpx<T>*>(a.out) + size_t(a.i0 + ii) * ng + z * slab;
-  cpx<T> acc[BPTL][YL::R];
+  // Inverse z transform of the staged tile.  Once every thread has read it, the
+  // next pair's tile starts to move into its place.  The psi_j tile is
+  // requested before: memory requests complete in order, so the wait for it
+  // never waits for the transfer.  (Staging and working tile are two arrays:
+  // an LDS read that might alias a transfer's destination is made to wait for
+  // the transfer, as it was with two exchanged buffers.)
+  auto transform = [&](cpx<T>(&v)[RS], cpx<T>(&pc)[RS], const cpx<T>* pj, const cpx<T>* next) {
+    const auto pjv = view(pj);
 #pragma unroll
-  for (int k = 0; k < BPTL; ++k)
+    for (int r = 0; r < RS; ++r) pc[r] = ldc<T>(pjv, o1, r * RSTEP);
+    // first stage, the waves with a butterfly less by a path of their own
+    // (branch-free slots, as in pass 2)
+    auto first = [&](auto sc) {
+      constexpr int SL = decltype(sc)::value;
+      cpx<T> u[SL > 0 ? SL : 1][RB];
+      auto pos = [&](int k, int& l, int& j) {
+        int b = tid + k * NT;
+        if (Z::NBB % NT != 0) b = b < Z::NBB ? b : Z::NBB - 1;
+        l = b % W;
+        j = b / W;
+      };
 #pragma unroll
-    for (int r = 0; r < YL::R; ++r) acc[k][r] = {T(0), T(0)};
+      for (int k = 0; k < SL; ++k) {
+        int l, j;
+        pos(k, l, j);
+#pragma unroll
+        for (int r = 0; r < RB; ++r) u[k][r] = sbuf[(j + r * RS) * W + l];
+      }
+#pragma unroll
+      for (int k = 0; k < SL; ++k) {
+        int l, j;
+        pos(k, l, j);
+        dft<T, RB, true>(u[k]);
+#pragma unroll
+        for (int r = 0; r < RB; ++r) lds[out_pos<RB, 1>(j, r) * W + l] = u[k][r];
+      }
+    };
+    if (Z::NBB % NT == 0 || wave * 64 + (Z::SB - 1) * NT < Z::NBB) first(std::integral_constant<int, Z::SB>{});
+    else first(std::integral_constant<int, Z::SB - 1>{});
+    lds_sync();
+    // (outside of the two paths: on a path that does not issue it the compiler
+    // would wait for everything)
+    dma_tile<T, N2, W, PL, NT, Z::RAG>(next, sbuf, lim);
+#pragma unroll
+    for (int r = 0; r < RS; ++r) v[r] = lds[(j1 + r * RB) * W + l1];
+    twiddle<T, N2, RS, IL::NS, true>(v, j1, tw);
+    dft<T, RS, true>(v);
+  };
+  cpx<T> row[RS];
+#pragma unroll
+  for (int r = 0; r < RS; ++r) row[r] = {T(0), T(0)};
 
-  dma_to_lds<SLAB_BYTES, NT>(t0, sbuf);
-  dma_sync();
-  for (int jj = 0; jj < jend; ++jj) {
-    // the weight is uniform: a scalar load (counted with the LDS operations,
-    // so that waiting for it never waits for the slab transfer)
-    const T wj = T(*(const __attribute__((address_space(4))) double*)(a.occ + a.j0 + jj) * a.inv_ng);
-    cpx<T> pc[BPTL][YL::R];
-    gather<T, GY, YL::R, NT>(pc, pload(psi0 + size_t(jj) * ng));
-    // first inverse x stage: staging slab -> registers -> working slab
-#pragma unroll
-    for (int k = 0; k < BPT0; ++k) {
-      const int b = tid + k * NT;
-      if (NB0 % NT == 0 || b < NB0) {
-        int line, j;
-        decode<GX, X0::R>(b, line, j);
-        cpx<T> v[X0::R];
-#pragma unroll
-        for (int r = 0; r < X0::R; ++r) v[r] = sbuf[line * N0 + j + r * (N0 / X0::R)];
-        dft<T, X0::R, true>(v);
-#pragma unroll
-        for (int r = 0; r < X0::R; ++r) lds[line * P0 + out_pos<X0::R, 1>(j, r)] = v[r];
-      }
-    }
-    lds_sync();  // the staging slab has been read by every thread
-    // the next pair's slab (the last pair moves its own slab again: the same
-    // transfers on every pair, so that the compiler's wait for the psi_j slab
-    // counts them and does not wait for them)
-    dma_to_lds<SLAB_BYTES, NT>(t0 + size_t(jj + 1 < jend ? jj + 1 : jj) * ng, sbuf);
-    stage_inplace<T, GX, X1::R, X1::NS, true, NT>(lds, tw0);
-    stage_inplace<T, GY, Y0::R, Y0::NS, true, NT>(lds, tw1);
-    // last stage: registers, psi_j-weighted accumulation, kept v_ij (SV)
-    cpx<T>* tv = reinterpret_cast<cpx<T>*>(a.t) + size_t(ii * a.jc + jj) * ng + z * slab;
-#pragma unroll
-    for (int k = 0; k < BPTL; ++k) {
-      int b = tid + k * NT;
-      if (NBL % NT != 0) b = b < NBL ? b : NBL - 1;
-      int line, j;
-      decode<GY, YL::R>(b, line, j);
-      cpx<T> v[YL::R];
-#pragma unroll
-      for (int r = 0; r < YL::R; ++r) v[r] = lds[line + (j + r * (N1 / YL::R)) * P0];
-      twiddle<T, N1, YL::R, YL::NS, true>(v, j, tw1);
-      dft<T, YL::R, true>(v);
-#pragma unroll
-      for (int r = 0; r < YL::R; ++r) {
-        cpx<T> t = cmul(pc[k][r], v[r]);
-        acc[k][r].x += wj * t.x;
-        acc[k][r].y += wj * t.y;
-      }
-      if constexpr (SV) {
-#pragma unroll
-        for (int r = 0; r < YL::R; ++r) stn(tv + unsigned(line + (j + r * (N1 / YL::R)) * N0), v[r]);
-      }
-    }
-    // the next pair's slab has arrived and the working slab is free
+  if constexpr (!SYM) {
+    const int ii = by;
+    const cpx<T>* t = tb + size_t(ii) * a.jc * ng;
+    dma_tile<T, N2, W, PL, NT, Z::RAG>(t, sbuf, lim);
     dma_sync();
-  }
-  // one read-modify-write of the output slab, all loads issued before the
-  // first store
-  cpx<T> po[BPTL][YL::R];
-  if (!a.first) gather<T, GY, YL::R, NT>(po, pload(outz));
+    for (int jj = 0; jj < a.jc; ++jj) {
+      const T wj = weight(a.j0 + jj);
+      const cpx<T>* pj = psi + size_t(a.j0 + jj) * ng;
+      cpx<T> pc[RS], v[RS];
+      // (the last pair moves its own tile again: the same transfers on every pair)
+      transform(v, pc, pj, t + size_t(jj + 1 < a.jc ? jj + 1 : jj) * ng);
 #pragma unroll
-  for (int k = 0; k < BPTL; ++k) {
-    const int b = tid + k * NT;
-    if (NBL % NT == 0 || b < NBL) {
-      int line, j;
-      decode<GY, YL::R>(b, line, j);
+      for (int r = 0; r < RS; ++r) {
+        const cpx<T> c = cmul(pc[r], v[r]);
+        row[r].x += wj * c.x;
+        row[r].y += wj * c.y;
+      }
+      dma_sync();
+    }
+    cpx<T>* o = out + size_t(a.i0 + ii) * ng;
+    cpx<T> prev[RS];
+    if (!a.first) {
 #pragma unroll
-      for (int r = 0; r < YL::R; ++r) {
-        const cpx<T> prev = a.first ? cpx<T>{T(0), T(0)} : po[k][r];
-        stg(outz + unsigned(line + (j + r * (N1 / YL::R)) * N0), csub(prev, acc[k][r]));
+      for (int r = 0; r < RS; ++r) prev[r] = ldc<T>(view(o), o1, r * RSTEP);
+    }
+    if (in1) {
+#pragma unroll
+      for (int r = 0; r < RS; ++r) stg<T>(view(o), o1, r * RSTEP, csub(a.first ? cpx<T>{T(0), T(0)} : prev[r], row[r]));
+    }
+  } else {
+    // psi_i's tile is kept for the group's pairs where the registers hold it
+    // with the sums, and read again for each pair where the kernel would spill
+    // (80^3, 96^3 and the non-cubic grids in FP64, ten-wave workgroups).  FP64,
+    // 60 x 90 x 120, GJ = 2: 3.7 us a pair against 4.4 with 26 registers
+    // spilled, or 4.6 and another 1.0 in pass 4 with GJ = 1; 72^3, where it
+    // fits: 1.9 against 2.0 read again.
+    constexpr bool AGAIN = (sizeof(T) == 8 && RS + RB >= 18) || NT > 512;
+    const int jg = by * GJ;                  // first j of the group
+    const int gn = a.jc - jg < GJ ? a.jc - jg : GJ;       // its j's
+    const int ibeg = a.tri ? jg : 0;                      // triangular block: pairs jj <= ii
+    cpx<T> col[GJ][RS];
+#pragma unroll
+    for (int u = 0; u < GJ; ++u)
+#pragma unroll
+      for (int r = 0; r < RS; ++r) col[u][r] = {T(0), T(0)};
+    const cpx<T>* t = tb + (size_t(ibeg) * a.jc + jg) * ng;
+    dma_tile<T, N2, W, PL, NT, Z::RAG>(t, sbuf, lim);
+    dma_sync();
+    for (int ii = ibeg; ii < a.ic; ++ii) {
+      const int un = a.tri && ii - jg + 1 < gn ? ii - jg + 1 : gn;  // live pairs of the row
+      const cpx<T>* ti = tb + (size_t(ii) * a.jc + jg) * ng;
+      const T wi = weight(a.i0 + ii);
+      cpx<T> pi[RS];
+      const auto piv = view(psi + size_t(a.i0 + ii) * ng);
+      if constexpr (!AGAIN) {
+#pragma unroll
+        for (int r = 0; r < RS; ++r) pi[r] = ldc<T>(piv, o1, r * RSTEP);
+      }
+#pragma unroll
+      for (int u = 0; u < GJ; ++u) {
+        if (u < un) {
+          const T wj = weight(a.j0 + jg + u);
+          const cpx<T>* pj = psi + size_t(a.j0 + jg + u) * ng;
+          cpx<T> pc[RS], v[RS];
+          const cpx<T>* next = u + 1 < un ? ti + size_t(u + 1) * ng
+                             : ii + 1 < a.ic ? ti + size_t(a.jc) * ng : ti + size_t(u) * ng;
+          transform(v, pc, pj, next);
+          const bool diag = a.tri && jg + u == ii;  // the pair (i, i) counts once
+          const T wc = diag ? T(0) : wi;
+#pragma unroll
+          for (int r = 0; r < RS; ++r) {
+            const cpx<T> c = cmul(pc[r], v[r]);
+            row[r].x += wj * c.x;
+            row[r].y += wj * c.y;
+          }
+          if constexpr (AGAIN) {
+            __builtin_amdgcn_sched_barrier(0);  // psi_j's registers are free now
+#pragma unroll
+            for (int r = 0; r < RS; ++r) pi[r] = ldc<T>(piv, o1, r * RSTEP);
+          }
+#pragma unroll
+          for (int r = 0; r < RS; ++r) {
+            // f_i/N_g psi_i conj(v)
+            const cpx<T> d = cmulc(v[r], pi[r]);
+            col[u][r].x += wc * d.x;
+            col[u][r].y += wc * d.y;
+          }
+          dma_sync();
+        }
+      }
+      if (in1) {
+        cpx<T>* o = const_cast<cpx<T>*>(ti) - t0;
+#pragma unroll
+        for (int r = 0; r < RS; ++r) stn<T>(view(o), o1, r * RSTEP, row[r]);
+      }
+#pragma unroll
+      for (int r = 0; r < RS; ++r) row[r] = {T(0), T(0)};
+    }
+    const bool init = a.first && a.tri;  // the block's first writer (a.first: pass 4 otherwise)
+#pragma unroll
+    for (int u = 0; u < GJ; ++u) {
+      if (u < gn) {
+        cpx<T>* o = out + size_t(a.j0 + jg + u) * ng;
+        cpx<T> prev[RS];
+        if (!init) {
+#pragma unroll
+          for (int r = 0; r < RS; ++r) prev[r] = ldc<T>(view(o), o1, r * RSTEP);
+        }
+        if (in1) {
+#pragma unroll
+          for (int r = 0; r < RS; ++r) stg<T>(view(o), o1, r * RSTEP, csub(init ? cpx<T>{T(0), T(0)} : prev[r], col[u][r]));
+        }
       }
     }
   }
 }
 
 // ============================================================== host launcher
-// Threads per workgroup: close to the butterfly count of each stage of a slab
-// (N * N / R), so that most stages take one butterfly per thread.
-template <int N> constexpr int threads_for() {
-  return N == 16 ? 64 : N == 24 ? 192 : N == 32 ? 256 : N == 40 ? 320 : N == 48 ? 384
-       : N == 60 ? 640 : N == 64 ? 512 : N == 72 ? 704 : N == 80 ? 832 : 768;
+// Threads of a pass-2 workgroup that take butterflies (the workgroup has whole
+// waves): a multiple of the line counts, so that a thread keeps its line, with
+// one to three butterflies in each stage.
+template <typename T, int N0, int N1> constexpr int slab_threads() {
+  constexpr bool f = sizeof(T) == 4;
+  if (N0 != N1) return f ? 180 : 540;  // 60 x 90
+  return N0 == 16 ? 64 : N0 == 24 ? 192 : N0 == 32 ? 128 : N0 == 40 ? 320 : N0 == 48 ? 192
+       : N0 == 60 ? 360 : N0 == 64 ? (f ? 256 : 512) : N0 == 72 ? (f ? 216 : 648)
+       : N0 == 80 ? (f ? 320 : 640) : f ? 384 : 768;
 }
-// Per-pass configuration of passes 1 and 3: threads per workgroup, the
-// ping-pong form (two LDS slabs, one barrier per stage) or one slab updated in
-// place, and prefetch across pair iterations where the doubled register set
-// fits without spilling (checked with the compiler's resource report).  The
-// defaults were chosen by measurement; a build may override them for one grid
-// size, PX_P13_N, to time alternatives (PX_P1_NT32, PX_P1_PP32, PX_P1_PF32,
-// PX_P3_NT32, PX_P3_PP32, PX_P3_PF32 and the same with 64 for FP64).
-#if defined(PX_P13_N)
-#define PX_OVR(M32, M64)                                    \
-  if (sizeof(T) == 4 && N == PX_P13_N) return M32;          \
-  if (sizeof(T) == 8 && N == PX_P13_N) return M64;
-#endif
-template <typename T, int N> constexpr int pass1_threads() {
-#if defined(PX_P13_N) && defined(PX_P1_NT32) && defined(PX_P1_NT64)
-  PX_OVR(PX_P1_NT32, PX_P1_NT64)
-#endif
-  return threads_for<N>();
-}
-template <typename T, int N> constexpr int pass3_threads() {
-#if defined(PX_P13_N) && defined(PX_P3_NT32) && defined(PX_P3_NT64)
-  PX_OVR(PX_P3_NT32, PX_P3_NT64)
-#endif
-  return threads_for<N>();
-}
-template <typename T, int N> constexpr bool pass1_pingpong() {
-#if defined(PX_P13_N) && defined(PX_P1_PP32) && defined(PX_P1_PP64)
-  PX_OVR(bool(PX_P1_PP32), bool(PX_P1_PP64))
-#endif
-  return pingpong_fits<T, N, N>();
-}
-template <typename T, int N> constexpr bool pass3_pingpong() {
-#if defined(PX_P13_N) && defined(PX_P3_PP32) && defined(PX_P3_PP64)
-  PX_OVR(bool(PX_P3_PP32), bool(PX_P3_PP64))
-#endif
-  return pingpong_fits<T, N, N>();
-}
-template <typename T, int N> constexpr bool prefetch1_for() {
-#if defined(PX_P13_N) && defined(PX_P1_PF32) && defined(PX_P1_PF64)
-  PX_OVR(bool(PX_P1_PF32), bool(PX_P1_PF64))
-#endif
-  return sizeof(T) == 4 ? true : (N <= 72 && N != 60);  // FP32 at 96^3: -21 % with it
-}
-// Pass 3 in the staged form (pass3_staged) instead of pass3_inv_xy_acc: FP32
-// at 72^3 to 96^3 (per 1,024-pair launch, same box: 96^3 3.52 -> 3.14 ms,
-// where the 12-wave workgroup has no registers for a second slab; 80^3 2.11 ->
-// 1.78 ms; 72^3 1.51 -> 1.36 ms).  Pass 4 then runs 4-9 % slower, so at 64^3
-// and below, where pass 3 gained nothing, the register form stays.
-template <typename T, int N> constexpr bool pass3_staged_for() {
-#if defined(PX_P13_N) && defined(PX_P3_STG32)
-  if (sizeof(T) == 4 && N == PX_P13_N) return bool(PX_P3_STG32);
-#endif
-  return sizeof(T) == 4 && (N == 72 || N == 80 || N == 96);
-}
-template <typename T, int N> constexpr bool prefetch3_for() {
-#if defined(PX_P13_N) && defined(PX_P3_PF32) && defined(PX_P3_PF64)
-  PX_OVR(bool(PX_P3_PF32), bool(PX_P3_PF64))
-#endif
-  return sizeof(T) == 4 ? N <= 72 : N <= 48;
+// Whether pass 2 requests the next pair's slab ahead (see PF).
+template <typename T, int N0, int N1> constexpr bool slab_prefetch() {
+  return sizeof(T) == 8 ? N0 >= 60 : N0 == N1 && N0 >= 60 && N0 != 80;
 }
 
-// Threads of a pass-2 workgroup.  FP32 at 72^3: 512 (two butterflies per
-// thread in each stage) lets three workgroups share a CU instead of two.  With
-// two x-sections per plane (see pass2_sections): 192 at 96^3 in both forms
-// (2-3 butterflies per thread; FP32 four workgroups per CU; measured against
-// 128-384 threads and one to four sections on the same box), FP32 256 at
-// 64^3 and 320 at 80^3 (half the single-section counts).
-template <typename T, int N> constexpr int pass2_threads_default() {
-  return N == 96 ? 192
-       : sizeof(T) == 4 && N == 72 ? 512
-       : sizeof(T) == 4 && N == 64 ? 256
-       : sizeof(T) == 4 && N == 80 ? 320
-       : threads_for<N>();
-}
-template <typename T, int N> constexpr int pass2_threads_for() {
-#if defined(PX_P2_N) && defined(PX_P2_NT32)
-  if (sizeof(T) == 4 && N == PX_P2_N) return PX_P2_NT32;
-#endif
-#if defined(PX_P2_N) && defined(PX_P2_NT64)
-  if (sizeof(T) == 8 && N == PX_P2_N) return PX_P2_NT64;
-#endif
-  return pass2_threads_default<T, N>();
-}
-
-// Threads of pass-2 configuration CFG (see pass2_sections_cfg): the default,
-// or for the alternative with two sections half the default (a multiple of
-// 64), with one section the single-section counts.
-template <typename T, int N, int CFG> constexpr int pass2_threads_cfg() {
-  if constexpr (CFG == 0) {
-    return pass2_threads_for<T, N>();
-  } else if constexpr (pass2_sections_cfg(sizeof(T) == 4, N, 1) == 2) {
-    constexpr int t = (pass2_threads_for<T, N>() / 2 + 63) / 64 * 64;
-    return t < 64 ? 64 : t;
-  } else {
-    return sizeof(T) == 4 && N == 72 ? 512 : sizeof(T) == 4 && N == 96 ? 384 : threads_for<N>();
-  }
-}
-
-// Pairs per pass-2 workgroup, with prefetch of the next plane: FP64 at 72^3,
-// where the plane's LDS already limits a CU to one workgroup and the loop
-// fits the registers.  Elsewhere two workgroups per CU overlap better than one
-// with a loop (FP32 at 72^3), or the loop would spill (FP64 at 80^3, 96^3).
-template <typename T, int N> constexpr int pass2_pairs_per_wg() {
-  return sizeof(T) == 8 && N == 72 ? 8 : 1;
-}
-
-// Pass 1, 2, 3 for the cubic grid N^3: one chunk (tasks == nullptr, the
-// chunk in `a`), or ntasks chunks of a task table in device memory, one per
-// blockIdx.z (max_ic / max_pairs: the largest chunk of the table).  The FP32
-// form always takes the G = 0 coefficient from FP64 slab sums.
-// ev (optional, 4 events) brackets the passes: ev[0] | pass 1 | ev[1] | pass 2 | ev[2] | pass 3 | ev[3].
-// Pass 2 of one chunk or task table in configuration CFG.
-template <int N, int CFG>
-void launch_pass2(bool fp32, const ChunkArgs& a, int npairs, bool ex, hipStream_t s,
-                  const ChunkArgs* tasks, int ntasks) {
-  constexpr int Q32 = pass2_pairs_per_wg<float, N>(), Q64 = pass2_pairs_per_wg<double, N>();
-  constexpr int X32 = pass2_sections_cfg(true, N, CFG), X64 = pass2_sections_cfg(false, N, CFG);
-  const int pq = fp32 ? Q32 : Q64;
-  const dim3 g2(N * (fp32 ? X32 : X64), (npairs + pq - 1) / pq, ntasks);
-  if (fp32) {
-    constexpr int NT2 = pass2_threads_cfg<float, N, CFG>();
-    if (ex) hipLaunchKernelGGL((pass2_z_kernel<float, N, N, N, NT2, true, true, Q32, (Q32 > 1), X32>), g2, dim3(NT2), 0, s, a, tasks);
-    else hipLaunchKernelGGL((pass2_z_kernel<float, N, N, N, NT2, true, false, Q32, (Q32 > 1), X32>), g2, dim3(NT2), 0, s, a, tasks);
-  } else {
-    constexpr int NT2 = pass2_threads_cfg<double, N, CFG>();
-    if (ex) hipLaunchKernelGGL((pass2_z_kernel<double, N, N, N, NT2, false, true, Q64, (Q64 > 1), X64>), g2, dim3(NT2), 0, s, a, tasks);
-    else hipLaunchKernelGGL((pass2_z_kernel<double, N, N, N, NT2, false, false, Q64, (Q64 > 1), X64>), g2, dim3(NT2), 0, s, a, tasks);
-  }
-}
-
-template <int N>
-hipError_t launch_chunk_n(bool fp32, const ChunkArgs& a, int npairs, bool ex, bool store_v,
-                          int p2cfg, hipStream_t s, hipEvent_t* ev, const ChunkArgs* tasks,
-                          int ntasks, int max_ic) {
-  if (!tasks) {
-    ntasks = 1;
-    max_ic = a.ic;
-  }
-  dim3 g1(N, max_ic, ntasks), g3(N, max_ic, ntasks);
+template <int N0, int N1, int N2, int CFG>
+hipError_t launch_chunk_cfg(bool fp32, const ChunkArgs& a, const ChunkDims& d, bool ex, hipStream_t s,
+                            hipEvent_t* ev, const ChunkArgs* tasks) {
+  constexpr int WF = tile_width<float, CFG>(), WD = tile_width<double, CFG>();
+  using ZF = ZTile<float, N0, N1, N2, WF>;
+  using ZD = ZTile<double, N0, N1, N2, WD>;
+  // pass 3 tiles
+  constexpr int VF = tile_width3<float, N2, CFG>(), VD = tile_width3<double, N2, CFG>();
+  using YF = ZTile<float, N0, N1, N2, VF, ztile_radix3<float, N2>()>;
+  using YD = ZTile<double, N0, N1, N2, VD, ztile_radix3<double, N2>()>;
+  const int ntile = fp32 ? ZF::NTILE : ZD::NTILE, ntile3 = fp32 ? YF::NTILE : YD::NTILE;
   if (ev) (void)hipEventRecord(ev[0], s);
-  constexpr int NT1F = pass1_threads<float, N>(), NT1D = pass1_threads<double, N>();
-  if (fp32)
-    hipLaunchKernelGGL((pass1_fwd_xy<float, N, N, NT1F, true, prefetch1_for<float, N>(), pass1_pingpong<float, N>()>),
-                       g1, dim3(NT1F), 0, s, a, tasks);
-  else
-    hipLaunchKernelGGL((pass1_fwd_xy<double, N, N, NT1D, false, prefetch1_for<double, N>(), pass1_pingpong<double, N>()>),
-                       g1, dim3(NT1D), 0, s, a, tasks);
+  const dim3 g1(tile_grid(ntile), d.max_ic, d.ntasks);
+  if (fp32) hipLaunchKernelGGL((pass1_z<float, N0, N1, N2, WF, true>), g1, dim3(ZF::NT), 0, s, a, tasks);
+  else hipLaunchKernelGGL((pass1_z<double, N0, N1, N2, WD, false>), g1, dim3(ZD::NT), 0, s, a, tasks);
   if (ev) (void)hipEventRecord(ev[1], s);
-  if (p2cfg == 0) launch_pass2<N, 0>(fp32, a, npairs, ex, s, tasks, ntasks);
-  else launch_pass2<N, 1>(fp32, a, npairs, ex, s, tasks, ntasks);
+  const int pq = pairs_per_slab_wg(N2, d.max_pairs, d.ntasks);
+  const dim3 g2(N2, (d.max_pairs + pq - 1) / pq, d.ntasks);
+  constexpr int NF = slab_threads<float, N0, N1>(), ND = slab_threads<double, N0, N1>();
+  constexpr bool PFF = slab_prefetch<float, N0, N1>(), PFD = slab_prefetch<double, N0, N1>();
+  if (fp32 && ex) hipLaunchKernelGGL((pass2_xy<float, N0, N1, N2, ZF::NTILE, NF, true, true, PFF>), g2, dim3(round64(NF)), 0, s, a, tasks, pq);
+  else if (fp32) hipLaunchKernelGGL((pass2_xy<float, N0, N1, N2, ZF::NTILE, NF, true, false, PFF>), g2, dim3(round64(NF)), 0, s, a, tasks, pq);
+  else if (ex) hipLaunchKernelGGL((pass2_xy<double, N0, N1, N2, ZD::NTILE, ND, false, true, PFD>), g2, dim3(round64(ND)), 0, s, a, tasks, pq);
+  else hipLaunchKernelGGL((pass2_xy<double, N0, N1, N2, ZD::NTILE, ND, false, false, PFD>), g2, dim3(round64(ND)), 0, s, a, tasks, pq);
   if (ev) (void)hipEventRecord(ev[2], s);
-  constexpr bool P32 = prefetch3_for<float, N>(), P64 = prefetch3_for<double, N>();
-  constexpr bool Q3F = pass3_pingpong<float, N>(), Q3D = pass3_pingpong<double, N>();
-  constexpr int NT3F = pass3_threads<float, N>(), NT3D = pass3_threads<double, N>();
-  constexpr bool S3F = pass3_staged_for<float, N>();
-  if (fp32 && S3F && store_v)
-    hipLaunchKernelGGL((pass3_staged<float, N, N, NT3F, true>), g3, dim3(NT3F), 0, s, a, tasks);
-  else if (fp32 && S3F)
-    hipLaunchKernelGGL((pass3_staged<float, N, N, NT3F, false>), g3, dim3(NT3F), 0, s, a, tasks);
-  else if (fp32 && store_v)
-    hipLaunchKernelGGL((pass3_inv_xy_acc<float, N, N, NT3F, P32, true, Q3F>), g3, dim3(NT3F), 0, s, a, tasks);
-  else if (fp32)
-    hipLaunchKernelGGL((pass3_inv_xy_acc<float, N, N, NT3F, P32, false, Q3F>), g3, dim3(NT3F), 0, s, a, tasks);
-  else if (store_v)
-    hipLaunchKernelGGL((pass3_inv_xy_acc<double, N, N, NT3D, P64, true, Q3D>), g3, dim3(NT3D), 0, s, a, tasks);
-  else
-    hipLaunchKernelGGL((pass3_inv_xy_acc<double, N, N, NT3D, P64, false, Q3D>), g3, dim3(NT3D), 0, s, a, tasks);
+  int gj = 0;
+  if (!d.store_v) {
+    if (fp32) hipLaunchKernelGGL((pass3_z<float, N0, N1, N2, VF, false, 1>), dim3(tile_grid(ntile3), d.max_ic, d.ntasks), dim3(YF::NT), 0, s, a, tasks);
+    else hipLaunchKernelGGL((pass3_z<double, N0, N1, N2, VD, false, 1>), dim3(tile_grid(ntile3), d.max_ic, d.ntasks), dim3(YD::NT), 0, s, a, tasks);
+  } else {
+    constexpr int GF = col_group(true, YF::RS), GD = col_group(false, YD::RS);
+    gj = fp32 ? GF : GD;
+    if (small_group(ntile3, d.max_jc, gj, d.ntasks)) gj = 1;
+    const dim3 g3(tile_grid(ntile3), (d.max_jc + gj - 1) / gj, d.ntasks);
+    if (fp32 && gj > 1) hipLaunchKernelGGL((pass3_z<float, N0, N1, N2, VF, true, GF>), g3, dim3(YF::NT), 0, s, a, tasks);
+    else if (fp32) hipLaunchKernelGGL((pass3_z<float, N0, N1, N2, VF, true, 1>), g3, dim3(YF::NT), 0, s, a, tasks);
+    else if (gj > 1) hipLaunchKernelGGL((pass3_z<double, N0, N1, N2, VD, true, GD>), g3, dim3(YD::NT), 0, s, a, tasks);
+    else hipLaunchKernelGGL((pass3_z<double, N0, N1, N2, VD, true, 1>), g3, dim3(YD::NT), 0, s, a, tasks);
+  }
   if (ev) (void)hipEventRecord(ev[3], s);
-  return hipGetLastError();
+  hipError_t e = hipGetLastError();
+  if (e == hipSuccess && d.store_v) e = launch_pass4(fp32, a, d, gj, size_t(N0) * N1 * N2, tasks, s);
+  if (ev) (void)hipEventRecord(ev[4], s);
+  return e;
 }
 
-// ---------------------------------------------------------------- other grids
-// Grids whose three lengths differ (the wavefunction grids of the paper's
-// 768- and 1536-atom cells, 60 x 60 x 90 and 60 x 90 x 120): configurations
-// derived from the plans plus a few choices measured at 60 x 90 x 120 (FP32,
-// per 1,024-pair launch, same box).  Slab kernels (passes 1, 3): threads = the
-// largest stage's butterfly count rounded up to whole waves, at most 768 (12
-// waves leave 170 registers per thread at one workgroup per CU; 960 threads
-// spilled in pass 3, 512 were 25 % slower); ping-pong slabs where two fit; the
-// FP32 form prefetches the next density orbital in pass 1 (2.27 -> 1.90 ms) and
-// runs pass 3 staged through LDS (3.55 -> 2.23 ms).  Pass 2: see
-// shape_sections; one pair per workgroup.  A build may override these for
-// timing (PX_SH_* below).
-#ifndef PX_SH_NT_CAP
-#define PX_SH_NT_CAP 768
-#endif
-#ifndef PX_SH_PF1
-#define PX_SH_PF1 1
-#endif
-#ifndef PX_SH_STG3
-#define PX_SH_STG3 1
-#endif
-constexpr int wave_threads(int butterflies, int cap) {
-  const int t = (butterflies + 63) / 64 * 64;
-  return t < cap ? t : cap;
-}
-template <int N0, int N1> constexpr int slab_threads() {
-  int m = 0;
-  for (int s = 0; s < Plan<N0>::nst; ++s) m = m > N1 * (N0 / Plan<N0>::rad[s]) ? m : N1 * (N0 / Plan<N0>::rad[s]);
-  for (int s = 0; s < Plan<N1>::nst; ++s) m = m > N0 * (N1 / Plan<N1>::rad[s]) ? m : N0 * (N1 / Plan<N1>::rad[s]);
-  return wave_threads(m, PX_SH_NT_CAP);
-}
-template <int NX, int N2> constexpr int plane_threads() {
-  int m = 0;
-  for (int s = 0; s < Plan<N2>::nst; ++s) m = m > NX * (N2 / Plan<N2>::rad[s]) ? m : NX * (N2 / Plan<N2>::rad[s]);
-  return wave_threads(m, 1024);
-}
-
+// Passes 1 to 4 of one chunk (tasks == nullptr, the chunk in `a`) or of the
+// chunks of a task table in device memory, one per blockIdx.z (d: the largest
+// sizes of the table).  ev (optional, 5 events) brackets the passes.
 template <int N0, int N1, int N2>
-hipError_t launch_chunk_shape(bool fp32, const ChunkArgs& a, int npairs, bool ex, bool store_v,
-                              hipStream_t s, hipEvent_t* ev, const ChunkArgs* tasks, int ntasks,
-                              int max_ic) {
-  if (!tasks) {
-    ntasks = 1;
-    max_ic = a.ic;
-  }
-  constexpr int NT1 = slab_threads<N0, N1>();
-  constexpr bool PPF = pingpong_fits<float, N0, N1>(), PPD = pingpong_fits<double, N0, N1>();
-  constexpr int XF = shape_sections(true, N0, N2), XD = shape_sections(false, N0, N2);
-  constexpr int NT2F = plane_threads<N0 / XF, N2>(), NT2D = plane_threads<N0 / XD, N2>();
-  const dim3 g1(N2, max_ic, ntasks), g2f(N1 * XF, npairs, ntasks), g2d(N1 * XD, npairs, ntasks);
-  if (ev) (void)hipEventRecord(ev[0], s);
-  if (fp32)
-    hipLaunchKernelGGL((pass1_fwd_xy<float, N0, N1, NT1, true, bool(PX_SH_PF1), PPF>), g1, dim3(NT1), 0, s, a, tasks);
-  else
-    hipLaunchKernelGGL((pass1_fwd_xy<double, N0, N1, NT1, false, false, PPD>), g1, dim3(NT1), 0, s, a, tasks);
-  if (ev) (void)hipEventRecord(ev[1], s);
-  if (fp32 && ex)
-    hipLaunchKernelGGL((pass2_z_kernel<float, N0, N1, N2, NT2F, true, true, 1, false, XF>), g2f, dim3(NT2F), 0, s, a, tasks);
-  else if (fp32)
-    hipLaunchKernelGGL((pass2_z_kernel<float, N0, N1, N2, NT2F, true, false, 1, false, XF>), g2f, dim3(NT2F), 0, s, a, tasks);
-  else if (ex)
-    hipLaunchKernelGGL((pass2_z_kernel<double, N0, N1, N2, NT2D, false, true, 1, false, XD>), g2d, dim3(NT2D), 0, s, a, tasks);
-  else
-    hipLaunchKernelGGL((pass2_z_kernel<double, N0, N1, N2, NT2D, false, false, 1, false, XD>), g2d, dim3(NT2D), 0, s, a, tasks);
-  if (ev) (void)hipEventRecord(ev[2], s);
-  if (fp32) {
-    if constexpr (PX_SH_STG3 != 0) {
-      if (store_v)
-        hipLaunchKernelGGL((pass3_staged<float, N0, N1, NT1, true>), g1, dim3(NT1), 0, s, a, tasks);
-      else
-        hipLaunchKernelGGL((pass3_staged<float, N0, N1, NT1, false>), g1, dim3(NT1), 0, s, a, tasks);
-    } else {
-      if (store_v)
-        hipLaunchKernelGGL((pass3_inv_xy_acc<float, N0, N1, NT1, false, true, PPF>), g1, dim3(NT1), 0, s, a, tasks);
-      else
-        hipLaunchKernelGGL((pass3_inv_xy_acc<float, N0, N1, NT1, false, false, PPF>), g1, dim3(NT1), 0, s, a, tasks);
-    }
-  } else if (store_v)
-    hipLaunchKernelGGL((pass3_inv_xy_acc<double, N0, N1, NT1, false, true, PPD>), g1, dim3(NT1), 0, s, a, tasks);
-  else
-    hipLaunchKernelGGL((pass3_inv_xy_acc<double, N0, N1, NT1, false, false, PPD>), g1, dim3(NT1), 0, s, a, tasks);
-  if (ev) (void)hipEventRecord(ev[3], s);
-  return hipGetLastError();
+hipError_t launch_chunk_t(bool fp32, const ChunkArgs& a, const ChunkDims& d, bool ex, int cfg,
+                          hipStream_t s, hipEvent_t* ev, const ChunkArgs* tasks) {
+  return cfg == 0 ? launch_chunk_cfg<N0, N1, N2, 0>(fp32, a, d, ex, s, ev, tasks)
+                  : launch_chunk_cfg<N0, N1, N2, 1>(fp32, a, d, ex, s, ev, tasks);
 }
 
 }  // namespace px

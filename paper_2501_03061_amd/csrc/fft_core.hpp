@@ -14,13 +14,14 @@
 // registers.
 //
 // Forward transforms use exp(-i...), inverse exp(+i...), both unnormalised.
-// Twiddles come from a table of the N-th roots of unity (FP64 sincospi,
-// rounded for FP32), held in LDS; powers w^r are formed by repeated complex
-// multiplication.  Composite radices (6, 9, 10, 12) are Cooley-Tukey in
+// Twiddles come from a table per stage of the N-th roots of unity (compile-time
+// FP64 values, rounded for FP32), held in LDS.  Composite radices (6, 9, 10, 12) are Cooley-Tukey in
 // registers with compile-time twiddles.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 namespace px {
 
@@ -174,6 +175,10 @@ template <typename T, int A, int B, bool INV> __device__ __forceinline__ void df
     for (int q = 0; q < B; ++q) {
       if (a == 0 || q == 0) {
         u[a][q] = s[q];
+      } else if (2 * a * q == R) {  // w^(R/2) = -1
+        u[a][q] = {-s[q].x, -s[q].y};
+      } else if (4 * a * q == R) {  // w^(R/4) = -+i
+        u[a][q] = mul_mi<T, INV>(s[q]);
       } else {
         constexpr const RootTable<R>& tab = kRoots<R>;
         const T c = T(tab.c[(a * q) % R]);
@@ -264,40 +269,28 @@ template <int N, int NL, int LS, int ES, bool LINE_FAST> struct Lines {
   static constexpr bool line_fast = LINE_FAST;
 };
 
-template <class G, int R> __device__ __forceinline__ void decode(int b, int& line, int& j) {
-  if constexpr (G::line_fast) {
-    line = b % G::nl;
-    j = b / G::nl;
-  } else {
-    j = b % (G::n / R);
-    line = b / (G::n / R);
-  }
-}
-
-template <int N, int R> constexpr int butterflies_per_thread(int nl, int nt) {
-  return (nl * (N / R) + nt - 1) / nt;
-}
-
-// Twiddle w^(r*k) for r = 1..R-1 applied in place; k = j mod NS, base root
-// index k*(N/(NS*R)) in the N-entry table (forward table; inverse conjugates).
-// FP32: every power is read from the table (each correctly rounded from FP64),
-// so the transform carries no error growth from repeated products (measured:
-// the same speed, a 4x smaller FP32 energy error at 96^3).  FP64: powers by
-// repeated multiplication (error r * 1e-16, far below tolerance).
+// Twiddles of a second stage (radix R, span NS, N = NS R): w^(r k), r = 1..R-1,
+// k = j mod NS, applied in place from the stage's own table t[r NS + k] = w_N^(r k)
+// (N entries, see fill_stage_table), so that a thread's factors lie at constant
+// distances from one address.  FP32: every power is read (each correctly
+// rounded from FP64), so the transform carries no error growth from repeated
+// products (measured: the same speed, a 4x smaller FP32 energy error at 96^3).
+// FP64: powers by repeated multiplication (error r * 1e-16, far below
+// tolerance), which keeps registers free.
 template <typename T, int N, int R, int NS, bool INV>
-__device__ __forceinline__ void twiddle(cpx<T>* v, int j, const cpx<T>* tw) {
+__device__ __forceinline__ void twiddle(cpx<T>* v, int j, const cpx<T>* t) {
   if constexpr (NS == 1) return;
-  const int k = j % NS;
-  constexpr int STEP = N / (NS * R);
+  static_assert(NS == 1 || NS * R == N, "second of two stages");
+  const cpx<T>* const tk = t + j % NS;
   if constexpr (sizeof(T) == 4) {
 #pragma unroll
     for (int r = 1; r < R; ++r) {
-      cpx<T> w = tw[r * k * STEP];
+      cpx<T> w = tk[r * NS];
       if (INV) w.y = -w.y;
       v[r] = cmul(v[r], w);
     }
   } else {
-    cpx<T> w = tw[k * STEP];
+    cpx<T> w = tk[NS];
     if (INV) w.y = -w.y;
     cpx<T> wr = w;
 #pragma unroll
@@ -313,73 +306,75 @@ template <int R, int NS> __device__ __forceinline__ int out_pos(int j, int r) {
   return (j / NS) * NS * R + (j % NS) + r * NS;
 }
 
+// A workgroup barrier that waits only for this wave's LDS accesses: global ->
+// LDS transfers and loads in flight stay in flight across it.  (The fence of
+// __syncthreads would wait for every outstanding vector memory operation.)
+// The signal fences keep the compiler from moving memory accesses across it.
+__device__ __forceinline__ void lds_sync() {
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+  __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0); vmcnt and expcnt not waited for
+  __builtin_amdgcn_s_barrier();
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+}
+
+// Slots of a stage of geometry G (lines fastest) shared by NA threads, a
+// multiple of the line count: thread t keeps its line, and slot k is butterfly
+// j = t / nl + k NA/nl of it.  When the butterflies do not fill the last slot,
+// the waves whose lanes all lie past the last butterfly take one slot less, and
+// the other lanes past it repeat it (the same values to the same addresses),
+// so that the code of a slot has no branches: conditional loads were waited
+// for one by one and copied.
+template <class G, int R, int NA> constexpr int slots() {
+  static_assert(G::line_fast && NA % G::nl == 0, "whole lines per thread row");
+  return (G::n / R + NA / G::nl - 1) / (NA / G::nl);
+}
+template <class G, int R, int NA> __device__ __forceinline__ void slot(int t, int k, int& line, int& j) {
+  constexpr int STEP = NA / G::nl, NJ = G::n / R;
+  if (NA % 64 != 0) t = t < NA ? t : NA - 1;
+  line = t % G::nl;
+  j = t / G::nl + k * STEP;
+  if (NJ % STEP != 0) j = j < NJ ? j : NJ - 1;
+}
+// f(integral_constant<int, S>) with the wave's slots S.
+template <class G, int R, int NA, class F> __device__ __forceinline__ void by_slots(F&& f) {
+  constexpr int S = slots<G, R, NA>(), STEP = NA / G::nl, NJ = G::n / R;
+  if constexpr (NJ % STEP == 0) {
+    f(std::integral_constant<int, S>{});
+  } else {
+    const int w0 = __builtin_amdgcn_readfirstlane(int(threadIdx.x) & ~63);  // the wave's first (smallest) thread
+    if (w0 / G::nl + (S - 1) * STEP < NJ) f(std::integral_constant<int, S>{});
+    else f(std::integral_constant<int, S - 1>{});
+  }
+}
+
 // One LDS -> LDS Stockham stage over all lines of geometry G, in place: every
 // thread loads its butterflies into registers, the block synchronises, then
 // each butterfly is transformed and written back.  Ends with a barrier.
-template <typename T, class G, int R, int NS, bool INV, int NT>
-__device__ __forceinline__ void stage_lds(cpx<T>* lds, const cpx<T>* tw) {
-  constexpr int NB = G::nl * (G::n / R);
-  constexpr int BPT = (NB + NT - 1) / NT;
-  cpx<T> v[BPT][R];
-  const int tid = threadIdx.x;
+template <typename T, class G, int R, int NS, bool INV, int NA>
+__device__ __forceinline__ void stage_lds(cpx<T>* lds, const cpx<T>* tw, int t) {
+  by_slots<G, R, NA>([&](auto sc) {
+    constexpr int S = decltype(sc)::value;
+    cpx<T> v[S > 0 ? S : 1][R];
 #pragma unroll
-  for (int k = 0; k < BPT; ++k) {
-    const int b = tid + k * NT;
-    if (NB % NT == 0 || b < NB) {
+    for (int k = 0; k < S; ++k) {
       int line, j;
-      decode<G, R>(b, line, j);
+      slot<G, R, NA>(t, k, line, j);
 #pragma unroll
       for (int r = 0; r < R; ++r) v[k][r] = lds[line * G::ls + (j + r * (G::n / R)) * G::es];
     }
-  }
-  __syncthreads();
+    lds_sync();
 #pragma unroll
-  for (int k = 0; k < BPT; ++k) {
-    const int b = tid + k * NT;
-    if (NB % NT == 0 || b < NB) {
+    for (int k = 0; k < S; ++k) {
       int line, j;
-      decode<G, R>(b, line, j);
+      slot<G, R, NA>(t, k, line, j);
       twiddle<T, G::n, R, NS, INV>(v[k], j, tw);
       dft<T, R, INV>(v[k]);
 #pragma unroll
       for (int r = 0; r < R; ++r) lds[line * G::ls + out_pos<R, NS>(j, r) * G::es] = v[k][r];
+      __builtin_amdgcn_sched_barrier(0);  // one butterfly's temporaries at a time
     }
-  }
-  __syncthreads();
-}
-
-// One out-of-place Stockham stage, src -> dst (both LDS, same geometry).  No
-// barrier inside: the caller separates stages that depend on each other.
-template <typename T, class G, int R, int NS, bool INV, int NT>
-__device__ __forceinline__ void stage_pp(const cpx<T>* src, cpx<T>* dst, const cpx<T>* tw) {
-  constexpr int NB = G::nl * (G::n / R);
-  constexpr int BPT = (NB + NT - 1) / NT;
-#pragma unroll
-  for (int k = 0; k < BPT; ++k) {
-    const int b = threadIdx.x + k * NT;
-    if (NB % NT == 0 || b < NB) {
-      int line, j;
-      decode<G, R>(b, line, j);
-      cpx<T> v[R];
-#pragma unroll
-      for (int r = 0; r < R; ++r) v[r] = src[line * G::ls + (j + r * (G::n / R)) * G::es];
-      twiddle<T, G::n, R, NS, INV>(v, j, tw);
-      dft<T, R, INV>(v);
-#pragma unroll
-      for (int r = 0; r < R; ++r) dst[line * G::ls + out_pos<R, NS>(j, r) * G::es] = v[r];
-    }
-  }
-}
-
-// Run stages [S0, S1) of the length-N transform over geometry G, LDS -> LDS,
-// in the forward (REV = false) or reversed radix order.
-template <typename T, class G, bool INV, int NT, int S, int S1, bool REV = INV>
-__device__ __forceinline__ void stages_lds(cpx<T>* lds, const cpx<T>* tw) {
-  if constexpr (S < S1) {
-    using St = StageOf<G::n, S, REV>;
-    stage_lds<T, G, St::R, St::NS, INV, NT>(lds, tw);
-    stages_lds<T, G, INV, NT, S + 1, S1, REV>(lds, tw);
-  }
+    lds_sync();
+  });
 }
 
 }  // namespace px

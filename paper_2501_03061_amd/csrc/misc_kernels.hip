@@ -92,13 +92,37 @@ hipError_t launch_convert_f64_f32(size_t n, const double* src, float* dst, hipSt
   return hipGetLastError();
 }
 
-// Pair energy S_ij = sum_G K |rho_ij(G)|^2 from the per-plane partials.
+// [z][y][x] -> [z][x][y] through 32 x 32 LDS tiles.
+template <typename K>
+__global__ __launch_bounds__(256) void kernel_transpose_k(int n0, int n1, const double* kern, K* kt) {
+  __shared__ K tile[32][33];
+  const size_t z = size_t(blockIdx.z) * n0 * n1;
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  const int x0 = blockIdx.x * 32, y0 = blockIdx.y * 32;
+#pragma unroll
+  for (int r = ty; r < 32; r += 8)
+    if (x0 + tx < n0 && y0 + r < n1) tile[r][tx] = K(kern[z + size_t(y0 + r) * n0 + x0 + tx]);
+  __syncthreads();
+#pragma unroll
+  for (int r = ty; r < 32; r += 8)
+    if (x0 + r < n0 && y0 + tx < n1) kt[z + size_t(x0 + r) * n1 + y0 + tx] = tile[tx][r];
+}
+
+hipError_t launch_kernel_transpose(bool fp32, int n0, int n1, int n2, const double* kern, void* kt,
+                                   hipStream_t s) {
+  const dim3 g((n0 + 31) / 32, (n1 + 31) / 32, n2);
+  if (fp32) hipLaunchKernelGGL(kernel_transpose_k<float>, g, dim3(256), 0, s, n0, n1, kern, static_cast<float*>(kt));
+  else hipLaunchKernelGGL(kernel_transpose_k<double>, g, dim3(256), 0, s, n0, n1, kern, static_cast<double*>(kt));
+  return hipGetLastError();
+}
+
+// Pair energy S_ij = sum_G K |rho_ij(G)|^2 from the per-slab partials.
 // FP32 form: S = K(0)|rho(0)|^2 + A * (N_g E_r - |rho(0)|^2) / B, where A and B
 // are the FP32-transform sums of K|rho|^2 and |rho|^2 over G != 0, E_r the
 // FP64 energy of the transform input and rho(0) its FP64 sum: the transform's
 // systematic norm drift (about 1e-7 relative in FP32) cancels in A / B.
-// One wave per pair: lane l adds the planes y = l, l + 64, ... (and the z
-// slabs likewise), then the wave adds its lanes in a fixed butterfly order.
+// One wave per pair: lane l adds the slabs kz = l, l + 64, ... (and the z
+// tiles likewise), then the wave adds its lanes in a fixed butterfly order.
 // (One thread per pair, as before, left a 1,024-pair chunk to four
 // workgroups that walked 432 values each: 42 us per chunk at 72^3.)
 __device__ __forceinline__ double lane_sum(double v) {
@@ -107,25 +131,25 @@ __device__ __forceinline__ double lane_sum(double v) {
   return v;
 }
 
-__device__ __forceinline__ double pair_energy(const double* expart, const G0Part* g0, int p, int n1,
-                                              int n2, double ng, int lane) {
+__device__ __forceinline__ double pair_energy(const double* expart, const G0Part* g0, int p, int n2,
+                                              int ntile, double ng, int lane) {
   if (g0 == nullptr) {
     double s = 0.0;
-    for (int y = lane; y < n1; y += 64) s += expart[size_t(p) * n1 + y];
+    for (int k = lane; k < n2; k += 64) s += expart[size_t(p) * n2 + k];
     return lane_sum(s);
   }
   double a = 0.0, b = 0.0, e0 = 0.0;
-  for (int y = lane; y < n1; y += 64) {
-    const double* e = expart + (size_t(p) * n1 + y) * 3;
+  for (int k = lane; k < n2; k += 64) {
+    const double* e = expart + (size_t(p) * n2 + k) * 3;
     a += e[0];
     b += e[1];
     e0 += e[2];
   }
   double sr = 0.0, si = 0.0, er = 0.0;
-  for (int z = lane; z < n2; z += 64) {
-    sr += g0[size_t(p) * n2 + z].re;
-    si += g0[size_t(p) * n2 + z].im;
-    er += g0[size_t(p) * n2 + z].en;
+  for (int z = lane; z < ntile; z += 64) {
+    sr += g0[size_t(p) * ntile + z].re;
+    si += g0[size_t(p) * ntile + z].im;
+    er += g0[size_t(p) * ntile + z].en;
   }
   a = lane_sum(a);
   b = lane_sum(b);
@@ -138,7 +162,7 @@ __device__ __forceinline__ double pair_energy(const double* expart, const G0Part
 }
 
 __global__ __launch_bounds__(256) void expart_reduce_k(const double* expart, const G0Part* g0,
-                                                       int n1, int n2, double ng, int i0, int ic,
+                                                       int n2, int ntile, double ng, int i0, int ic,
                                                        int j0, int jc, double* S, int lds,
                                                        int mirror, int tri) {
   const int p = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -146,18 +170,18 @@ __global__ __launch_bounds__(256) void expart_reduce_k(const double* expart, con
   const int ii = p / jc, jj = p % jc;
   if (tri && jj > ii) return;  // a triangular block solves jj <= ii only
   if (tri) mirror = jj < ii;
-  const double s = pair_energy(expart, g0, p, n1, n2, ng, lane);
+  const double s = pair_energy(expart, g0, p, n2, ntile, ng, lane);
   if (lane == 0) {
     S[size_t(i0 + ii) * lds + (j0 + jj)] = s;
     if (mirror) S[size_t(j0 + jj) * lds + (i0 + ii)] = s;  // S_ji = S_ij for a real even kernel
   }
 }
 
-hipError_t launch_expart_reduce(const double* expart, const G0Part* g0, int n1, int n2, double ng,
+hipError_t launch_expart_reduce(const double* expart, const G0Part* g0, int n2, int ntile, double ng,
                                 int i0, int ic, int j0, int jc, double* S, int lds, bool mirror,
                                 bool tri, hipStream_t s) {
   const int np = ic * jc;
-  hipLaunchKernelGGL(expart_reduce_k, dim3((np + 3) / 4), dim3(256), 0, s, expart, g0, n1, n2,
+  hipLaunchKernelGGL(expart_reduce_k, dim3((np + 3) / 4), dim3(256), 0, s, expart, g0, n2, ntile,
                      ng, i0, ic, j0, jc, S, lds, int(mirror), int(tri));
   return hipGetLastError();
 }
@@ -165,13 +189,13 @@ hipError_t launch_expart_reduce(const double* expart, const G0Part* g0, int n1, 
 // The same reduction for every chunk of a task table (S, its stride and the
 // mirror flag taken from each task).
 __global__ __launch_bounds__(256) void expart_reduce_tasks_k(const ChunkArgs* tasks, int fp32,
-                                                             int n1, int n2, double ng) {
+                                                             int n2, int ntile, double ng) {
   const ChunkArgs& a = tasks[blockIdx.y];
   const int p = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (p >= a.ic * a.jc) return;  // wave-uniform
   const int ii = p / a.jc, jj = p % a.jc;
   if (a.tri && jj > ii) return;  // a triangular block solves jj <= ii only
-  const double s = pair_energy(a.expart, fp32 ? a.g0 : nullptr, p, n1, n2, ng, lane);
+  const double s = pair_energy(a.expart, fp32 ? a.g0 : nullptr, p, n2, ntile, ng, lane);
   if (lane == 0) {
     a.S[size_t(a.i0 + ii) * a.s_ld + (a.j0 + jj)] = s;
     if (a.store_v && (!a.tri || jj < ii)) a.S[size_t(a.j0 + jj) * a.s_ld + (a.i0 + ii)] = s;
@@ -179,9 +203,9 @@ __global__ __launch_bounds__(256) void expart_reduce_tasks_k(const ChunkArgs* ta
 }
 
 hipError_t launch_expart_reduce_tasks(bool fp32, const ChunkArgs* tasks, int ntasks, int max_slots,
-                                      int n1, int n2, double ng, hipStream_t s) {
+                                      int n2, int ntile, double ng, hipStream_t s) {
   hipLaunchKernelGGL(expart_reduce_tasks_k, dim3((max_slots + 3) / 4, ntasks), dim3(256), 0, s,
-                     tasks, int(fp32), n1, n2, ng);
+                     tasks, int(fp32), n2, ntile, ng);
   return hipGetLastError();
 }
 

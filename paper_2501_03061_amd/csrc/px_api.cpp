@@ -35,7 +35,7 @@ struct px_context {
   };
   std::vector<StatusWord> last_status;
   int latched = PX_OK;
-  // (n0,n1,n2,prec) -> pair chunk ic x jc and the pass-2 configuration (0, 1)
+  // (n0,n1,n2,prec) -> pair chunk ic x jc and the z-tile configuration (0, 1)
   std::map<std::tuple<int, int, int, int>, std::tuple<int, int, int>> tuning;
   // measurement mode: HIP events around each pass of each chunk
   bool profiling = false;
@@ -49,7 +49,6 @@ struct px_context {
   double ace_ms[4] = {0, 0, 0, 0};
   int64_t ace_calls = 0;
   bool symmetric_ace = true;  // ACE build solves only pairs j <= i (block level)
-  bool tri_diag = true;       // ... and within the diagonal blocks (pair level)
   // batched form: the graph of the last batched call, replayed while the call
   // signature (instances, pointers, workspace) stays the same
   bool use_graph = true;
@@ -114,10 +113,10 @@ bool misaligned(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) !=
 size_t elem_bytes(px_precision p) { return p == PX_PREC_FP32 ? 8 : 16; }
 
 void default_tuning(const px_cell* cell, px_precision prec, int* ic, int* jc) {
-  // ic output orbitals x jc density orbitals per chunk.  Pass 1 and 3 launch
-  // n2 * ic workgroups and loop over jc pairs each; larger chunks amortise the
-  // phi slab and the output read-modify-write (measured best near 32 x 16 at
-  // 72^3 in both precisions).  The pair buffer holds ic*jc slabs.
+  // ic output orbitals x jc density orbitals per chunk.  Passes 1 and 3 launch
+  // ic workgroups per tile and loop over jc pairs each; larger chunks amortise
+  // the phi tiles and the output read-modify-write.  The pair buffer holds
+  // ic*jc slabs.
   (void)cell;
   (void)prec;
   *ic = 32;
@@ -139,7 +138,7 @@ void tuning_for(const px_context* c, const px_cell* cell, px_precision prec, int
 
 // Workspace layout of one exchange application.
 struct ExLayout {
-  size_t t, g0, expart, S, k32, end;
+  size_t t, g0, expart, S, kt, end;
 };
 
 ExLayout ex_layout(const px_cell* cell, px_precision prec, int n_psi, int n_phi, int ic, int jc,
@@ -151,17 +150,17 @@ ExLayout ex_layout(const px_cell* cell, px_precision prec, int n_psi, int n_phi,
   l.t = off;
   off = align_up(off + pairs * ngrid(cell) * elem_bytes(prec));
   l.g0 = off;
-  if (prec == PX_PREC_FP32) off = align_up(off + pairs * cell->n[2] * sizeof(px::G0Part));
+  if (prec == PX_PREC_FP32)
+    off = align_up(off + pairs * px::ztile_count(true, cell->n, p2) * sizeof(px::G0Part));
   l.expart = off;
   l.S = off;
   if (energy) {
-    const size_t slots = size_t(cell->n[1]) * px::pass2_sections_grid(prec == PX_PREC_FP32, cell->n, p2);
-    off = align_up(off + pairs * slots * 8 * (prec == PX_PREC_FP32 ? 3 : 1));
+    off = align_up(off + pairs * cell->n[2] * 8 * (prec == PX_PREC_FP32 ? 3 : 1));
     l.S = off;
     off = align_up(off + size_t(n_phi) * n_psi * 8);
   }
-  l.k32 = off;
-  if (prec == PX_PREC_FP32) off = align_up(off + ngrid(cell) * sizeof(float));
+  l.kt = off;
+  off = align_up(off + ngrid(cell) * (prec == PX_PREC_FP32 ? sizeof(float) : sizeof(double)));
   l.end = off;
   return l;
 }
@@ -359,10 +358,9 @@ px_status need_ws(px_context* c, size_t bytes) {
 // Enqueue the pair pipeline; `out` gets Vx phi.  With energy, S[i][j]
 // receives sum_G K |rho_ij(G)|^2 per pair.  Symmetric mode (phi is psi): the
 // orbitals are cut into square blocks of B = max(ic, jc); only blocks J <= I
-// are solved, and for J < I pass 3 keeps v_ij so that pass 4 adds the
-// transposed contributions to the J block (v_ji = conj(v_ij)).  A diagonal
-// block J = I is solved as its lower triangle j <= i (pass 4 adds the pairs
-// j < i), so every unordered pair is solved once.
+// are solved, and pass 3 adds the transposed contributions to the J block
+// (v_ji = conj(v_ij)) beside those to the I block.  A diagonal block J = I is
+// solved as its lower triangle j <= i, so every unordered pair is solved once.
 px_status run_exchange(px_context* c, const px_cell* cell, px_precision prec, int n_psi,
                        const void* psi, const double* occ, int n_phi, const void* phi,
                        const double* kern, void* out, const ExLayout& l, bool energy, int ic,
@@ -376,16 +374,16 @@ px_status run_exchange(px_context* c, const px_cell* cell, px_precision prec, in
   a.out = out;
   a.occ = occ;
   a.kern = kern;
-  if (fp32) {
-    // the FP32 form multiplies by K(G) rounded to FP32 (K(0) stays FP64)
-    float* k32 = reinterpret_cast<float*>(c->ws + l.k32);
-    px_status st = hip_check(c, px::launch_convert_f64_f32(ng, kern, k32, s), "kernel to FP32");
+  // the table as pass 2 reads it; the FP32 form multiplies by K(G) rounded to
+  // FP32 (K(0) stays FP64)
+  a.kt = c->ws + l.kt;
+  {
+    px_status st = hip_check(c, px::launch_kernel_transpose(fp32, cell->n[0], cell->n[1], cell->n[2], kern,
+                                                            c->ws + l.kt, s), "kernel table");
     if (st != PX_OK) return st;
-    a.kern32 = k32;
   }
   a.g0 = reinterpret_cast<px::G0Part*>(c->ws + l.g0);
   a.expart = reinterpret_cast<double*>(c->ws + l.expart);
-  a.n2 = cell->n[2];
   a.inv_ng = 1.0 / double(ng);
   double* S = reinterpret_cast<double*>(c->ws + l.S);
   if (symmetric) ic = jc = (ic > jc ? ic : jc);
@@ -408,35 +406,26 @@ px_status run_exchange(px_context* c, const px_cell* cell, px_precision prec, in
       a.j0 = j0;
       a.jc = (n_psi - j0) < jc ? (n_psi - j0) : jc;
       a.first = j0 == 0;
-      // a diagonal block is solved as its lower triangle and keeps v_ij for
-      // the transposed pass like the blocks below it
-      a.tri = symmetric && c->tri_diag && j0 == i0 && a.ic == a.jc;
-      a.store_v = symmetric && (j0 < i0 || a.tri);
+      // a diagonal block is solved as its lower triangle
+      a.tri = symmetric && j0 == i0;
+      a.store_v = symmetric;
       const int npairs = px::chunk_pairs(a);
       hipEvent_t* ev = c->profiling ? &c->events[5 * nchunks] : nullptr;
       px_status st = hip_check(
-          c, px::launch_chunk(fp32, cell->n, a, npairs, energy, p2, s, ev), "pair pipeline");
+          c, px::launch_chunk(fp32, cell->n, a, energy, p2, s, ev), "pair pipeline");
       if (st != PX_OK) return st;
-      if (a.store_v) {
-        st = hip_check(c, px::launch_pass4(fp32, a, ng, s), "transposed accumulation");
-        if (st != PX_OK) return st;
-      }
       if (c->profiling) {
-        (void)hipEventRecord(c->events[5 * nchunks + 4], s);
         // algorithmic bytes of the 6 N_g b pair model, 2 N_g b per solved pair
         // in each pass (pass 1: read psi_j, write the pair slab; pass 2: read
-        // and rewrite it; pass 3: read it and psi_j).  The symmetric mode's
-        // kept v_ij is outside the model: pass 3 writes it (not counted here)
-        // and pass 4 reads it back, N_g b per pair below the diagonal (a
-        // triangular block keeps v_ij for its npairs pairs; pass 4 reads the
-        // npairs - ic of them below the diagonal)
-        const double np = double(npairs), np4 = a.tri ? double(npairs - a.ic) : np;
+        // and rewrite it; pass 3: read it and psi_j).  Pass 4 (row sums read,
+        // outputs read and written) is outside the model: 2 N_g b per row
+        const double np = double(npairs);
         for (int k = 0; k < 3; ++k) {
           c->prof_bytes[k] += 2.0 * pair_bytes * np;
           c->prof_launches[k] += 1;
         }
         if (a.store_v) {
-          c->prof_bytes[3] += pair_bytes * np4;
+          c->prof_bytes[3] += 2.0 * pair_bytes * a.ic;
           c->prof_launches[3] += 1;
         }
         has4.push_back(a.store_v);
@@ -444,8 +433,7 @@ px_status run_exchange(px_context* c, const px_cell* cell, px_precision prec, in
       ++nchunks;
       if (energy) {
         st = hip_check(c, px::launch_expart_reduce(a.expart, fp32 ? a.g0 : nullptr,
-                                                   cell->n[1] * px::pass2_sections_grid(fp32, cell->n, p2),
-                                                   cell->n[2], double(ng), i0, a.ic, j0, a.jc, S,
+                                                   cell->n[2], px::ztile_count(fp32, cell->n, p2), double(ng), i0, a.ic, j0, a.jc, S,
                                                    n_psi, a.store_v != 0, a.tri != 0, s),
                        "energy partials");
         if (st != PX_OK) return st;
@@ -1219,11 +1207,9 @@ namespace {
 
 struct BatchWave {
   int g[3];         // grid of the wave's instances
-  int p2;           // pass-2 configuration of that size
+  int p2;           // z-tile configuration of that grid
   int first, count; // tasks [first, first + count)
   int max_ic, max_jc, max_pairs, max_slots;  // max_pairs: solved pairs; max_slots: ic * jc
-  bool any_v;       // its tasks keep v_ij for pass 4 (a wave holds one block diagonal, so
-                    // all of its tasks or none)
 };
 
 // The ACE tail of the instances whose last chunk is in wave after_wave: their
@@ -1235,7 +1221,7 @@ struct TailGroup {
 
 struct BatchPlan {
   size_t tasks_off = 0, jobs_off = 0, table_end = 0, t_off = 0, g0_off = 0, ex_off = 0;
-  std::vector<size_t> S_off, W_off, K32_off;
+  std::vector<size_t> S_off, W_off, kt_off;
   // ACE: per instance M (unless the caller's), L (FP32: then U in complex64),
   // U and the diagonal-block inverses; per lane the Gram split partials
   std::vector<size_t> M_off, L_off, U_off, dinv_off, part_off;
@@ -1252,7 +1238,7 @@ int block_for(const px_context* c, const px_cell* cell, px_precision prec) {
   tuning_for(c, cell, prec, &ic, &jc);
   return ic > jc ? ic : jc;
 }
-int pass2_cfg_for(const px_context* c, const px_cell* cell, px_precision prec) {
+int tile_cfg_for(const px_context* c, const px_cell* cell, px_precision prec) {
   int ic, jc, p2;
   tuning_for(c, cell, prec, &ic, &jc, &p2);
   return p2;
@@ -1271,7 +1257,7 @@ BatchPlan plan_batch(const px_context* c, int n_inst, const px_instance* in, px_
   BatchPlan P;
   const bool fp32 = prec == PX_PREC_FP32;
   const size_t b = elem_bytes(prec);
-  size_t t_bytes = 0, side_pairs = 0;  // sizes of the pair buffer and of the per-plane partials
+  size_t t_bytes = 0, g0_slots = 0, ex_slots = 0;  // sizes of the pair buffer and of the partials
   // schedule: grids in order of size
   using Grid = std::array<int, 3>;
   auto grid_of = [&](int k) { return Grid{in[k].cell.n[0], in[k].cell.n[1], in[k].cell.n[2]}; };
@@ -1297,13 +1283,12 @@ BatchPlan plan_batch(const px_context* c, int n_inst, const px_instance* in, px_
     const size_t ng = size_t(gr[0]) * gr[1] * gr[2];
     const size_t cap = std::max(min_pairs, c->batch_cap_bytes / (ng * b));
     t_bytes = std::max(t_bytes, cap * ng * b);
-    // per pair: n2 slab sums (g0) and n1 * XS energy-partial slots
+    // per pair: one G = 0 sum per z tile and n2 energy-partial slots
     int p2 = 0;  // the tuning of the grid (every instance of a grid shares it)
     for (int k = 0; k < n_inst; ++k)
-      if (grid_of(k) == gr) p2 = pass2_cfg_for(c, &in[k].cell, prec);
-    const size_t per_pair = std::max(size_t(gr[1]) * px::pass2_sections_grid(fp32, gr.data(), p2),
-                                     size_t(gr[2]));
-    side_pairs = std::max(side_pairs, cap * per_pair);
+      if (grid_of(k) == gr) p2 = tile_cfg_for(c, &in[k].cell, prec);
+    g0_slots = std::max(g0_slots, cap * px::ztile_count(fp32, gr.data(), p2));
+    ex_slots = std::max(ex_slots, cap * size_t(gr[2]));
     for (int d = 0; d < max_nb; ++d) {
       std::vector<Chunk> diag;
       for (int k = 0; k < n_inst; ++k) {
@@ -1318,7 +1303,7 @@ BatchPlan plan_batch(const px_context* c, int n_inst, const px_instance* in, px_
         const int icc = std::min(ch.B, n - ch.I * ch.B), jcc = std::min(ch.B, n - ch.J * ch.B);
         const size_t pairs = size_t(icc) * jcc;
         if (used + pairs > cap) {
-          P.waves.push_back({{gr[0], gr[1], gr[2]}, p2, int(P.tasks.size()), 0, 0, 0, 0, 0, false});
+          P.waves.push_back({{gr[0], gr[1], gr[2]}, p2, int(P.tasks.size()), 0, 0, 0, 0, 0});
           used = 0;
         }
         BatchWave& w = P.waves.back();
@@ -1328,9 +1313,8 @@ BatchPlan plan_batch(const px_context* c, int n_inst, const px_instance* in, px_
         a.j0 = ch.J * ch.B;
         a.jc = jcc;
         a.first = d == 0;
-        a.tri = d == 0 && c->tri_diag && icc == jcc;
-        a.store_v = d > 0 || a.tri;
-        a.n2 = gr[2];
+        a.tri = d == 0;
+        a.store_v = 1;  // (block pairs I > J, and the triangles)
         a.inv_ng = 1.0 / double(ng);
         a.s_ld = n;
         // pointers are filled below once the layout is known; keep the
@@ -1348,7 +1332,6 @@ BatchPlan plan_batch(const px_context* c, int n_inst, const px_instance* in, px_
         // triangular block), not the block's pair slots
         w.max_pairs = std::max(w.max_pairs, px::chunk_pairs(a));
         w.max_slots = std::max(w.max_slots, int(pairs));
-        w.any_v = w.any_v || a.store_v;
         used += pairs;
       }
     }
@@ -1382,21 +1365,19 @@ BatchPlan plan_batch(const px_context* c, int n_inst, const px_instance* in, px_
   P.t_off = off;
   off = align_up(off + t_bytes);
   P.g0_off = off;
-  if (fp32) off = align_up(off + side_pairs * sizeof(px::G0Part));
+  if (fp32) off = align_up(off + g0_slots * sizeof(px::G0Part));
   P.ex_off = off;
-  off = align_up(off + side_pairs * 8 * (fp32 ? 3 : 1));
+  off = align_up(off + ex_slots * 8 * (fp32 ? 3 : 1));
   P.S_off.resize(n_inst);
   P.W_off.resize(n_inst);
-  P.K32_off.resize(n_inst);
+  P.kt_off.resize(n_inst);
   for (int k = 0; k < n_inst; ++k) {
     P.S_off[k] = off;
     off = align_up(off + size_t(in[k].n) * in[k].n * 8);
   }
-  if (fp32) {
-    for (int k = 0; k < n_inst; ++k) {
-      P.K32_off[k] = off;
-      off = align_up(off + ngrid(&in[k].cell) * sizeof(float));
-    }
+  for (int k = 0; k < n_inst; ++k) {
+    P.kt_off[k] = off;
+    off = align_up(off + ngrid(&in[k].cell) * (fp32 ? sizeof(float) : sizeof(double)));
   }
   if (ace) {
     P.M_off.resize(n_inst);
@@ -1436,13 +1417,12 @@ BatchPlan plan_batch(const px_context* c, int n_inst, const px_instance* in, px_
         const size_t pofs = reinterpret_cast<size_t>(a.t);
         const int k = int(reinterpret_cast<size_t>(a.S));
         a.t = ws + P.t_off + pofs * ng * b;
-        a.g0 = reinterpret_cast<px::G0Part*>(ws + P.g0_off + pofs * w.g[2] * sizeof(px::G0Part));
-        a.expart = reinterpret_cast<double*>(ws + P.ex_off + pofs * w.g[1] *
-                                             px::pass2_sections_grid(fp32, w.g, w.p2) * 8 *
-                                             (fp32 ? 3 : 1));
+        a.g0 = reinterpret_cast<px::G0Part*>(ws + P.g0_off + pofs * px::ztile_count(fp32, w.g, w.p2) *
+                                                                 sizeof(px::G0Part));
+        a.expart = reinterpret_cast<double*>(ws + P.ex_off + pofs * w.g[2] * 8 * (fp32 ? 3 : 1));
         a.S = reinterpret_cast<double*>(ws + P.S_off[k]);
         a.out = ace ? static_cast<void*>(ws + P.W_off[k]) : in[k].out;
-        if (fp32) a.kern32 = reinterpret_cast<const float*>(ws + P.K32_off[k]);
+        a.kt = ws + P.kt_off[k];
       }
     }
     for (size_t q = 0; q < P.jobs.size(); ++q) {
@@ -1572,31 +1552,23 @@ px_status enqueue_batch(px_context* c, const BatchPlan& P, int n_inst, const px_
                            "task table upload");
   if (st != PX_OK) return st;
   if (ace && (st = ensure_lanes(c, P.waves.size())) != PX_OK) return st;
-  if (fp32) {
-    for (int k = 0; k < n_inst; ++k) {
-      st = hip_check(c, px::launch_convert_f64_f32(ngrid(&in[k].cell), in[k].kernel_G,
-                                                   reinterpret_cast<float*>(ws + P.K32_off[k]), s),
-                     "batched kernel to FP32");
-      if (st != PX_OK) return st;
-    }
+  for (int k = 0; k < n_inst; ++k) {
+    const int32_t* n = in[k].cell.n;
+    st = hip_check(c, px::launch_kernel_transpose(fp32, n[0], n[1], n[2], in[k].kernel_G, ws + P.kt_off[k], s),
+                   "batched kernel table");
+    if (st != PX_OK) return st;
   }
   bool used[px_context::kTailLanes] = {false, false};
   size_t gi = 0;
   for (int wi = 0; wi < int(P.waves.size()) && st == PX_OK; ++wi) {
     const BatchWave& w = P.waves[wi];
     const size_t ng = size_t(w.g[0]) * w.g[1] * w.g[2];
-    st = hip_check(c, px::launch_chunk_tasks(fp32, w.g, dt + w.first, w.count, w.max_ic,
-                                             w.max_pairs, true, w.any_v, w.p2, s),
+    const px::ChunkDims dims{w.count, w.max_ic, w.max_jc, w.max_pairs, 1};
+    st = hip_check(c, px::launch_chunk_tasks(fp32, w.g, dt + w.first, dims, true, w.p2, s),
                    "batched pair pipeline");
     if (st != PX_OK) break;
-    if (w.any_v) {
-      st = hip_check(c, px::launch_pass4_tasks(fp32, dt + w.first, w.count, w.max_jc, ng, s),
-                     "batched transposed accumulation");
-      if (st != PX_OK) break;
-    }
     st = hip_check(c, px::launch_expart_reduce_tasks(fp32, dt + w.first, w.count, w.max_slots,
-                                                     w.g[1] * px::pass2_sections_grid(fp32, w.g, w.p2), w.g[2],
-                                                     double(ng), s),
+                                                     w.g[2], px::ztile_count(fp32, w.g, w.p2), double(ng), s),
                    "batched energy partials");
     if (st != PX_OK) break;
     if (gi < P.groups.size() && P.groups[gi].after_wave == wi) {
@@ -1646,7 +1618,7 @@ std::vector<unsigned char> batch_key(const px_context* c, int n_inst, const px_i
   put(&c->batch_cap_bytes, sizeof c->batch_cap_bytes);
   for (int k = 0; k < n_inst; ++k) {
     put(&in[k], sizeof(px_instance));
-    const int B = block_for(c, &in[k].cell, prec), p2 = pass2_cfg_for(c, &in[k].cell, prec);
+    const int B = block_for(c, &in[k].cell, prec), p2 = tile_cfg_for(c, &in[k].cell, prec);
     put(&B, sizeof B);
     put(&p2, sizeof p2);
   }
@@ -1764,7 +1736,7 @@ px_status px_autotune(px_context* ctx, const px_cell* cell, px_precision prec, i
   hipError_t he = hipSetDevice(ctx->device);
   if (he != hipSuccess) return hip_check(ctx, he, "hipSetDevice");
   // square pair blocks B (the Hermitian-pair mode's chunks are B x B) and the
-  // two compiled pass-2 configurations; candidates whose pair buffer does not
+  // two compiled z-tile configurations; candidates whose pair buffer does not
   // fit the attached workspace are skipped
   const int cand[] = {16, 24, 32, 48, 64, 96, 128, 192, 256};
   const auto key = std::make_tuple(cell->n[0], cell->n[1], cell->n[2], int(prec));
@@ -1780,7 +1752,7 @@ px_status px_autotune(px_context* ctx, const px_cell* cell, px_precision prec, i
   for (int B : cand) {
     if (covered) break;
     covered = B >= n;
-    for (int p2 = 0; p2 < px::pass2_configs(cell->n) && st == PX_OK; ++p2) {
+    for (int p2 = 0; p2 < px::kTileConfigs && st == PX_OK; ++p2) {
       const ExLayout l = ex_layout(cell, prec, n, n, B, B, false, p2);
       if (ctx->ws == nullptr || ctx->ws_bytes < l.end) continue;
       float ms = 0.f, best_ms = 1e30f;
@@ -1852,10 +1824,9 @@ px_status px_load_tuning(px_context* ctx, const char* cache_path, int32_t* appli
     if (sscanf(pp, "\"prec\": \"%4[a-z0-9]\"", prec) != 1) continue;
     if (sscanf(pb, "\"block\": %d", &blk) != 1 || blk <= 0 || blk > 4096) continue;
     const int pr = strcmp(prec, "fp32") == 0 ? int(PX_PREC_FP32) : int(PX_PREC_FP64);
-    int p2 = 0;  // pass-2 configuration (absent in older lines: the default)
+    int p2 = 0;  // z-tile configuration (absent in older lines: the default)
     const char* pq = strstr(line, "\"p2\": ");
-    const int grid[3] = {n0, n1, n2};
-    if (pq && (sscanf(pq, "\"p2\": %d", &p2) != 1 || p2 < 0 || p2 >= px::pass2_configs(grid))) p2 = 0;
+    if (pq && (sscanf(pq, "\"p2\": %d", &p2) != 1 || p2 < 0 || p2 >= px::kTileConfigs)) p2 = 0;
     ctx->tuning[std::make_tuple(n0, n1, n2, pr)] = {blk, blk, p2};
     ++count;
   }

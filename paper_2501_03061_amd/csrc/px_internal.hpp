@@ -23,21 +23,22 @@ struct ChunkArgs {
   void* out;            // [n_phi][N_g]
   const double* occ;    // [n_psi]
   const double* kern;   // [N_g] FP64, FFT order
-  const float* kern32;  // [N_g] the same rounded to FP32 (FP32 form; K(0) is read from kern)
-  G0Part* g0;           // [ic*jc][n2] FP64 slab sums (FP32 form)
-  double* expart;       // FP64 energy partials per (pair, y-plane): sum K|rho(G)|^2 (FP64
-                        // form), or {sum_{G!=0} K|rho|^2, sum_{G!=0} |rho|^2, G=0 term} (FP32 form)
-  int n2;
+  const void* kt;       // [n2][n0][n1] the table of the form: FP64, or rounded to FP32 (FP32
+                        // form; K(0) is read from kern)
+  G0Part* g0;           // [ic*jc][tiles] FP64 tile sums (FP32 form)
+  double* expart;       // FP64 energy partials per (pair, kz): sum K|rho(G)|^2 (FP64 form),
+                        // or {sum_{G!=0} K|rho|^2, sum_{G!=0} |rho|^2, G=0 term} (FP32 form)
   int i0, ic, j0, jc;
-  int first;            // pass 3 overwrites the output instead of accumulating
+  int first;            // the chunk's first pass to write the output block i0 overwrites it
+                        // instead of accumulating
   double* S;            // pair-energy matrix of the instance (task-table mode)
   int s_ld;             // its row stride
-  int store_v;          // pass 3 also writes N_g * v_ij back into the pair slab (symmetric mode)
+  int store_v;          // Hermitian-pair mode: pass 3 also sums the transposed pairs, pass 4 runs
   double inv_ng;
   int tri;              // diagonal block of the symmetric mode (i0 == j0, ic == jc) solved as
                         // its lower triangle jj <= ii: passes 1 and 3 run jj = 0..ii, pass 2
                         // takes the ic (ic + 1) / 2 pairs of the triangle (slots keep the
-                        // square layout p = ii jc + jj), pass 4 adds the pairs jj < ii
+                        // square layout p = ii jc + jj), the transposed sums take jj < ii
 };
 
 #if defined(__HIPCC__)
@@ -73,10 +74,9 @@ __device__ __forceinline__ ChunkArgs chunk_args(const ChunkArgs& a0, const Chunk
     a.out = c->out;
     a.occ = c->occ;
     a.kern = c->kern;
-    a.kern32 = c->kern32;
+    a.kt = c->kt;
     a.g0 = c->g0;
     a.expart = c->expart;
-    a.n2 = c->n2;
     a.i0 = c->i0;
     a.ic = c->ic;
     a.j0 = c->j0;
@@ -98,89 +98,80 @@ __device__ __forceinline__ ChunkArgs chunk_args(const ChunkArgs& a0, const Chunk
 
 // Grids with compiled pipelines: the cubic sizes and the non-cubic shapes.
 bool grid_supported(int n0, int n1, int n2);
-bool grid_cubic(int n0, int n1, int n2);
 
-// x-sections per y-plane tile of pass 2 (the z transforms, kernel multiply and
-// the exchange-energy partials): a pass-2 workgroup takes N0/XS of the plane's
-// N0 z-lines, and a pair has N1 * XS energy-partial slots.  Chosen per grid
-// size and form by measurement (per 1,024-pair launch, same box): at 96^3 two
-// sections of 48 lines (37 KB of LDS in FP32, four workgroups of 192 threads
-// per CU instead of two of 384) take FP32 pass 2 from 3.67 to 2.62 ms and FP64
-// from 5.47 to 5.11 ms; FP32 at 80^3 2.13 -> 1.74 ms, at 64^3 0.76 -> 0.68 ms;
-// at 48^3 and 72^3, and FP64 below 96^3, sections were slower or no faster.
-// The build may override the choice for one size (PX_P2_N with PX_P2_XS32 /
-// PX_P2_XS64).
-constexpr int pass2_sections(bool fp32, int n) {
-#if defined(PX_P2_N) && defined(PX_P2_XS32)
-  if (fp32 && n == PX_P2_N) return PX_P2_XS32;
-#endif
-#if defined(PX_P2_N) && defined(PX_P2_XS64)
-  if (!fp32 && n == PX_P2_N) return PX_P2_XS64;
-#endif
-  return n == 96 || (fp32 && (n == 64 || n == 80)) ? 2 : 1;
+// Points of the plane in a z tile (see exchange_kernels.hpp): rows of 256 bytes
+// (configuration 0) or 512 (1, which the autotuner times as well).
+constexpr int ztile_width(bool fp32, int cfg) { return (cfg == 0 ? 256 : 512) / (fp32 ? 8 : 16); }
+constexpr int kTileConfigs = 2;
+// z tiles of a pair on grid n[3]: the slots of a pair's G = 0 tile sums.
+inline int ztile_count(bool fp32, const int* n, int cfg) {
+  const int w = ztile_width(fp32, cfg);
+  return (n[0] * n[1] + w - 1) / w;
 }
-// Pass-2 configuration cfg: 0 the measured default, 1 the alternative that the
-// autotuner times as well (one section where the default has two, else two).
-constexpr int pass2_sections_cfg(bool fp32, int n, int cfg) {
-  return cfg == 0 ? pass2_sections(fp32, n) : (pass2_sections(fp32, n) == 1 ? 2 : 1);
+// Density orbitals j whose sums pass 3 keeps in registers (Hermitian-pair mode)
+// when a thread holds rs points of a tile: GJ rs complex sums, as many as leave
+// two waves per SIMD without spills (checked with -Rpass-analysis on every
+// grid; spills inside the loop cost more than the columns save).  More columns cost pass 3
+// registers and save pass 4 2/GJ of a slab (72^3 FP32, rs = 9, passes 3 and 4:
+// GJ = 2 2.1 us a pair, 3 1.36, 4 1.24, 5 1.23).
+constexpr int col_group(bool fp32, int rs) {
+  return fp32 ? (rs <= 5 ? 8 : rs <= 8 ? 6 : rs >= 10 ? 3 : 4) : (rs <= 5 ? 4 : rs >= 10 ? 2 : 3);
 }
-// Non-cubic grids: the fewest x-sections (a divisor of n0) that keep a pass-2
-// tile (n2 lines of n0/XS + 1 padded values) within 64 KB of LDS in the FP32
-// form (two 768-thread workgroups per CU) and within 40 KB in FP64.  Measured
-// at 60 x 90 x 120 per 1,024-pair launch: FP32 one section 2.88 ms against
-// 3.03 with two; FP64 three sections 4.28 ms against 4.82 with one and 6.00
-// with two.  PX_SH_XS32 / PX_SH_XS64 override for timing.
-constexpr int shape_sections(bool fp32, int n0, int n2) {
-#if defined(PX_SH_XS32)
-  if (fp32) return PX_SH_XS32;
-#endif
-#if defined(PX_SH_XS64)
-  if (!fp32) return PX_SH_XS64;
-#endif
-  for (int xs = 1; xs <= n0; ++xs)
-    if (n0 % xs == 0 && n2 * (n0 / xs + 1) * (fp32 ? 8 : 16) <= (fp32 ? 64 : 40) * 1024) return xs;
-  return n0;
+// Waves per SIMD that the register allocation of pass 3 aims at.
+constexpr int pass3_waves(bool fp32, bool sym, int nt) { return sym ? (fp32 && nt > 512 ? 3 : 2) : 1; }
+// Largest sizes of the chunks of one launch.
+struct ChunkDims {
+  int ntasks;     // chunks
+  int max_ic, max_jc;
+  int max_pairs;  // solved pairs (chunk_pairs)
+  int store_v;    // of every chunk
+};
+// Whether pass 3 has too few workgroups with groups of gj columns to fill the
+// chip (256 CUs): then one column per workgroup.
+inline bool small_group(int ntile, int max_jc, int gj, int ntasks) {
+  return size_t(ntile) * ((max_jc + gj - 1) / gj) * ntasks < 384;
 }
-// The same for any grid n[3]: non-cubic grids have one configuration.
-inline int pass2_sections_grid(bool fp32, const int* n, int cfg) {
-  return grid_cubic(n[0], n[1], n[2]) ? pass2_sections_cfg(fp32, n[0], cfg)
-                                      : shape_sections(fp32, n[0], n[2]);
+// Pairs that a pass-2 workgroup takes (the kernel values of its slab are
+// loaded once for them), with at least 4096 workgroups left.
+constexpr int kSlabPairs = 8;  // at most
+inline int pairs_per_slab_wg(int n2, int max_pairs, int ntasks) {
+  const size_t wgs = size_t(n2) * max_pairs * ntasks;
+  const size_t q = wgs / 4096;
+  return q < 1 ? 1 : q > kSlabPairs ? kSlabPairs : int(q);
 }
-// Pass-2 configurations the autotuner can choose from on grid n[3].
-inline int pass2_configs(const int* n) { return grid_cubic(n[0], n[1], n[2]) ? 2 : 1; }
-// Launches pass 1, 2, 3 of one chunk on grid n[3]; ev (nullable) = 4 events
-// recorded before pass 1, between the passes and after pass 3.
-hipError_t launch_chunk(bool fp32, const int* n, const ChunkArgs& a, int npairs, bool ex, int p2cfg,
-                        hipStream_t s, hipEvent_t* ev);
 
-// The same passes over a task table in device memory (ntasks chunks of one
-// grid, all with ic <= max_ic and at most max_pairs solved pairs
-// (chunk_pairs), and all with the given store_v), one launch each.
-hipError_t launch_chunk_tasks(bool fp32, const int* n, const ChunkArgs* tasks, int ntasks, int max_ic,
-                              int max_pairs, bool ex, bool store_v, int p2cfg, hipStream_t s);
-// Pass 4 over a task table (tasks without kept v_ij are skipped).
-hipError_t launch_pass4_tasks(bool fp32, const ChunkArgs* tasks, int ntasks, int max_jc, size_t ng,
-                              hipStream_t s);
+// Launches passes 1 to 3 (and 4 with store_v) of one chunk on grid n[3] in tile
+// configuration cfg; ev (nullable) = 5 events recorded before pass 1, between
+// the passes and after the last.
+hipError_t launch_chunk(bool fp32, const int* n, const ChunkArgs& a, bool ex, int cfg, hipStream_t s,
+                        hipEvent_t* ev);
+// The same passes over a task table in device memory (chunks of one grid
+// within the sizes of d), one launch each.
+hipError_t launch_chunk_tasks(bool fp32, const int* n, const ChunkArgs* tasks, const ChunkDims& d, bool ex,
+                              int cfg, hipStream_t s);
+// Pass 4 (Hermitian-pair mode): out[i] -= the sums over groups of gj pairs that
+// pass 3 left in the pair buffer, for one chunk or a task table.
+hipError_t launch_pass4(bool fp32, const ChunkArgs& a, const ChunkDims& d, int gj, size_t ng,
+                        const ChunkArgs* tasks, hipStream_t s);
 // Energy partials -> S for every task of a table (see launch_expart_reduce).
 // max_slots: the largest ic * jc of the table.
 hipError_t launch_expart_reduce_tasks(bool fp32, const ChunkArgs* tasks, int ntasks, int max_slots,
-                                      int n1, int n2, double ng, hipStream_t s);
-
-// Pass 4 (symmetric mode): out[j] -= sum_i f_i/N_g psi_i conj(v_ij) from the
-// pair slabs that pass 3 left in the pair buffer.
-hipError_t launch_pass4(bool fp32, const ChunkArgs& a, size_t ng, hipStream_t s);
+                                      int n2, int ntile, double ng, hipStream_t s);
 
 // misc_kernels.hip
 hipError_t launch_kernel_hse(int n0, int n1, int n2, double L0, double L1, double L2, double mu,
                              double* kern, hipStream_t s);
 hipError_t launch_convert_c128_c64(size_t n, const void* src, void* dst, hipStream_t s);
+// The kernel table [n2][n1][n0] transposed to [n2][n0][n1], FP64 or rounded to FP32
+hipError_t launch_kernel_transpose(bool fp32, int n0, int n1, int n2, const double* kern, void* kt,
+                                   hipStream_t s);
 // n real FP64 values -> FP32 (round to nearest even)
 hipError_t launch_convert_f64_f32(size_t n, const double* src, float* dst, hipStream_t s);
 hipError_t launch_stream_copy(size_t bytes, const void* src, void* dst, hipStream_t s);
 // S[i][j] (row stride lds) from the chunk's energy partials (see ChunkArgs);
 // FP32 form (g0 non-null): the G != 0 part is rescaled so that its energy
 // matches Parseval's identity with the FP64 energy of the transform input.
-hipError_t launch_expart_reduce(const double* expart, const G0Part* g0, int n1, int n2, double ng,
+hipError_t launch_expart_reduce(const double* expart, const G0Part* g0, int n2, int ntile, double ng,
                                 int i0, int ic, int j0, int jc, double* S, int lds, bool mirror,
                                 bool tri, hipStream_t s);
 // e_x = scale * sum_i sum_j f_i f_j S[i][j]

@@ -29,7 +29,7 @@ import os
 COPY_BYTES = 2 << 30
 ROOT = os.path.dirname(os.path.abspath(__file__))
 KERNEL_SOURCES = ("exchange_kernels.hpp", "fft_core.hpp", "px_internal.hpp", "exchange_inst.hip",
-                  "pair_transpose.hip")
+                  "pair_rows.hip")
 WORKLOAD_TEXT = {"large96": "large96 workload (96^3 grid, 1536 orbitals)",
                  "mid72": "mid72 workload (72^3 grid, 512 orbitals)",
                  "mixed96": "mixed96 workload (96^3 grid, 1536 orbitals, full occupation matrix)",
@@ -83,11 +83,9 @@ def _per_kernel(d):
 
 
 def _short(name):
-    # "void px::pass3_inv_xy_acc<float, 72, ...>(...)" -> "pass3_inv_xy_acc"; the staged
-    # form of pass 3 (FP32 at 72^3-96^3) counts as pass 3
+    # "void px::pass3_z<float, 72, ...>(...)" -> "pass3_z"
     base = name.split("(")[0].split("<")[0]
-    short = base.split("::")[-1].replace("void ", "").strip()
-    return "pass3_inv_xy_acc" if short == "pass3_staged" else short
+    return base.split("::")[-1].replace("void ", "").strip()
 
 
 def summarize(trace, fetch, write, copy_fetch, copy_write, bench_json, out, commands, workload):
@@ -111,7 +109,7 @@ def summarize_trace(trace, bench_json, out, commands, workload):
         lines.append(f"| {k} | {v['avg_us']:.1f} | {v['launches_per_step']} | {v['ms_per_step']:.1f} | "
                      f"{v['model_GBps']:.0f} |")
     # the same passes in the trace: FP32 instantiations of each pass merged by
-    # dispatch count (pass 3 runs with and without the kept v_ij)
+    # dispatch count (pass 3 runs with and without the transposed sums)
     merged = collections.defaultdict(lambda: [0, 0.0])
     for r in stats:
         if "<float" in r["Name"] and _short(r["Name"]) in rec["extra"]["passes"]:
@@ -311,7 +309,7 @@ def summarize_sq(dirs, out, commands, workload):
              "SQ_BUSY_CU_CYCLES; L2 latency = TCP_TCC_READ_REQ_LATENCY / TCP_TCC_READ_REQ (cycles).", "",
              "| kernel | dispatches | VALU instr. per wave | VALU issue share | wait share | LDS conflict "
              "share | TA busy | L2 read latency (cycles) |", "|---|---|---|---|---|---|---|---|"]
-    order = ["pass1_fwd_xy", "pass2_z_kernel", "pass3_inv_xy_acc", "pass4_transpose_acc", "gemm_xhy_k",
+    order = ["pass1_z", "pass2_xy", "pass3_z", "pass4_rows", "gemm_xhy_k",
              "gemm_xc_k"]
 
     def avg(cs, c):
