@@ -144,15 +144,6 @@ constexpr int round64(int n) { return (n + 63) / 64 * 64; }
 // Workgroup size for the register allocation: whole waves on every SIMD.
 constexpr int round256(int n) { return (n + 255) / 256 * 256; }
 
-// A workgroup barrier after all of this wave's memory operations, global ->
-// LDS transfers included (vmcnt(0) lgkmcnt(0)).
-__device__ __forceinline__ void dma_sync() {
-  __atomic_signal_fence(__ATOMIC_SEQ_CST);
-  __builtin_amdgcn_s_waitcnt(0x0070);
-  __builtin_amdgcn_s_barrier();
-  __atomic_signal_fence(__ATOMIC_SEQ_CST);
-}
-
 // ============================================================== z tiles
 // Geometry of the z-tile passes on an N0 x N1 x N2 grid: W points of the plane
 // (the last tile is short when W does not divide N0 N1: its lanes past the

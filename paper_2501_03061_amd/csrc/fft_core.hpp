@@ -317,6 +317,15 @@ __device__ __forceinline__ void lds_sync() {
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
 }
 
+// A workgroup barrier after all of this wave's memory operations, global ->
+// LDS transfers included (vmcnt(0) lgkmcnt(0)).
+__device__ __forceinline__ void dma_sync() {
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+  __builtin_amdgcn_s_waitcnt(0x0070);
+  __builtin_amdgcn_s_barrier();
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+}
+
 // Slots of a stage of geometry G (lines fastest) shared by NA threads, a
 // multiple of the line count: thread t keeps its line, and slot k is butterfly
 // j = t / nl + k NA/nl of it.  When the butterflies do not fill the last slot,

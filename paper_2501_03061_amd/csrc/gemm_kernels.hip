@@ -66,23 +66,58 @@ template <typename T> __device__ __forceinline__ int drow(int q, int t) {
 }
 
 constexpr int XHY_SUB = 1024;  // FP32 form: r-span of one FP32 accumulation
-constexpr int XHY_KU = 4;      // k-steps of 4 per unrolled iteration (16 r)
-constexpr int XC_KU = 4;       // k-steps of 4 per group in xc (16 a)
+
+// 16 bytes per lane from global memory into LDS (lane l of the wave to the
+// l-th 16 bytes of the wave-uniform destination).
+__device__ __forceinline__ void dma16(const void* g, void* l) {
+  __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1)))*)g,
+                                   (void __attribute__((address_space(3)))*)l, 16, 0, 0);
+}
+
+// f(integral_constant NI, integral_constant NJ) with a wave's valid 16-wide
+// tiles in each direction (0 to 2): sub-tiles past the matrix are not computed.
+template <class F> __device__ __forceinline__ void by_tiles(int ni, int nj, F&& f) {
+  using std::integral_constant;
+  if (ni >= 2 && nj >= 2) f(integral_constant<int, 2>{}, integral_constant<int, 2>{});
+  else if (ni >= 2 && nj == 1) f(integral_constant<int, 2>{}, integral_constant<int, 1>{});
+  else if (ni == 1 && nj >= 2) f(integral_constant<int, 1>{}, integral_constant<int, 2>{});
+  else if (ni == 1 && nj == 1) f(integral_constant<int, 1>{}, integral_constant<int, 1>{});
+  else f(integral_constant<int, 0>{}, integral_constant<int, 0>{});
+}
 
 // ---------------------------------------------------------------- xhy
 // grid (ceil(na/64), ceil(nb/64), nsplit), 256 threads; wave w covers the
-// 32x32 sub-block (w&1, w>>1) as 2x2 MFMA tiles.  Occupancy target of two
-// waves per SIMD: the three accumulator sets fit in 256 registers without
-// spills, where the default allocation (FP64) left one wave per SIMD.
-// tri > 0 (a Hermitian result, na = nb): only the tiles (ta, tb) with ta <= tb
-// of the tri x tri tile grid are computed, blockIdx.x enumerating them row by
-// row; the reduction mirrors the others.
+// 32x32 sub-block (w&1, w>>1) as 2x2 MFMA tiles.  tri > 0 (a Hermitian result,
+// na = nb): only the tiles (ta, tb) with ta <= tb of the tri x tri tile grid are
+// computed, blockIdx.x enumerating them row by row; the reduction mirrors the
+// others.
+//
+// Stages of 256 bytes of each row (32 complex64, 16 complex128) of the 64 + 64
+// rows go through LDS by global -> LDS transfers, the next stage moving while
+// one is multiplied.  The two stages are arrays of their own: LDS reads that
+// may alias a transfer in flight would wait for it.  16-byte piece c of row i
+// sits at slot c ^ (i & 7), so that eight rows' same pieces lie in eight
+// different 16-byte columns (no bank conflicts), which the transfer's free
+// choice of source addresses gives at no cost.  Rows past the matrix repeat
+// its last row, pieces past the chunk its last piece (masked in the last stage,
+// which has a copy of the loop body of its own: a masked path inside the loop
+// cost 80 registers).
+//
+// Bound by the matrix cores: 6 na nb N_g real operations at 157 TFLOP/s (FP32)
+// or 79 (FP64).  512 x 512 x 72^3 FP32 (with xc, the ACE application) 12.25 ->
+// 9.75 ms, 120 TFLOP/s, against operands loaded by every wave from global memory into
+// registers with masks; 200 x 200 x 48^3 FP64 1.82 -> 1.34 ms, of which the
+// 16-wide tiles past 200 that are no longer computed are a third.
+struct XhyStage { static constexpr int ROW = 256, BYTES = 128 * ROW; };  // X rows, then Y rows
 template <typename T>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void gemm_xhy_k(int na, int nb, size_t ng, const cpx<T>* X,
                                                   const cpx<T>* Y, double* part, size_t kchunk,
                                                   int tri) {
   using A = typename Acc<T>::t;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  constexpr int SZ = int(sizeof(cpx<T>)), KT = XhyStage::ROW / SZ;  // r of a stage
+  __shared__ __attribute__((aligned(16))) char st0[XhyStage::BYTES], st1[XhyStage::BYTES];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   int ta = blockIdx.x, tb = blockIdx.y;
   if (tri > 0) {  // wave-uniform decode of the upper-triangle tile index
     int k = blockIdx.x;
@@ -99,17 +134,28 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void g
   const size_t r_end = (r_begin + kchunk < ng) ? r_begin + kchunk : ng;
   const int q = lane >> 4, m = lane & 15;
 
-  const cpx<T>* xrow[2];
-  const cpx<T>* yrow[2];
-  bool xv[2], yv[2];
+  // transfers: waves 0 and 1 move X's rows, 2 and 3 Y's, four rows each time
+  // (a wave-uniform row and a 32-bit lane offset of up to three rows more)
+  const bool isx = w < 2;
+  const int row0 = (isx ? ta : tb) * 64 + (w & 1) * 32, rlim = (isx ? na : nb) - 1;
+  const char* const src = reinterpret_cast<const char*>(isx ? X : Y) + r_begin * SZ;
+  unsigned off[8];
 #pragma unroll
-  for (int t = 0; t < 2; ++t) {
-    const int a = a_base + 16 * t + m, b = b_base + 16 * t + m;
-    xv[t] = a < na;
-    yv[t] = b < nb;
-    xrow[t] = X + size_t(xv[t] ? a : 0) * ng;
-    yrow[t] = Y + size_t(yv[t] ? b : 0) * ng;
+  for (int i = 0; i < 8; ++i) {
+    const int r = row0 + 4 * i < rlim ? row0 + 4 * i : rlim;
+    off[i] = unsigned(r + q < rlim ? q : rlim - r) * unsigned(ng * SZ);
   }
+  const unsigned last = unsigned((r_end - r_begin) * SZ) - 16;  // the chunk's last piece
+  auto stage_in = [&](int k, char* st) {
+    char* const dst = st + w * 32 * XhyStage::ROW;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int r = row0 + 4 * i < rlim ? row0 + 4 * i : rlim;
+      const unsigned c = unsigned(k) * XhyStage::ROW + unsigned((m ^ ((4 * i + q) & 7)) * 16);
+      dma16(src + size_t(r) * ng * SZ + (off[i] + (c < last ? c : last)), dst + i * 4 * XhyStage::ROW);
+    }
+  };
+
   // Gauss's three products: with x = a + ib (a = xr, b = -xi) and y = c + id,
   // k1 = (a + b) c, k2 = a (d - c), k3 = b (c + d); re = k1 - k3, im = k1 + k2
   A k1[2][2], k2[2][2], k3[2][2];
@@ -122,74 +168,71 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void g
 #pragma unroll
       for (int t = 0; t < 4; ++t) dre[i][j][t] = dim[i][j][t] = 0.0;
     }
+  const int nst = int((r_end - r_begin + KT - 1) / KT);
+  const int rem = int((r_end - r_begin) - size_t(nst - 1) * KT);  // r of the last stage
 
-  // Groups of 4*XHY_KU consecutive r.  Two register sets alternate: the next
-  // group loads into the idle set while the current one feeds the MFMAs.
-  // Loads past the chunk end read a valid address and are masked to zero, so
-  // every iteration issues the same loads (the group count is padded to even).
-  constexpr size_t GR = 4 * XHY_KU;
-  constexpr size_t GPS = XHY_SUB / GR;  // groups per FP32 accumulation span
-  const size_t ngroups = r_end > r_begin ? (r_end - r_begin + GR - 1) / GR : 0;
-  // (FP32: each lane's four consecutive complex values of a row come in two
-  // 16-byte loads, which halves the address work of the gather; the grids
-  // have N_g and the chunk bounds even, so a pair never straddles the end)
-  auto load = [&](size_t g, cpx<T>(&xa)[2][XHY_KU], cpx<T>(&yb)[2][XHY_KU]) {
-    const size_t rl = r_begin + g * GR + 4 * q;
+  const int ni = a_base >= na ? 0 : a_base + 16 >= na ? 1 : 2;
+  const int nj = b_base >= nb ? 0 : b_base + 16 >= nb ? 1 : 2;
+  by_tiles(ni, nj, [&](auto nic, auto njc) {
+    constexpr int NI = decltype(nic)::value, NJ = decltype(njc)::value;
+    // a stage: four k-steps of 4 r per 16 r; lane q holds r = 4 q + s of them
+    constexpr int PS = 16 / SZ;  // values of r in a piece
+    auto multiply = [&](const char* st, auto tail) {
+      if constexpr (NI > 0) {
+        const char* const xr = st + ((w & 1) * 32 + m) * XhyStage::ROW;
+        const char* const yr = st + (64 + (w >> 1) * 32 + m) * XhyStage::ROW;
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
+        for (int h = 0; h < KT / (4 * PS); ++h) {
+          // piece of this lane: PS values of r, the same k-steps for all rows
+          const int r0 = SZ == 8 ? 16 * (h / 2) + 4 * q + 2 * (h % 2) : 4 * q + h;
+          const int slot = ((r0 / PS) ^ (m & 7)) * 16;
+          cpx<T> xa[NI][PS], yb[NJ][PS];
+          auto get = [&](const char* row, cpx<T>(&v)[PS]) {
+            if constexpr (SZ == 8) {
+              const vf4g x = *reinterpret_cast<const vf4g*>(row + slot);
+              v[0] = {x.x, x.y};
+              v[1] = {x.z, x.w};
+            } else {
+              v[0] = load_c(reinterpret_cast<const cpx<T>*>(row + slot));
+            }
+            if constexpr (decltype(tail)::value) {
+#pragma unroll
+              for (int s = 0; s < PS; ++s)
+                if (r0 + s >= rem) v[s] = {T(0), T(0)};
+            }
+          };
+#pragma unroll
+          for (int i = 0; i < NI; ++i) get(xr + i * 16 * XhyStage::ROW, xa[i]);
+#pragma unroll
+          for (int j = 0; j < NJ; ++j) get(yr + j * 16 * XhyStage::ROW, yb[j]);
+#pragma unroll
+          for (int s = 0; s < PS; ++s) {
+            T xs[NI], yd[NJ], ys[NJ];
+#pragma unroll
+            for (int i = 0; i < NI; ++i) xs[i] = xa[i][s].x - xa[i][s].y;
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+              yd[j] = yb[j][s].y - yb[j][s].x;
+              ys[j] = yb[j][s].x + yb[j][s].y;
+            }
+#pragma unroll
+            for (int i = 0; i < NI; ++i)
+#pragma unroll
+              for (int j = 0; j < NJ; ++j) {
+                k1[i][j] = mfma(xs[i], yb[j][s].x, k1[i][j]);
+                k2[i][j] = mfma(xa[i][s].x, yd[j], k2[i][j]);
+                k3[i][j] = mfma(-xa[i][s].y, ys[j], k3[i][j]);
+              }
+          }
+        }
+      }
+    };
+    auto flush = [&] {  // FP32 accumulators to FP64
       if constexpr (sizeof(T) == 4) {
 #pragma unroll
-        for (int s = 0; s < XHY_KU; s += 2) {
-          const size_t r = rl + s;
-          const bool in = r < r_end;
-          const size_t rc = in ? r : r_begin;
-          const vf4g x = gload4(xrow[t] + rc), y = gload4(yrow[t] + rc);
-          const bool ux = in && xv[t], uy = in && yv[t];
-          xa[t][s] = ux ? cpx<T>{x.x, x.y} : cpx<T>{T(0), T(0)};
-          xa[t][s + 1] = ux ? cpx<T>{x.z, x.w} : cpx<T>{T(0), T(0)};
-          yb[t][s] = uy ? cpx<T>{y.x, y.y} : cpx<T>{T(0), T(0)};
-          yb[t][s + 1] = uy ? cpx<T>{y.z, y.w} : cpx<T>{T(0), T(0)};
-        }
-      } else {
+        for (int i = 0; i < NI; ++i)
 #pragma unroll
-        for (int s = 0; s < XHY_KU; ++s) {
-          const size_t r = rl + s;
-          const bool in = r < r_end;
-          const size_t rc = in ? r : r_begin;
-          const cpx<T> x = load_c(xrow[t] + rc), y = load_c(yrow[t] + rc);
-          xa[t][s] = (in && xv[t]) ? x : cpx<T>{T(0), T(0)};
-          yb[t][s] = (in && yv[t]) ? y : cpx<T>{T(0), T(0)};
-        }
-      }
-    }
-  };
-  auto compute = [&](size_t g, cpx<T>(&xa)[2][XHY_KU], cpx<T>(&yb)[2][XHY_KU]) {
-#pragma unroll
-    for (int s = 0; s < XHY_KU; ++s) {
-      T xs[2], yd[2], ys[2];
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        xs[t] = xa[t][s].x - xa[t][s].y;
-        yd[t] = yb[t][s].y - yb[t][s].x;
-        ys[t] = yb[t][s].x + yb[t][s].y;
-      }
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          k1[i][j] = mfma(xs[i], yb[j][s].x, k1[i][j]);
-          k2[i][j] = mfma(xa[i][s].x, yd[j], k2[i][j]);
-          k3[i][j] = mfma(-xa[i][s].y, ys[j], k3[i][j]);
-        }
-    }
-    if constexpr (sizeof(T) == 4) {
-      // FP32 accumulators span at most XHY_SUB values of r, then go to FP64
-      // (a padding group adds zeros, so a repeated flush is harmless)
-      if ((g + 1) % GPS == 0 || g + 1 >= ngroups) {
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-          for (int j = 0; j < 2; ++j) {
+          for (int j = 0; j < NJ; ++j) {
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
               dre[i][j][t] += double(k1[i][j][t]) - double(k3[i][j][t]);
@@ -198,18 +241,25 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void g
             k1[i][j] = k2[i][j] = k3[i][j] = A{0, 0, 0, 0};
           }
       }
+    };
+    auto step = [&](int k, const char* cur, char* nxt) {
+      stage_in(k + 1, nxt);
+      multiply(cur, std::false_type{});
+      dma_sync();
+    };
+    stage_in(0, st0);
+    dma_sync();
+    int k = 0;
+    for (; k + 2 < nst; k += 2) {
+      step(k, st0, st1);
+      step(k + 1, st1, st0);
+      // FP32 accumulators span at most XHY_SUB values of r
+      if ((k + 2) % (XHY_SUB / KT) == 0) flush();
     }
-  };
-  if (ngroups > 0) {
-    cpx<T> xa0[2][XHY_KU], yb0[2][XHY_KU], xa1[2][XHY_KU], yb1[2][XHY_KU];
-    load(0, xa0, yb0);
-    for (size_t g = 0; g < ngroups; g += 2) {
-      load(g + 1, xa1, yb1);
-      compute(g, xa0, yb0);
-      load(g + 2, xa0, yb0);
-      compute(g + 1, xa1, yb1);
-    }
-  }
+    if (k + 1 < nst) step(k++, st0, st1);
+    multiply(k % 2 ? st1 : st0, std::true_type{});  // the last stage, masked
+    flush();
+  });
   double* out = part + size_t(blockIdx.z) * na * nb * 2;
 #pragma unroll
   for (int i = 0; i < 2; ++i)
@@ -350,12 +400,31 @@ hipError_t launch_gemm_xhy_herm(bool fp32, int n, size_t ng, const void* X, cons
 // j: b).  Occupancy
 // targets (no spills): three waves per SIMD in the FP32 form, two in FP64
 // (one by default; ACE application in FP64 -15 %).
+//
+// Stages of KT rows a: 64 values of r of X by global -> LDS transfers (the
+// next stage moving while one is multiplied), 64 columns b of C through
+// registers (its rows need not be 16-byte aligned).  FP32: 16-byte piece c of
+// row a sits at slot c ^ 8 (a & 3), so that the four rows that one read covers
+// lie in different banks.  A is C^T and B is X: a lane's results then have one r and
+// the stores of 16 lanes are contiguous.
+template <typename T> struct XcStage {
+  static constexpr int SZ = int(sizeof(cpx<T>)), KT = 128 / SZ, ROW = 64 * SZ, BYTES = KT * ROW;
+  static constexpr int NC = KT * 64 / 256;  // entries of C per thread
+  static __device__ __forceinline__ int at(int a, int c) {  // byte offset of entry (a, c)
+    const int b = c * SZ;
+    return a * ROW + (SZ == 8 ? b ^ ((a & 3) << 7) : b);
+  }
+};
 template <typename T>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 3 : 2))) void gemm_xc_k(int na, int nb, size_t ng, const cpx<T>* X,
                                                  const T* C, int ldc, double alpha,
                                                  cpx<T>* Z, int upper) {
   using A = typename Acc<T>::t;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  using S = XcStage<T>;
+  constexpr int KT = S::KT, SZ = S::SZ;
+  __shared__ __attribute__((aligned(16))) char xs0[S::BYTES], xs1[S::BYTES], cs0[S::BYTES], cs1[S::BYTES];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const unsigned nbt = unsigned(nb + 63) / 64, nrt = unsigned((ng + 63) / 64);
   const int bt = int(upper ? blockIdx.x / nrt : blockIdx.x % nbt);
   const size_t rt = upper ? blockIdx.x % nrt : blockIdx.x / nbt;
@@ -367,90 +436,121 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
     const int lim = bt * 64 + 64;
     a_end = lim < na ? lim : na;
   }
-  bool rv[2], bv[2];
-  size_t rr[2];
-  int bb[2];
-#pragma unroll
-  for (int t = 0; t < 2; ++t) {
-    rr[t] = r_base + 16 * t + m;
-    rv[t] = rr[t] < ng;
-    bb[t] = b_base + 16 * t + m;
-    bv[t] = bb[t] < nb;
-  }
   // Gauss's three products (x = a + ib, C entry c + id): k1 = (a + b) c,
-  // k2 = a (d - c), k3 = b (c + d); re = k1 - k3, im = k1 + k2
+  // k2 = a (d - c), k3 = b (c + d); re = k1 - k3, im = k1 + k2.  [j][i]: b, r
   A k1[2][2], k2[2][2], k3[2][2];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int j = 0; j < 2; ++j)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) k1[i][j] = k2[i][j] = k3[i][j] = A{0, 0, 0, 0};
-  // Groups of 4*XC_KU consecutive a (4 per MFMA k-step); two register sets
-  // alternate as in xhy, with masked loads from clamped addresses.
-  const size_t rc[2] = {rv[0] ? rr[0] : 0, rv[1] ? rr[1] : 0};
-  const int bc[2] = {bv[0] ? bb[0] : 0, bv[1] ? bb[1] : 0};
-  constexpr int GA = 4 * XC_KU;
-  const int ngroups = (a_end + GA - 1) / GA;
-  auto load = [&](int g, cpx<T>(&xa)[2][XC_KU], cpx<T>(&cb)[2][XC_KU]) {
+    for (int i = 0; i < 2; ++i) k1[j][i] = k2[j][i] = k3[j][i] = A{0, 0, 0, 0};
+  const int nst = (a_end + KT - 1) / KT;
+
+  // X: each transfer of a wave moves 1 KiB (two rows of complex64, one of
+  // complex128); rows past a_end repeat the last, values past N_g the last piece
+  constexpr int LPR = S::ROW / 16, RPT = 64 / LPR, NX = S::BYTES / 4096;
+  // (a wave-uniform row and a 32-bit lane offset of at most one row more)
+  const int xrow = lane / LPR;
+  const unsigned rmax = unsigned(ng - rt * 64 < 64 ? ng - rt * 64 : 64) - 16 / SZ;
+  const cpx<T>* const xt = X + rt * 64;
+  auto x_in = [&](int k, char* st) {
 #pragma unroll
-    for (int s = 0; s < XC_KU; ++s) {
-      const int a = g * GA + 4 * s + q;
-      const bool av = a < a_end;
-      const int ac = av ? a : 0;
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const cpx<T> x = load_c(X + size_t(ac) * ng + rc[t]);
-        const T* c = C + (size_t(ac) * ldc + bc[t]) * 2;
-        const T c0 = c[0], c1 = c[1];
-        xa[t][s] = (av && rv[t]) ? x : cpx<T>{T(0), T(0)};
-        cb[t][s] = (av && bv[t]) ? cpx<T>{c0, c1} : cpx<T>{T(0), T(0)};
-      }
+    for (int i = 0; i < NX; ++i) {
+      const int al = (w * NX + i) * RPT;  // first row within the stage
+      const int a = k * KT + al < a_end ? k * KT + al : a_end - 1;
+      const int ar = a + xrow < a_end ? xrow : 0;
+      // the entry that belongs at this lane's slot (its piece's first)
+      const unsigned c = unsigned(SZ == 8 ? (((lane % LPR) * 16) ^ (((al + xrow) & 3) << 7)) / SZ : lane % LPR);
+      dma16(reinterpret_cast<const char*>(xt + size_t(a) * ng) + (unsigned(ar) * unsigned(ng) + (c < rmax ? c : rmax)) * unsigned(SZ),
+            st + (w * NX + i) * 1024);
     }
   };
-  auto compute = [&](cpx<T>(&xa)[2][XC_KU], cpx<T>(&cb)[2][XC_KU]) {
+  // C: entry e = tid + 256 i of the stage (zero past the matrix)
+  cpx<T> cr[S::NC];
+  const int cb = bt * 64 + lane;
+  auto c_get = [&](int k) {
 #pragma unroll
-    for (int s = 0; s < XC_KU; ++s) {
-      T xs[2], cd[2], cs[2];
+    for (int i = 0; i < S::NC; ++i) {
+      const int a = k * KT + w + 4 * i;  // wave-uniform
+      const cpx<T> c = load_c(reinterpret_cast<const cpx<T>*>(C) + size_t(a < a_end ? a : 0) * ldc + unsigned(cb < nb ? cb : 0));
+      cr[i] = a < a_end && cb < nb ? c : cpx<T>{T(0), T(0)};
+    }
+  };
+  auto c_put = [&](char* st) {
 #pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        xs[t] = xa[t][s].x + xa[t][s].y;
-        cd[t] = cb[t][s].y - cb[t][s].x;
-        cs[t] = cb[t][s].x + cb[t][s].y;
-      }
+    for (int i = 0; i < S::NC; ++i)
+      *reinterpret_cast<cpx<T>*>(st + S::at(w + 4 * i, lane)) = cr[i];
+  };
+
+  const int nj = b_base >= nb ? 0 : b_base + 16 >= nb ? 1 : 2;
+  const int ni = r_base >= ng ? 0 : r_base + 16 >= ng ? 1 : 2;
+  by_tiles(ni, nj, [&](auto nic, auto njc) {
+    constexpr int NI = decltype(nic)::value, NJ = decltype(njc)::value;
+    auto multiply = [&](const char* xs, const char* cs, int left, auto tail) {
+      if constexpr (NI > 0) {
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+        for (int s = 0; s < KT / 4; ++s) {
+          const int a = 4 * s + q;
+          cpx<T> x[NI], c[NJ];
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          k1[i][j] = mfma(xs[i], cb[j][s].x, k1[i][j]);
-          k2[i][j] = mfma(xa[i][s].x, cd[j], k2[i][j]);
-          k3[i][j] = mfma(xa[i][s].y, cs[j], k3[i][j]);
+          for (int i = 0; i < NI; ++i) {
+            x[i] = load_c(reinterpret_cast<const cpx<T>*>(xs + S::at(a, (w & 1) * 32 + 16 * i + m)));
+            if (decltype(tail)::value && a >= left) x[i] = {T(0), T(0)};
+          }
+#pragma unroll
+          for (int j = 0; j < NJ; ++j)
+            c[j] = load_c(reinterpret_cast<const cpx<T>*>(cs + S::at(a, (w >> 1) * 32 + 16 * j + m)));
+          T xq[NI], cd[NJ], cq[NJ];
+#pragma unroll
+          for (int i = 0; i < NI; ++i) xq[i] = x[i].x + x[i].y;
+#pragma unroll
+          for (int j = 0; j < NJ; ++j) {
+            cd[j] = c[j].y - c[j].x;
+            cq[j] = c[j].x + c[j].y;
+          }
+#pragma unroll
+          for (int j = 0; j < NJ; ++j)
+#pragma unroll
+            for (int i = 0; i < NI; ++i) {
+              k1[j][i] = mfma(c[j].x, xq[i], k1[j][i]);
+              k2[j][i] = mfma(cd[j], x[i].x, k2[j][i]);
+              k3[j][i] = mfma(cq[j], x[i].y, k3[j][i]);
+            }
+          if (s % 2 == 1) __builtin_amdgcn_sched_barrier(0);  // two steps' operands at a time
         }
+      }
+    };
+    auto step = [&](int k, const char* xs, const char* cs, char* xn, char* cn) {
+      c_put(cn);  // stage k + 1
+      x_in(k + 1, xn);
+      c_get(k + 2);
+      multiply(xs, cs, KT, std::false_type{});
+      dma_sync();
+    };
+    x_in(0, xs0);
+    c_get(0);
+    c_put(cs0);
+    c_get(1);
+    dma_sync();
+    int k = 0;
+    for (; k + 2 < nst; k += 2) {
+      step(k, xs0, cs0, xs1, cs1);
+      step(k + 1, xs1, cs1, xs0, cs0);
     }
-  };
-  if (ngroups > 0) {
-    cpx<T> xa0[2][XC_KU], cb0[2][XC_KU], xa1[2][XC_KU], cb1[2][XC_KU];
-    load(0, xa0, cb0);
-    for (int g = 0; g < ngroups; g += 2) {
-      load(g + 1, xa1, cb1);
-      compute(xa0, cb0);
-      load(g + 2, xa0, cb0);
-      compute(xa1, cb1);
-    }
-  }
+    if (k + 1 < nst) step(k++, xs0, cs0, xs1, cs1);
+    multiply(k % 2 ? xs1 : xs0, k % 2 ? cs1 : cs0, a_end - k * KT, std::true_type{});  // the last stage, masked
+  });
   const T al = T(alpha);
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int j = 0; j < 2; ++j)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int b = b_base + 16 * j + m;
+    for (int t = 0; t < 4; ++t) {
+      const int b = b_base + 16 * j + drow<T>(q, t);
       if (b >= nb) continue;
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const size_t r = r_base + 16 * i + drow<T>(q, t);
-        if (r < ng) {
-          cpx<T>* o = Z + size_t(b) * ng + r;
-          o->x = al * (k1[i][j][t] - k3[i][j][t]);
-          o->y = al * (k1[i][j][t] + k2[i][j][t]);
-        }
+      for (int i = 0; i < 2; ++i) {
+        const size_t r = r_base + 16 * i + m;
+        if (r < ng)
+          Z[size_t(b) * ng + r] = {al * (k1[j][i][t] - k3[j][i][t]), al * (k1[j][i][t] + k2[j][i][t])};
       }
     }
 }
