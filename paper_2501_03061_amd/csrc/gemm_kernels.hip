@@ -283,21 +283,44 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void g
       }
 }
 
-__global__ void xhy_reduce_k(int na, int nb, const double* part, int nsplit, double scale,
+// Sum of the splits' partials of each entry: R threads of a workgroup take every
+// R-th split of 256 / R neighbouring entries, and the first of them adds the R
+// sums in order.  R > 1 where the splits are many (small matrices): with one
+// thread per entry, 108 splits of a 16 x 16 matrix were one workgroup's serial
+// loop.
+template <int R>
+__global__ __launch_bounds__(256) void xhy_reduce_k(int na, int nb, const double* part, int nsplit, double scale,
                              double* M, int ldm, float* M32, int herm) {
+  constexpr int E = 256 / R;
+  __shared__ double2 sum[R > 1 ? R : 1][R > 1 ? E : 1];
   const size_t n = size_t(na) * nb;
-  for (size_t e = size_t(blockIdx.x) * blockDim.x + threadIdx.x; e < n;
-       e += size_t(gridDim.x) * blockDim.x) {
-    const size_t a = e / nb, b = e % nb;
+  const int le = threadIdx.x % E, row = threadIdx.x / E;
+  for (size_t e0 = size_t(blockIdx.x) * E; e0 < n; e0 += size_t(gridDim.x) * E) {
+    const size_t e = e0 + le;
+    const bool in = e < n;
+    const size_t a = in ? e / nb : 0, b = in ? e % nb : 0;
     // a Hermitian result keeps only the tiles on and above the diagonal:
     // entries below it are the conjugates of their mirror images
     const bool mirror = herm && (a / 64) > (b / 64);
-    const size_t src = mirror ? b * nb + a : e;
+    const size_t src = mirror ? b * nb + a : a * nb + b;
     double re = 0.0, im = 0.0;
-    for (int s = 0; s < nsplit; ++s) {
-      re += part[(size_t(s) * n + src) * 2];
-      im += part[(size_t(s) * n + src) * 2 + 1];
+    for (int s = row; s < nsplit; s += R) {
+      const double2 v = *reinterpret_cast<const double2*>(part + (size_t(s) * n + src) * 2);
+      re += v.x;
+      im += v.y;
     }
+    if constexpr (R > 1) {
+      __syncthreads();  // the previous entries have been added
+      sum[row][le] = make_double2(re, im);
+      __syncthreads();
+      if (row > 0) continue;
+#pragma unroll
+      for (int k = 1; k < R; ++k) {
+        re += sum[k][le].x;
+        im += sum[k][le].y;
+      }
+    }
+    if (!in) continue;
     if (mirror) im = -im;
     M[(a * ldm + b) * 2] = scale * re;
     M[(a * ldm + b) * 2 + 1] = scale * im;
@@ -308,19 +331,24 @@ __global__ void xhy_reduce_k(int na, int nb, const double* part, int nsplit, dou
   }
 }
 
-// r-span of one split: aim at ~2048 workgroups, at least 1024 values of r,
-// and at most max_split splits (the partials need max_split * na * nb
-// complex128 values of scratch).  Among 1 to 2 times the aimed split count the
-// one whose workgroups best fill whole rounds of the resident ones (two per CU
-// on 256 CUs) is taken: the workgroups of a launch all run about equally long,
-// so a last round half full idles half the chip for one workgroup's time
-// (ACE application at 96^3 x 1536: 4 -> 8 splits, about -2 %).  herm counts
-// the tiles on and above the diagonal that the Hermitian form launches.
+// r-span of one split: aim at one round of resident workgroups (two per CU on
+// 256 CUs), at least 128 values of r, and at most max_split splits (the partials
+// need max_split * na * nb complex128 values of scratch).  Among 1 to 2 times
+// the aimed split count the one whose workgroups best fill whole rounds is
+// taken: the workgroups of a launch all run about equally long, so a last round
+// half full idles half the chip for one workgroup's time (ACE application at
+// 96^3 x 1536: 4 -> 8 splits, about -2 %).  herm counts the tiles on and above
+// the diagonal that the Hermitian form launches.  Against four rounds of at
+// least 1024 values (the contraction with its reduction, us): 16 x 16 x 24^3
+// FP32 31 -> 11, 64 x 64 x 48^3 FP32 106 -> 47, 200 x 200 x 48^3 FP64 871 ->
+// 828, 300 x 300 x 60 x 60 x 90 FP32 1883 -> 1870; at least 64 values: 48^3
+// a fifth slower again (more partials to add).
+constexpr size_t kMinChunk = 128;
 static size_t xhy_kchunk(int na, int nb, size_t ng, int max_split, bool herm, int* nsplit) {
   constexpr size_t kResident = 2 * 256;
   const size_t ta = size_t(na + 63) / 64, tb = size_t(nb + 63) / 64;
   const size_t tiles = herm ? ta * (ta + 1) / 2 : ta * tb;
-  const size_t want0 = (2048 + tiles - 1) / tiles;
+  const size_t want0 = (kResident + tiles - 1) / tiles;
   size_t want = want0;
   double best = 0.0;
   for (size_t s = want0; s <= 2 * want0; ++s) {
@@ -332,7 +360,7 @@ static size_t xhy_kchunk(int na, int nb, size_t ng, int max_split, bool herm, in
     }
   }
   size_t kchunk = (ng + want - 1) / want;
-  if (kchunk < 1024) kchunk = 1024;
+  if (kchunk < kMinChunk) kchunk = kMinChunk;
   if (max_split > 0 && (ng + kchunk - 1) / kchunk > size_t(max_split))
     kchunk = (ng + size_t(max_split) - 1) / size_t(max_split);
   kchunk = (kchunk + 15) / 16 * 16;
@@ -340,8 +368,8 @@ static size_t xhy_kchunk(int na, int nb, size_t ng, int max_split, bool herm, in
   return kchunk;
 }
 
-size_t gemm_xhy_part_elems(int na, int nb, size_t ng, int* nsplit) {
-  xhy_kchunk(na, nb, ng, 0, false, nsplit);
+size_t gemm_xhy_part_elems(int na, int nb, size_t ng, int* nsplit, bool herm) {
+  xhy_kchunk(na, nb, ng, 0, herm, nsplit);
   return size_t(*nsplit) * na * nb;
 }
 
@@ -369,9 +397,13 @@ static hipError_t xhy_launch(bool fp32, int na, int nb, size_t ng, const void* X
                        static_cast<const cpx<double>*>(X), static_cast<const cpx<double>*>(Y),
                        part, kchunk, tri);
   const size_t n = size_t(na) * nb;
-  const int blocks = int((n + 255) / 256 < 4096 ? (n + 255) / 256 : 4096);
-  hipLaunchKernelGGL(xhy_reduce_k, dim3(blocks), dim3(256), 0, s, na, nb, part, nsplit, scale, M,
-                     ldm, M32, int(herm));
+  const bool many = nsplit >= 32;
+  const size_t blocks = many ? (n + 15) / 16 : (n + 255) / 256;
+  const dim3 rg(unsigned(blocks < 4096 ? blocks : 4096));
+  if (many)
+    hipLaunchKernelGGL(xhy_reduce_k<16>, rg, dim3(256), 0, s, na, nb, part, nsplit, scale, M, ldm, M32, int(herm));
+  else
+    hipLaunchKernelGGL(xhy_reduce_k<1>, rg, dim3(256), 0, s, na, nb, part, nsplit, scale, M, ldm, M32, int(herm));
   return hipGetLastError();
 }
 

@@ -187,7 +187,7 @@ AceLayout ace_layout(const px_cell* cell, px_precision prec, int n, int ic, int 
   a.dinv = off;
   off = align_up(off + px::chol_dinv_bytes(n));
   int nsplit = 0;
-  const size_t pe = px::gemm_xhy_part_elems(n, n, ngrid(cell), &nsplit);
+  const size_t pe = px::gemm_xhy_part_elems(n, n, ngrid(cell), &nsplit, true);
   a.part = off;
   off = align_up(off + pe * 16);
   a.end = off;
@@ -285,7 +285,7 @@ StepLayout step_layout(const px_cell* cell, px_precision prec, int n, int n_phi,
   l.ap = apply_layout(cell, n, n_phi);
   size_t off = l.ap.end;
   int nsplit = 0;
-  const size_t pe = px::gemm_xhy_part_elems(n_phi, n_phi, ngrid(cell), &nsplit);
+  const size_t pe = px::gemm_xhy_part_elems(n_phi, n_phi, ngrid(cell), &nsplit, true);
   l.part2 = off;
   off = align_up(off + pe * 16);
   const size_t blk = size_t(n_phi) * ngrid(cell) * elem_bytes(prec);
@@ -673,7 +673,7 @@ px_status ace_build_run(px_context* ctx, const px_cell* cell, px_precision prec,
     if (st != PX_OK) return st;
   }
   int nsplit = 0;
-  px::gemm_xhy_part_elems(n, n, ng, &nsplit);
+  px::gemm_xhy_part_elems(n, n, ng, &nsplit, true);
   if (ctx->profiling) (void)hipEventRecord(ev[1], stream);
   // M = dV Psi^H W, Hermitised; -M = L L^H; U = L^{-H}; xi = W U
   // M is Hermitian up to rounding: the tiles above the diagonal are mirrored
@@ -1102,7 +1102,7 @@ px_status px_ptim_step(px_context* ctx, const px_cell* cell, px_precision prec, 
   int32_t* sts = reinterpret_cast<int32_t*>(w + l.st);
   int ns1 = 0, ns2 = 0;
   px::gemm_xhy_part_elems(n, n_phi, ng, &ns1);
-  px::gemm_xhy_part_elems(n_phi, n_phi, ng, &ns2);
+  px::gemm_xhy_part_elems(n_phi, n_phi, ng, &ns2, true);
   void* pbufs[2] = {w + l.buf0, w + l.buf1};
   double* sbufs[2] = {D(l.sbuf0), D(l.sbuf1)};
   const void* cur_p = phi_n;
@@ -1400,7 +1400,7 @@ BatchPlan plan_batch(const px_context* c, int n_inst, const px_instance* in, px_
     size_t part = 0;
     for (int k = 0; k < n_inst; ++k) {
       int ns = 0;
-      part = std::max(part, px::gemm_xhy_part_elems(in[k].n, in[k].n, ngrid(&in[k].cell), &ns));
+      part = std::max(part, px::gemm_xhy_part_elems(in[k].n, in[k].n, ngrid(&in[k].cell), &ns, true));
     }
     P.part_off.resize(px_context::kTailLanes);
     for (int l = 0; l < px_context::kTailLanes; ++l) {
@@ -1490,7 +1490,7 @@ px_status enqueue_tail(px_context* c, const BatchPlan& P, const TailGroup& g, co
       if (st != PX_OK) return st;
     }
     int nsplit = 0;
-    px::gemm_xhy_part_elems(x.n, x.n, ng, &nsplit);
+    px::gemm_xhy_part_elems(x.n, x.n, ng, &nsplit, true);
     st = hip_check(c, px::launch_gemm_xhy_herm(fp32, x.n, ng, x.psi, ws + P.W_off[k],
                                                omega / double(ng), P.jobs[q].M, part, nsplit, ls),
                    "batched M");
