@@ -236,111 +236,19 @@ hipError_t launch_energy(const double* S, const double* occ, int n, double scale
 
 }  // namespace px
 
-// ---------------------------------------------------------------- PT-IM-style loop
+// ---------------------------------------------------------------- midpoint of sigma
 namespace px {
 
-template <typename T> struct V2;
-template <> struct V2<double> { typedef double t __attribute__((ext_vector_type(2))); };
-template <> struct V2<float> { typedef float t __attribute__((ext_vector_type(2))); };
-
-// mid = (a + b)/2 over n complex values
-template <typename T>
-__global__ void midpoint_k(size_t n, const T* a, const T* b, T* mid) {
-  using V = typename V2<T>::t;
-  for (size_t i = size_t(blockIdx.x) * blockDim.x + threadIdx.x; i < n;
-       i += size_t(gridDim.x) * blockDim.x) {
-    V x = reinterpret_cast<const V*>(a)[i], y = reinterpret_cast<const V*>(b)[i];
-    V m = {T(0.5) * (x.x + y.x), T(0.5) * (x.y + y.y)};
-    reinterpret_cast<V*>(mid)[i] = m;
-  }
+// mid = (a + b)/2 over n complex128 values
+__global__ void midpoint_k(size_t n, const double* a, const double* b, double* mid) {
+  for (size_t i = size_t(blockIdx.x) * blockDim.x + threadIdx.x; i < 2 * n;
+       i += size_t(gridDim.x) * blockDim.x)
+    mid[i] = 0.5 * (a[i] + b[i]);
 }
 
-// nxt = phi_n - i*c*(y + y2) (y2 nullable); per-block FP64 partials of
-// |nxt - cur|^2 and |nxt|^2
-template <typename T>
-__global__ __launch_bounds__(256) void ptim_update_k(size_t n, const T* phi_n, const T* y,
-                                                     const T* y2, const T* cur, T* nxt, double c,
-                                                     double* partial) {
-  using V = typename V2<T>::t;
-  __shared__ double red[2][256];
-  double dd = 0.0, nn = 0.0;
-  for (size_t i = size_t(blockIdx.x) * blockDim.x + threadIdx.x; i < n;
-       i += size_t(gridDim.x) * blockDim.x) {
-    V p = reinterpret_cast<const V*>(phi_n)[i], v = reinterpret_cast<const V*>(y)[i];
-    double vr = double(v.x), vi = double(v.y);
-    if (y2) {  // the two terms are added in FP64
-      const V w = reinterpret_cast<const V*>(y2)[i];
-      vr += double(w.x);
-      vi += double(w.y);
-    }
-    V q = reinterpret_cast<const V*>(cur)[i];
-    // -i c (vr + i vi) = c vi - i c vr
-    const double nr = double(p.x) + c * vi, ni = double(p.y) - c * vr;
-    V o = {T(nr), T(ni)};
-    reinterpret_cast<V*>(nxt)[i] = o;
-    const double dr = double(o.x) - double(q.x), di = double(o.y) - double(q.y);
-    dd += dr * dr + di * di;
-    nn += double(o.x) * double(o.x) + double(o.y) * double(o.y);
-  }
-  red[0][threadIdx.x] = dd;
-  red[1][threadIdx.x] = nn;
-  __syncthreads();
-  for (int off = 128; off > 0; off >>= 1) {
-    if (threadIdx.x < off) {
-      red[0][threadIdx.x] += red[0][threadIdx.x + off];
-      red[1][threadIdx.x] += red[1][threadIdx.x + off];
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    partial[2 * blockIdx.x] = red[0][0];
-    partial[2 * blockIdx.x + 1] = red[1][0];
-  }
-}
-
-// res = sqrt(sum dd / sum nn) over nblocks partials, fixed order
-__global__ void residual_k(const double* partial, int nblocks, double* res) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  double a = 0.0, b = 0.0;
-  for (int k = 0; k < nblocks; ++k) {
-    a += partial[2 * k];
-    b += partial[2 * k + 1];
-  }
-  *res = sqrt(a / b);
-}
-
-constexpr int kUpdateBlocks = 1024;
-
-int ptim_update_blocks() { return kUpdateBlocks; }
-
-hipError_t launch_midpoint(bool fp32, size_t n, const void* a, const void* b, void* mid,
-                           hipStream_t s) {
-  const int blocks = int((n + 255) / 256 < 8192 ? (n + 255) / 256 : 8192);
-  if (fp32)
-    hipLaunchKernelGGL(midpoint_k<float>, dim3(blocks), dim3(256), 0, s, n,
-                       static_cast<const float*>(a), static_cast<const float*>(b),
-                       static_cast<float*>(mid));
-  else
-    hipLaunchKernelGGL(midpoint_k<double>, dim3(blocks), dim3(256), 0, s, n,
-                       static_cast<const double*>(a), static_cast<const double*>(b),
-                       static_cast<double*>(mid));
-  return hipGetLastError();
-}
-
-hipError_t launch_ptim_update(bool fp32, size_t n, const void* phi_n, const void* y,
-                              const void* y2, const void* cur, void* nxt, double c, double* partial,
-                              double* res, hipStream_t s) {
-  if (fp32)
-    hipLaunchKernelGGL(ptim_update_k<float>, dim3(kUpdateBlocks), dim3(256), 0, s, n,
-                       static_cast<const float*>(phi_n), static_cast<const float*>(y),
-                       static_cast<const float*>(y2), static_cast<const float*>(cur),
-                       static_cast<float*>(nxt), c, partial);
-  else
-    hipLaunchKernelGGL(ptim_update_k<double>, dim3(kUpdateBlocks), dim3(256), 0, s, n,
-                       static_cast<const double*>(phi_n), static_cast<const double*>(y),
-                       static_cast<const double*>(y2), static_cast<const double*>(cur),
-                       static_cast<double*>(nxt), c, partial);
-  hipLaunchKernelGGL(residual_k, dim3(1), dim3(64), 0, s, partial, kUpdateBlocks, res);
+hipError_t launch_midpoint(size_t n, const double* a, const double* b, double* mid, hipStream_t s) {
+  const size_t blocks = (2 * n + 255) / 256;
+  hipLaunchKernelGGL(midpoint_k, dim3(unsigned(blocks < 8192 ? blocks : 8192)), dim3(256), 0, s, n, a, b, mid);
   return hipGetLastError();
 }
 
@@ -348,6 +256,10 @@ hipError_t launch_ptim_update(bool fp32, size_t n, const void* phi_n, const void
 
 // ---------------------------------------------------------------- density
 namespace px {
+
+template <typename T> struct V2;
+template <> struct V2<double> { typedef double t __attribute__((ext_vector_type(2))); };
+template <> struct V2<float> { typedef float t __attribute__((ext_vector_type(2))); };
 
 // rho(r) = sum_i w_i |phi_i(r)|^2 with the occupation-matrix eigenvalues w_i
 // (Eq. 12 with sigma diagonalised: N products instead of N^2), accumulated in

@@ -230,7 +230,7 @@ LoopLayout loop_layout(const px_cell* cell, px_precision prec, int n, int n_phi)
   l.buf1 = off;
   off = align_up(off + blk);
   l.partial = off;
-  off = align_up(off + size_t(px::ptim_update_blocks()) * 16);
+  off = align_up(off + px::ptim_xc_partials(n_phi, ngrid(cell)) * sizeof(double));
   l.end = off;
   return l;
 }
@@ -295,7 +295,7 @@ StepLayout step_layout(const px_cell* cell, px_precision prec, int n, int n_phi,
     off = align_up(off + blk);
   }
   l.partial = off;
-  off = align_up(off + size_t(px::ptim_update_blocks()) * 16);
+  off = align_up(off + px::ptim_xc_partials(n_phi, ngrid(cell)) * sizeof(double));
   const size_t mat = size_t(n_phi) * n_phi * 16;
   size_t* mats[12] = {&l.S, &l.Hm, &l.Mneg, &l.L, &l.U, &l.T, &l.X, &l.smid, &l.sbuf0, &l.sbuf1,
                       &l.A1, &l.A2};
@@ -809,14 +809,12 @@ px_status px_ptim_exchange_loop(px_context* ctx, const px_cell* cell, px_precisi
   if (he != hipSuccess) return hip_check(ctx, he, "hipSetDevice");
   const bool fp32 = prec == PX_PREC_FP32;
   const size_t ng = ngrid(cell);
-  const size_t nel = size_t(n_phi) * ng;
   const double dV = cell->L[0] * cell->L[1] * cell->L[2] / double(ng);
   double* C = reinterpret_cast<double*>(ctx->ws + l.ap.C);
   float* C32 = fp32 ? reinterpret_cast<float*>(ctx->ws + l.ap.C32) : nullptr;
   const void* Cc = fp32 ? static_cast<const void*>(C32) : C;
   double* part = reinterpret_cast<double*>(ctx->ws + l.ap.part);
   void* mid = ctx->ws + l.mid;
-  void* y = mid;
   void* bufs[2] = {ctx->ws + l.buf0, ctx->ws + l.buf1};
   double* partial = reinterpret_cast<double*>(ctx->ws + l.partial);
   int nsplit = 0;
@@ -824,18 +822,15 @@ px_status px_ptim_exchange_loop(px_context* ctx, const px_cell* cell, px_precisi
   const void* cur = phi_n;
   for (int k = 0; k < n_iter; ++k) {
     void* nxt = (k == n_iter - 1) ? phi_out : bufs[k & 1];
-    st = hip_check(ctx, px::launch_midpoint(fp32, nel, phi_n, cur, mid, stream), "midpoint");
-    if (st != PX_OK) return st;
-    st = hip_check(ctx, px::launch_gemm_xhy(fp32, n, n_phi, ng, xi, mid, dV, C, n_phi, part,
-                                            nsplit, C32, stream),
+    // (the first midpoint is phi_n itself; the update leaves the next one)
+    st = hip_check(ctx, px::launch_gemm_xhy(fp32, n, n_phi, ng, xi, k == 0 ? phi_n : mid, dV, C, n_phi,
+                                            part, nsplit, C32, stream),
                    "C = dV xi^H mid");
     if (st != PX_OK) return st;
-    st = hip_check(ctx, px::launch_gemm_xc(fp32, n, n_phi, ng, xi, Cc, n_phi, -1.0, y, false, stream),
-                   "y = -xi C");
-    if (st != PX_OK) return st;
-    st = hip_check(ctx, px::launch_ptim_update(fp32, nel, phi_n, y, nullptr, cur, nxt, dt_alpha,
-                                               partial, residuals + k, stream),
-                   "update");
+    st = hip_check(ctx, px::launch_ptim_xc(fp32, n, n_phi, ng, xi, Cc, n_phi,
+                                           {phi_n, nullptr, cur, nxt, k + 1 < n_iter ? mid : nullptr,
+                                            dt_alpha, partial, residuals + k}, stream),
+                   "update with -xi C");
     if (st != PX_OK) return st;
     cur = nxt;
   }
@@ -1090,7 +1085,6 @@ px_status px_ptim_step(px_context* ctx, const px_cell* cell, px_precision prec, 
   if (he != hipSuccess) return hip_check(ctx, he, "hipSetDevice");
   const bool fp32 = prec == PX_PREC_FP32;
   const size_t ng = ngrid(cell);
-  const size_t nel = size_t(n_phi) * ng;
   const double dV = cell->L[0] * cell->L[1] * cell->L[2] / double(ng);
   char* w = ctx->ws;
   auto D = [w](size_t off) { return reinterpret_cast<double*>(w + off); };
@@ -1112,9 +1106,10 @@ px_status px_ptim_step(px_context* ctx, const px_cell* cell, px_precision prec, 
     const bool last = k == n_iter - 1;
     void* nxt_p = last ? phi_out : pbufs[k & 1];
     double* nxt_s = last ? sigma_out : sbufs[k & 1];
-    void* mid = w + l.mid;
-    // Eq. 4: midpoints
-    if ((st = ok(px::launch_midpoint(fp32, nel, phi_n, cur_p, mid, stream), "midpoint")) != PX_OK) return st;
+    // Eq. 4: midpoints (the first is phi_n itself; the orbital update leaves the
+    // next one in the buffer that this iteration does not read)
+    const void* mid = k == 0 ? phi_n : w + (k & 1 ? l.mid : l.Z);
+    void* nxt_mid = last ? nullptr : w + (k & 1 ? l.Z : l.mid);
     // Y = V_ACE mid = -xi (dV xi^H mid) (Eq. 14; alpha is folded into dt_alpha)
     if ((st = ok(px::launch_gemm_xhy(fp32, n, n_phi, ng, xi, mid, dV, C, n_phi, D(l.ap.part), ns1, C32,
                                      stream), "C = dV xi^H mid")) != PX_OK) return st;
@@ -1140,14 +1135,13 @@ px_status px_ptim_step(px_context* ctx, const px_cell* cell, px_precision prec, 
       return st;
     if (fp32 && (st = ok(px::launch_convert_f64_f32(size_t(2) * n_phi * n_phi, D(l.X), X32, stream),
                          "X to FP32")) != PX_OK) return st;
-    // Z = -mid X (the projection P~ Y with its sign), then Phi^(k+1) = Phi_n - i dt_alpha (Y + Z)
-    if ((st = ok(px::launch_gemm_xc(fp32, n_phi, n_phi, ng, mid, Xc, n_phi, -1.0, w + l.Z, false, stream),
-                 "Z = -mid X")) != PX_OK) return st;
-    if ((st = ok(px::launch_ptim_update(fp32, nel, phi_n, w + l.Y, w + l.Z, cur_p, nxt_p, dt_alpha,
-                                        D(l.partial), residuals + k, stream), "orbital update")) != PX_OK)
+    // Phi^(k+1) = Phi_n - i dt_alpha (Y + Z), Z = -mid X (the projection P~ Y with its sign)
+    if ((st = ok(px::launch_ptim_xc(fp32, n_phi, n_phi, ng, mid, Xc, n_phi,
+                                    {phi_n, w + l.Y, cur_p, nxt_p, nxt_mid, dt_alpha, D(l.partial),
+                                     residuals + k}, stream), "orbital update with -mid X")) != PX_OK)
       return st;
     // sigma^(k+1) = sigma_n - i dt_alpha (Hm smid - smid Hm) (Eq. 6)
-    if ((st = ok(px::launch_midpoint(false, size_t(n_phi) * n_phi, sigma_n, cur_s, D(l.smid), stream),
+    if ((st = ok(px::launch_midpoint(size_t(n_phi) * n_phi, sigma_n, cur_s, D(l.smid), stream),
                  "sigma midpoint")) != PX_OK) return st;
     if ((st = ok(px::launch_zgemm(false, n_phi, D(l.Hm), D(l.smid), D(l.A1), stream), "Hm smid")) != PX_OK)
       return st;

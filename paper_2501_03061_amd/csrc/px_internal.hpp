@@ -178,14 +178,8 @@ hipError_t launch_expart_reduce(const double* expart, const G0Part* g0, int n2, 
 hipError_t launch_energy(const double* S, const double* occ, int n, double scale, double* e_x,
                          hipStream_t s);
 
-// PT-IM-style loop pieces (n = complex element count)
-hipError_t launch_midpoint(bool fp32, size_t n, const void* a, const void* b, void* mid,
-                           hipStream_t s);
-// nxt = phi_n - i*c*(y + y2) (y2 nullable); res = ||nxt - cur|| / ||nxt|| accumulated in FP64
-hipError_t launch_ptim_update(bool fp32, size_t n, const void* phi_n, const void* y,
-                              const void* y2, const void* cur, void* nxt, double c, double* partial,
-                              double* res, hipStream_t s);
-int ptim_update_blocks();
+// mid = (a + b)/2 over n complex128 values
+hipError_t launch_midpoint(size_t n, const double* a, const double* b, double* mid, hipStream_t s);
 
 // rho[r] = sum_i w[i] |phi_i(r)|^2 (FP64), phi [n][ng] complex in the form's precision
 hipError_t launch_density(bool fp32, size_t ng, int n, const void* phi, const double* w,
@@ -219,6 +213,26 @@ size_t gemm_xhy_part_elems(int na, int nb, size_t ng, int* nsplit, bool herm = f
 // Splits launch_gemm_xhy uses when at most max_split are available (fewer,
 // longer splits than the default when max_split is below it).
 int gemm_xhy_splits(int na, int nb, size_t ng, int max_split);
+// One update of the implicit-midpoint fixed point with the product Z[b][r] =
+// -sum_a X[a][r] C[a][b] as its last term (gemm_xc with alpha = -1; the product
+// rounded to the form's type, then added to y in FP64):
+//   nxt = phi_n - i c (y + Z) (y nullable), mid = (phi_n + nxt)/2 (nullable; the
+//   next iteration's midpoint), res = ||nxt - cur|| / ||nxt|| summed in FP64.
+// Blocks [nb][ng]; nxt and mid may not overlap X (other workgroups read it).
+// partial: ptim_xc_partials(nb, ng) doubles.
+struct PtimUpdate {
+  const void* phi_n;
+  const void* y;
+  const void* cur;
+  void* nxt;
+  void* mid;
+  double c;
+  double* partial;
+  double* res;
+};
+size_t ptim_xc_partials(int nb, size_t ng);
+hipError_t launch_ptim_xc(bool fp32, int na, int nb, size_t ng, const void* X, const void* C, int ldc,
+                          const PtimUpdate& p, hipStream_t s);
 // Z[b][r] = alpha * sum_a X[a][r] C[a][b]
 //   X: [na][ng], C: [na][ldc] row-major in the precision of the form (complex128, or
 //   complex64 rounded from the FP64 matrix), Z: [nb][ng]; upper: C upper triangular

@@ -9,6 +9,7 @@ products, each within a few eps = 6e-8 of the operands' norms)."""
 import numpy as np
 import pytest
 
+import oracle
 from paper_2501_03061_amd import px
 from _gpu import banner, relerr, to_dev, to_host
 
@@ -39,3 +40,31 @@ def test_ace_apply_edges(px_ctx, n, n_xi, n_phi, fp32):
         err = relerr(out, ref)
         print(f"{f.__name__} {err:.2e}", flush=True)
         assert err < (5e-6 if fp32 else 1e-13)
+
+
+@pytest.mark.parametrize("fp32", [False, True])
+@pytest.mark.parametrize("n,n_xi,n_phi,iters", [((5, 7, 9), 4, 1, 1), ((16, 16, 16), 9, 17, 2), ((10, 12, 11), 33, 65, 3)])
+def test_loop_edges(px_ctx, n, n_xi, n_phi, iters, fp32):
+    """The fixed point's update in the contraction's stores: the first midpoint
+    is phi_n itself, the last iteration leaves none; tolerances as above, the
+    map being contracted with a norm below one (residuals to 1e-9, 1e-5)."""
+    import torch
+    ng = n[0] * n[1] * n[2]
+    if fp32 and ng % 2:
+        pytest.skip("the FP32 form needs an even N_g")
+    banner(f"ptim loop grid {n} n={n_xi} n_phi={n_phi} iters={iters} fp32={fp32}")
+    rng = np.random.default_rng(6)
+    dt = np.complex64 if fp32 else np.complex128
+    shape = (n[2], n[1], n[0])
+    dV, dta = 0.28 ** 3, 0.25
+    xi, phi = [((rng.standard_normal((k, *shape)) + 1j * rng.standard_normal((k, *shape))) / np.sqrt(dV * ng * n_xi)).astype(dt)
+               for k in (n_xi, n_phi)]
+    ref, rres = oracle.ptim_exchange_loop(xi.astype(np.complex128), phi.astype(np.complex128), dV, n_iter=iters, dt=dta, alpha=1.0)
+    cell = px.Cell(tuple(0.28 * m for m in n), n)
+    out, res = px_ctx.px_ptim_exchange_loop(cell, to_dev(xi), to_dev(phi), iters, dta)
+    torch.cuda.synchronize()
+    err = relerr(to_host(out), ref)
+    rerr = np.abs(to_host(res) - np.array(rres)).max()
+    print(f"loop {err:.2e} residuals {rerr:.2e}", flush=True)
+    assert err < (5e-6 if fp32 else 1e-13)
+    assert rerr < (1e-5 if fp32 else 1e-9)
