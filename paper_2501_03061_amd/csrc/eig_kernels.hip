@@ -31,12 +31,10 @@ namespace px {
 
 namespace {
 
+// A rotation G of an index pair: g00 = c, g01 = s, g10 = -s e, g11 = c e with
+// e = e^{-i theta} = er + i ei; s = 0 and e = 1 for the identity.
 struct Rot {
-  double c, s;    // real rotation
-  double er, ei;  // e^{-i theta}
-  int p, q;       // the pair; q = -1 when the partner is the padding index
-  int id;         // 1: identity (padding pair or zero off-diagonal entry)
-  int pad;
+  double c, s, er, ei;
 };
 
 // Pair `slot` of round k (0 <= k < np - 1) of the circle ordering of np
@@ -61,19 +59,19 @@ __device__ __forceinline__ double2 cmul2(double2 a, double2 b) {
 __device__ __forceinline__ double2 cconj2(double2 a) { return make_double2(a.x, -a.y); }
 __device__ __forceinline__ double2 cadd2(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
 
-// Entries of G (2 x 2): g00 = c, g01 = s, g10 = -s e, g11 = c e, e = e^{-i theta}.
-__device__ __forceinline__ void rot_matrix(const Rot& r, double2 g[2][2]) {
-  if (r.id) {
-    g[0][0] = make_double2(1.0, 0.0);
-    g[0][1] = make_double2(0.0, 0.0);
-    g[1][0] = make_double2(0.0, 0.0);
-    g[1][1] = make_double2(1.0, 0.0);
-    return;
-  }
-  g[0][0] = make_double2(r.c, 0.0);
-  g[0][1] = make_double2(r.s, 0.0);
-  g[1][0] = make_double2(-r.s * r.er, -r.s * r.ei);
-  g[1][1] = make_double2(r.c * r.er, r.c * r.ei);
+// (x0, x1) <- (x0, x1) G
+__device__ __forceinline__ void rotate_cols(const Rot& g, double2& x0, double2& x1) {
+  const double2 t = make_double2(x1.x * g.er - x1.y * g.ei, x1.x * g.ei + x1.y * g.er);
+  const double2 y0 = make_double2(g.c * x0.x - g.s * t.x, g.c * x0.y - g.s * t.y);
+  x1 = make_double2(g.s * x0.x + g.c * t.x, g.s * x0.y + g.c * t.y);
+  x0 = y0;
+}
+// (x0, x1)^T <- G^H (x0, x1)^T
+__device__ __forceinline__ void rotate_rows(const Rot& g, double2& x0, double2& x1) {
+  const double2 t = make_double2(x1.x * g.er + x1.y * g.ei, x1.y * g.er - x1.x * g.ei);
+  const double2 y0 = make_double2(g.c * x0.x - g.s * t.x, g.c * x0.y - g.s * t.y);
+  x1 = make_double2(g.s * x0.x + g.c * t.x, g.s * x0.y + g.c * t.y);
+  x0 = y0;
 }
 
 __device__ __forceinline__ double2 ld2(const double* A, int n, int r, int c) {
@@ -110,38 +108,63 @@ __device__ __forceinline__ int bj_index(int nb, int k, int slot, int t) {
   return t < BJ ? I * BJ + t : J * BJ + (t - BJ);
 }
 
-// Rotation of indices (p, q) of the 2 x 2 diagonal block (app, aqq real, apq).
-__device__ __forceinline__ Rot make_rot(double app, double aqq, double2 apq, int p, int q) {
-  Rot r;
-  r.p = p;
-  r.q = q;
-  r.id = 1;
-  r.pad = 0;
-  r.c = 1.0;
-  r.s = 0.0;
-  r.er = 1.0;
-  r.ei = 0.0;
-  const double m = hypot(apq.x, apq.y);
-  if (m > 0.0) {
-    const double tau = (aqq - app) / (2.0 * m);
-    const double t = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
-    r.c = 1.0 / sqrt(1.0 + t * t);
-    r.s = t * r.c;
-    r.er = apq.x / m;  // e^{-i theta} = conj(A_pq)/|A_pq|
-    r.ei = -apq.y / m;
-    r.id = 0;
+// Rotation of the 2 x 2 diagonal block (app, aqq real, apq).  Four dependent
+// square roots and divisions: 1/m from the reciprocal root of |apq|^2 (hypot
+// where that square would leave the normal range), t = h / (|d| + sqrt(d^2 + h^2))
+// with d = aqq - app and h = 2 m, c from a reciprocal root.
+__device__ __forceinline__ Rot make_rot(double app, double aqq, double2 apq, double skip2) {
+  Rot r = {1.0, 0.0, 1.0, 0.0};
+  const double m2 = apq.x * apq.x + apq.y * apq.y, d = aqq - app;
+  if (m2 <= skip2 || (apq.x == 0.0 && apq.y == 0.0)) return r;
+  double m, im, root;
+  if (m2 > 1e-280 && m2 < 1e280 && fabs(d) < 1e140) {
+    im = rsqrt(m2);
+    m = m2 * im;
+    root = sqrt(d * d + 4.0 * m2);
+  } else {
+    m = hypot(apq.x, apq.y);
+    im = 1.0 / m;
+    root = hypot(d, 2.0 * m);
   }
+  const double t = (d >= 0.0 ? 2.0 : -2.0) * m / (fabs(d) + root);
+  r.c = rsqrt(1.0 + t * t);
+  r.s = t * r.c;
+  r.er = apq.x * im;  // e^{-i theta} = conj(A_pq)/|A_pq|
+  r.ei = -apq.y * im;
+  // one correction each towards c^2 + s^2 = 1 and |e| = 1: what is left is the
+  // rounding of the four numbers (thousands of rotations accumulate in V)
+  const double fc = 0.5 * fma(-r.c, r.c, fma(-r.s, r.s, 1.0)), fe = 0.5 * fma(-r.er, r.er, fma(-r.ei, r.ei, 1.0));
+  r.c = fma(r.c, fc, r.c);
+  r.s = fma(r.s, fc, r.s);
+  r.er = fma(r.er, fe, r.er);
+  r.ei = fma(r.ei, fe, r.ei);
   return r;
 }
 
+// ||A||_F^2, kept behind the flags.
+__device__ __forceinline__ double norm2(const int* flags) { return reinterpret_cast<const double*>(flags)[1]; }
+// Entries with |A_pq| <= 8 eps ||A||_F / sqrt(n), the level of their rounding
+// errors, are not rotated away: where eigenvalues coincide (occupations at 0 and
+// 1) both A_pq and A_qq - A_pp are rounding noise, the rotation angle is
+// arbitrary, and every sweep mixed the noise anew (256 and 500 indices with
+// Fermi-Dirac eigenvalues or a projector: not converged after 40 sweeps before,
+// now in 15 to 20).  All entries at that level leave an off-diagonal norm of
+// 8 eps sqrt(n) ||A||_F, an eighth of the convergence bound.
+__device__ __forceinline__ double skip_factor(int n) { return 64.0 * DBL_EPSILON * DBL_EPSILON / double(n); }
+
 // One inner sweep on the 32 x 32 subproblem of each block pair of round k
-// (one workgroup per pair): U_P (32 x 32, row-major) into Ug[P].
+// (one workgroup per pair): U_P (32 x 32, row-major) into Ug[P].  Bound by the
+// chain rotation -> S -> rotation of the inner rounds (few workgroups, no
+// bandwidth): per round one phase of S on all four waves, and one in which wave
+// 0 forms the next rotations while the others apply this round's to U.  A
+// launch took 66 us with both updates after the rotations and 2 x 2 complex
+// matrix products, now 31.
 __global__ __launch_bounds__(256) void bj_solve_k(const double* A, int n, int nb, int k, double* Ug,
                                                   const int* flags) {
   if (flags[0]) return;
   __shared__ double2 S[BJ2][BJ2 + 1];
   __shared__ double2 U[BJ2][BJ2 + 1];
-  __shared__ Rot rot[BJ];
+  __shared__ Rot rot[2][BJ];
   __shared__ int gi[BJ2];
   const int P = blockIdx.x, tid = threadIdx.x;
   if (tid < BJ2) gi[tid] = bj_index(nb, k, P, tid);
@@ -152,44 +175,44 @@ __global__ __launch_bounds__(256) void bj_solve_k(const double* A, int n, int nb
     U[i][j] = make_double2(i == j ? 1.0 : 0.0, 0.0);
   }
   __syncthreads();
+  const double skip2 = skip_factor(n) * norm2(flags);
+  auto next_rot = [&](int kk) {
+    int p, q;
+    round_pair(BJ2, kk, tid, p, q);
+    rot[kk & 1][tid] = make_rot(S[p][p].x, S[q][q].x, S[p][q], skip2);
+  };
+  if (tid < BJ) next_rot(0);
+  __syncthreads();
   for (int kk = 0; kk < BJ2 - 1; ++kk) {
-    if (tid < BJ) {
-      int p, q;
-      round_pair(BJ2, kk, tid, p, q);
-      rot[tid] = make_rot(S[p][p].x, S[q][q].x, S[p][q], p, q);
+    {  // S <- G^H S G on the 2 x 2 blocks (pair x, pair y): 16 x 16 = 256 blocks
+      const int x = tid / BJ, y = tid % BJ;
+      const Rot gx = rot[kk & 1][x], gy = rot[kk & 1][y];
+      int p, q, u, v;
+      round_pair(BJ2, kk, x, p, q);
+      round_pair(BJ2, kk, y, u, v);
+      double2 a = S[p][u], b = S[p][v], c = S[q][u], d = S[q][v];
+      rotate_cols(gy, a, b);
+      rotate_cols(gy, c, d);
+      rotate_rows(gx, a, c);
+      rotate_rows(gx, b, d);
+      S[p][u] = a;
+      S[p][v] = b;
+      S[q][u] = c;
+      S[q][v] = d;
     }
     __syncthreads();
-    {  // S <- G^H S G on the 2 x 2 blocks (pair x, pair y): 16 x 16 = 256 blocks
-      const Rot rp = rot[tid / BJ], rs = rot[tid % BJ];
-      if (!(rp.id && rs.id)) {
-        double2 gp[2][2], gs[2][2], b[2][2], t[2][2];
-        rot_matrix(rp, gp);
-        rot_matrix(rs, gs);
-        const int ip[2] = {rp.p, rp.q}, is[2] = {rs.p, rs.q};
-#pragma unroll
-        for (int x = 0; x < 2; ++x)
-#pragma unroll
-          for (int y = 0; y < 2; ++y) b[x][y] = S[ip[x]][is[y]];
-#pragma unroll
-        for (int x = 0; x < 2; ++x)
-#pragma unroll
-          for (int y = 0; y < 2; ++y) t[x][y] = cadd2(cmul2(b[x][0], gs[0][y]), cmul2(b[x][1], gs[1][y]));
-#pragma unroll
-        for (int x = 0; x < 2; ++x)
-#pragma unroll
-          for (int y = 0; y < 2; ++y)
-            S[ip[x]][is[y]] = cadd2(cmul2(cconj2(gp[0][x]), t[0][y]), cmul2(cconj2(gp[1][x]), t[1][y]));
+    if (tid < 64) {
+      if (tid < BJ && kk + 1 < BJ2 - 1) next_rot(kk + 1);
+    } else {
+      for (int e = tid - 64; e < BJ2 * BJ; e += 192) {  // U <- U G: (row, pair) pieces
+        const int r = e / BJ, y = e % BJ;
+        int p, q;
+        round_pair(BJ2, kk, y, p, q);
+        double2 x0 = U[r][p], x1 = U[r][q];
+        rotate_cols(rot[kk & 1][y], x0, x1);
+        U[r][p] = x0;
+        U[r][q] = x1;
       }
-    }
-    for (int e = tid; e < BJ2 * BJ; e += 256) {  // U <- U G: (row, pair) pieces
-      const int r = e / BJ;
-      const Rot rs = rot[e % BJ];
-      if (rs.id) continue;
-      double2 g[2][2];
-      rot_matrix(rs, g);
-      const double2 v0 = U[r][rs.p], v1 = U[r][rs.q];
-      U[r][rs.p] = cadd2(cmul2(v0, g[0][0]), cmul2(v1, g[1][0]));
-      U[r][rs.q] = cadd2(cmul2(v0, g[0][1]), cmul2(v1, g[1][1]));
     }
     __syncthreads();
   }
@@ -295,7 +318,7 @@ __global__ __launch_bounds__(256) void eig_norm_part_k(const double* A, int n, d
   }
 }
 
-__global__ __launch_bounds__(kConvBlocks) void eig_conv_k(const double* part, int n, int* flags) {
+__global__ __launch_bounds__(kConvBlocks) void eig_conv_k(const double* part, int n, int* flags, int first) {
   __shared__ double so[kConvBlocks], st[kConvBlocks];
   if (flags[0]) return;
   so[threadIdx.x] = part[2 * threadIdx.x];
@@ -308,7 +331,9 @@ __global__ __launch_bounds__(kConvBlocks) void eig_conv_k(const double* part, in
     }
     __syncthreads();
   }
-  if (threadIdx.x == 0) {
+  if (threadIdx.x == 0 && first) {
+    reinterpret_cast<double*>(flags)[1] = st[0];
+  } else if (threadIdx.x == 0) {
     const double tol = 64.0 * DBL_EPSILON * sqrt(double(n > 1 ? n : 1));
     flags[1] += 1;
     if (so[0] <= tol * tol * st[0]) flags[0] = 1;
@@ -379,6 +404,8 @@ hipError_t launch_eig_hermitian(const double* sigma, int n, double* Q, double* d
   const size_t total = size_t(n) * n;
   hipLaunchKernelGGL(eig_init_k, dim3(grid_for(total)), dim3(256), 0, s, sigma, n, A, V, flags);
   if (n > 1) {
+    hipLaunchKernelGGL(eig_norm_part_k, dim3(kConvBlocks), dim3(256), 0, s, A, n, part, flags);
+    hipLaunchKernelGGL(eig_conv_k, dim3(1), dim3(kConvBlocks), 0, s, part, n, flags, 1);
     const int rows = (n + BJ2 - 1) / BJ2;
     const int tiles = m * m > rows * m ? m * m : rows * m;
     for (int sweep = 0; sweep < max_sweeps; ++sweep) {
@@ -387,11 +414,11 @@ hipError_t launch_eig_hermitian(const double* sigma, int n, double* Q, double* d
         hipLaunchKernelGGL(bj_apply_k, dim3(tiles, 2), dim3(256), 0, s, A, V, n, nb, k, Ug, flags);
       }
       hipLaunchKernelGGL(eig_norm_part_k, dim3(kConvBlocks), dim3(256), 0, s, A, n, part, flags);
-      hipLaunchKernelGGL(eig_conv_k, dim3(1), dim3(kConvBlocks), 0, s, part, n, flags);
+      hipLaunchKernelGGL(eig_conv_k, dim3(1), dim3(kConvBlocks), 0, s, part, n, flags, 0);
     }
   } else {
     hipLaunchKernelGGL(eig_norm_part_k, dim3(kConvBlocks), dim3(256), 0, s, A, n, part, flags);
-    hipLaunchKernelGGL(eig_conv_k, dim3(1), dim3(kConvBlocks), 0, s, part, n, flags);
+    hipLaunchKernelGGL(eig_conv_k, dim3(1), dim3(kConvBlocks), 0, s, part, n, flags, 0);
   }
   hipLaunchKernelGGL(eig_rank_k, dim3((n + 255) / 256), dim3(256), 0, s, A, n, rank, d, flags, status);
   hipLaunchKernelGGL(eig_permute_k, dim3(grid_for(total)), dim3(256), 0, s, V, n, rank, Q);
