@@ -108,31 +108,41 @@ __device__ __forceinline__ int bj_index(int nb, int k, int slot, int t) {
   return t < BJ ? I * BJ + t : J * BJ + (t - BJ);
 }
 
-// Rotation of the 2 x 2 diagonal block (app, aqq real, apq).  Four dependent
-// square roots and divisions: 1/m from the reciprocal root of |apq|^2 (hypot
-// where that square would leave the normal range), t = h / (|d| + sqrt(d^2 + h^2))
-// with d = aqq - app and h = 2 m, c from a reciprocal root.
+// 1/sqrt(x) and 1/x of a normal x, the hardware's approximation with one Newton
+// step (about 1e-13).
+__device__ __forceinline__ double rsq1(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  return fma(0.5 * y, fma(-x * y, y, 1.0), y);
+}
+__device__ __forceinline__ double rcp1(double x) {
+  const double y = __builtin_amdgcn_rcp(x);
+  return fma(y, fma(-x, y, 1.0), y);
+}
+
+// Rotation of the 2 x 2 diagonal block (app, aqq real, apq).  With m = |apq|,
+// d = aqq - app and h = 2 m the tangent is h / (|d| + sqrt(d^2 + h^2)); four
+// dependent roots and reciprocals.  Their error only leaves 1e-13 of the entry
+// behind; c^2 + s^2 = 1 and |e| = 1, which thousands of rotations accumulate in V,
+// are restored to the rounding of the four numbers by one correction each.
+// Outside the normal range of the squares: hypot and exact division.
 __device__ __forceinline__ Rot make_rot(double app, double aqq, double2 apq, double skip2) {
   Rot r = {1.0, 0.0, 1.0, 0.0};
   const double m2 = apq.x * apq.x + apq.y * apq.y, d = aqq - app;
   if (m2 <= skip2 || (apq.x == 0.0 && apq.y == 0.0)) return r;
-  double m, im, root;
+  double im, t;
   if (m2 > 1e-280 && m2 < 1e280 && fabs(d) < 1e140) {
-    im = rsqrt(m2);
-    m = m2 * im;
-    root = sqrt(d * d + 4.0 * m2);
+    im = rsq1(m2);
+    const double x = fma(d, d, 4.0 * m2);
+    t = (d >= 0.0 ? 2.0 : -2.0) * (m2 * im) * rcp1(fma(x, rsq1(x), fabs(d)));
   } else {
-    m = hypot(apq.x, apq.y);
+    const double m = hypot(apq.x, apq.y);
     im = 1.0 / m;
-    root = hypot(d, 2.0 * m);
+    t = (d >= 0.0 ? 2.0 : -2.0) * m / (fabs(d) + hypot(d, 2.0 * m));
   }
-  const double t = (d >= 0.0 ? 2.0 : -2.0) * m / (fabs(d) + root);
-  r.c = rsqrt(1.0 + t * t);
+  r.c = rsq1(fma(t, t, 1.0));
   r.s = t * r.c;
   r.er = apq.x * im;  // e^{-i theta} = conj(A_pq)/|A_pq|
   r.ei = -apq.y * im;
-  // one correction each towards c^2 + s^2 = 1 and |e| = 1: what is left is the
-  // rounding of the four numbers (thousands of rotations accumulate in V)
   const double fc = 0.5 * fma(-r.c, r.c, fma(-r.s, r.s, 1.0)), fe = 0.5 * fma(-r.er, r.er, fma(-r.ei, r.ei, 1.0));
   r.c = fma(r.c, fc, r.c);
   r.s = fma(r.s, fc, r.s);
@@ -158,7 +168,8 @@ __device__ __forceinline__ double skip_factor(int n) { return 64.0 * DBL_EPSILON
 // bandwidth): per round one phase of S on all four waves, and one in which wave
 // 0 forms the next rotations while the others apply this round's to U.  A
 // launch took 66 us with both updates after the rotations and 2 x 2 complex
-// matrix products, now 31.
+// matrix products, now 30 (twelve waves, U beside S: 31; what is left is mostly
+// the LDS traffic of the rotations, S and U).
 __global__ __launch_bounds__(256) void bj_solve_k(const double* A, int n, int nb, int k, double* Ug,
                                                   const int* flags) {
   if (flags[0]) return;
@@ -220,10 +231,38 @@ __global__ __launch_bounds__(256) void bj_solve_k(const double* A, int n, int nb
   for (int e = tid; e < BJ2 * BJ2; e += 256) out[e] = U[e / BJ2][e % BJ2];
 }
 
+typedef double d4 __attribute__((ext_vector_type(4)));
+
+// D (16 x 16 tile at (i0, j0)) = op(L) R of 32 x 32 complex matrices in LDS, one
+// wave per tile on v_mfma_f64_16x16x4f64 (lane l: left row and right column
+// l % 16, k = l / 16; result rows l / 16 + 4 t, column l % 16).  op: the matrix
+// itself, or its conjugate transpose.
+template <bool CT>
+__device__ __forceinline__ void tile_product(const double2 (*L)[BJ2 + 1], const double2 (*R)[BJ2 + 1], int i0, int j0,
+                                             d4& re, d4& im) {
+  const int m = threadIdx.x & 15, q = (threadIdx.x >> 4) & 3;
+  re = d4{0, 0, 0, 0};
+  im = d4{0, 0, 0, 0};
+#pragma unroll
+  for (int k = 0; k < BJ2; k += 4) {
+    double2 a = CT ? L[k + q][i0 + m] : L[i0 + m][k + q];
+    if (CT) a.y = -a.y;
+    const double2 b = R[k + q][j0 + m];
+    re = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.x, re, 0, 0, 0);
+    im = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.y, im, 0, 0, 0);
+    re = __builtin_amdgcn_mfma_f64_16x16x4f64(-a.y, b.y, re, 0, 0, 0);
+    im = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, b.x, im, 0, 0, 0);
+  }
+}
+
 // The block rotations of round k: A_PS <- U_P^H A_PS U_S for every pair of
 // block pairs (blockIdx.y = 0, blockIdx.x = P * m + S), V_rS <- V_rS U_S for
 // every 32-row tile r and block pair S (blockIdx.y = 1, blockIdx.x = r * m + S).
-// Each tile is read and written by its own workgroup only.
+// Each tile is read and written by its own workgroup only.  One wave per 16 x 16
+// quarter of the tile; bound by the latency of its loads (all three matrices
+// are requested together) and of the two dependent products: 6.6 us a launch,
+// against 16 with the products on the vector units from LDS and U_P requested
+// after the first.
 __global__ __launch_bounds__(256) void bj_apply_k(double* A, double* V, int n, int nb, int k,
                                                   const double* Ug, const int* flags) {
   if (flags[0]) return;
@@ -233,54 +272,49 @@ __global__ __launch_bounds__(256) void bj_apply_k(double* A, double* V, int n, i
   if (blockIdx.x >= unsigned(is_a ? m * m : rows * m)) return;
   __shared__ double2 X[BJ2][BJ2 + 1];
   __shared__ double2 W[BJ2][BJ2 + 1];
-  __shared__ int ri[BJ2], ci[BJ2];
+  __shared__ double2 L[BJ2][BJ2 + 1];
   const int P = blockIdx.x / m, Sx = blockIdx.x % m;
-  if (tid < BJ2) {
-    ri[tid] = is_a ? bj_index(nb, k, P, tid) : P * BJ2 + tid;
-    ci[tid] = bj_index(nb, k, Sx, tid);
-  }
-  __syncthreads();
+  auto row_of = [&](int t) { return is_a ? bj_index(nb, k, P, t) : P * BJ2 + t; };
   double* M = is_a ? A : V;
   const double2* us = reinterpret_cast<const double2*>(Ug) + size_t(Sx) * BJ2 * BJ2;
-  for (int e = tid; e < BJ2 * BJ2; e += 256) {
-    const int i = e / BJ2, j = e % BJ2;
-    X[i][j] = (ri[i] < n && ci[j] < n) ? ld2(M, n, ri[i], ci[j]) : make_double2(0.0, 0.0);
-    W[i][j] = us[e];
-  }
-  __syncthreads();
-  // T = X U_S: four entries per thread, rows i0 + 8q of one column j (each
-  // entry of U_S read once for the four)
-  const int i0 = tid / BJ2, j = tid % BJ2;
-  double2 t[4];
+  const double2* up = reinterpret_cast<const double2*>(Ug) + size_t(is_a ? P : Sx) * BJ2 * BJ2;
+  {
+    const int j = tid % BJ2, c = bj_index(nb, k, Sx, j);
+    double2 x[4], u[4], l[4];
 #pragma unroll
-  for (int q = 0; q < 4; ++q) t[q] = make_double2(0.0, 0.0);
-#pragma unroll 8
-  for (int l = 0; l < BJ2; ++l) {
-    const double2 w = W[l][j];
+    for (int q = 0; q < 4; ++q) {
+      const int i = tid / BJ2 + 8 * q, r = row_of(i);
+      const bool in = r < n && c < n;
+      x[q] = ld2(M, n, in ? r : 0, in ? c : 0);
+      if (!in) x[q] = make_double2(0.0, 0.0);
+      u[q] = us[i * BJ2 + j];
+      l[q] = up[i * BJ2 + j];
+    }
 #pragma unroll
-    for (int q = 0; q < 4; ++q) t[q] = cadd2(t[q], cmul2(X[i0 + 8 * q][l], w));
-  }
-  if (is_a) {
-    // out = U_P^H T
-    __syncthreads();
-    const double2* up = reinterpret_cast<const double2*>(Ug) + size_t(P) * BJ2 * BJ2;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) X[i0 + 8 * q][j] = t[q];
-    for (int e = tid; e < BJ2 * BJ2; e += 256) W[e / BJ2][e % BJ2] = up[e];
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < 4; ++q) t[q] = make_double2(0.0, 0.0);
-#pragma unroll 8
-    for (int l = 0; l < BJ2; ++l) {
-      const double2 x = X[l][j];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) t[q] = cadd2(t[q], cmul2(cconj2(W[l][i0 + 8 * q]), x));
+    for (int q = 0; q < 4; ++q) {
+      const int i = tid / BJ2 + 8 * q;
+      X[i][j] = x[q];
+      W[i][j] = u[q];
+      L[i][j] = l[q];
     }
   }
+  __syncthreads();
+  const int i0 = ((tid >> 6) & 1) * 16, j0 = (tid >> 7) * 16;
+  const int mm = tid & 15, qq = (tid >> 4) & 3;
+  d4 re, im;
+  tile_product<false>(X, W, i0, j0, re, im);  // T = X U_S
+  if (is_a) {
+    __syncthreads();
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int i = i0 + 8 * q;
-    if (ri[i] < n && ci[j] < n) st2(M, n, ri[i], ci[j], t[q]);
+    for (int t = 0; t < 4; ++t) X[i0 + qq + 4 * t][j0 + mm] = make_double2(re[t], im[t]);
+    __syncthreads();
+    tile_product<true>(L, X, i0, j0, re, im);  // U_P^H T
+  }
+  const int c = bj_index(nb, k, Sx, j0 + mm);
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const int r = row_of(i0 + qq + 4 * t);
+    if (r < n && c < n) st2(M, n, r, c, make_double2(re[t], im[t]));
   }
 }
 
