@@ -76,123 +76,129 @@ __global__ void chol_init_k(CholJob j0, const CholJob* jobs) {
   if (blockIdx.x == 0 && threadIdx.x == 0) j.status[0] = 0;
 }
 
-// Factor the diagonal block at k0 (size kb <= KB) in LDS; write L_kk back and
+// Factor the diagonal block at k0 (size kb <= KB); write L_kk back and
 // inv(L_kk) into the job's dinv (KB x KB per block, row-major complex).
+//
+// Elimination on [A | I] without roots (A = L1 D L1^H): step k subtracts
+// m = a[r][k] / d_k times row k from the rows r > k, of A for the columns
+// c > k and of the inverse for c <= k, so that one value per (r, c) is live, in
+// a register: a[r][c] up to step c, (L1^{-1})[r][c] from then on.  LDS carries
+// column k of A and row k of the inverse only, one barrier a step.  Bound by the
+// latency of the kb dependent steps: 46 us a block with three barriers a step
+// and the inverse by one thread per column, now 29 (one formula for all entries
+// instead of the branches, and a shorter reciprocal: no change).
 __global__ __launch_bounds__(256) void chol_diag_k(CholJob j0, const CholJob* jobs, int k0) {
-  __shared__ double a[KB][KB][2];
-  __shared__ double x[KB][KB][2];
-  __shared__ int bad;
+  __shared__ double2 col[2][KB], row[2][KB];
+  __shared__ double dd[KB];
   const CholJob j = chol_job(j0, jobs);
   const int n = j.n;
   if (k0 >= n || j.status[0] != 0) return;
-  double* const L = j.L;
-  double* const Dinv = j.dinv + size_t(k0 / KB) * KB * KB * 2;
+  double2* const L = reinterpret_cast<double2*>(j.L);
+  double2* const Dinv = reinterpret_cast<double2*>(j.dinv) + size_t(k0 / KB) * KB * KB;
   const int kb = (n - k0) < KB ? (n - k0) : KB;
-  const int t = threadIdx.x;
-  for (int e = t; e < KB * KB; e += 256) {
-    const int r = e / KB, c = e % KB;
-    const bool in = r < kb && c < kb;
-    a[r][c][0] = in ? L[(size_t(k0 + r) * n + k0 + c) * 2] : 0.0;
-    a[r][c][1] = in ? L[(size_t(k0 + r) * n + k0 + c) * 2 + 1] : 0.0;
+  const int t = threadIdx.x, c = t % KB, r0 = t / KB;  // entries (r0 + 8 i, c)
+  double2 v[4], l[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int r = r0 + 8 * i;
+    const bool in = r < kb && c <= r;
+    v[i] = in ? L[size_t(k0 + r) * n + k0 + c] : make_double2(0.0, 0.0);
+    l[i] = make_double2(0.0, 0.0);
+    if (c == 0) col[0][r] = v[i];
   }
-  if (t == 0) bad = 0;
   __syncthreads();
-  // unblocked right-looking factorisation of the lower triangle
   for (int k = 0; k < kb; ++k) {
-    if (t == 0) {
-      const double d = a[k][k][0];
-      if (!(d > 0.0)) bad = k0 + k + 1;
-      a[k][k][0] = d > 0.0 ? sqrt(d) : 1.0;
-      a[k][k][1] = 0.0;
+    const double2* const cl = col[k & 1];
+    const double d = cl[k].x;
+    if (!(d > 0.0)) {  // (the same for every thread)
+      if (t == 0) j.status[0] = k0 + k + 1;
+      return;
     }
-    __syncthreads();
-    if (bad) break;
-    const double dk = a[k][k][0];
-    for (int r = k + 1 + t; r < kb; r += 256) {
-      a[r][k][0] /= dk;
-      a[r][k][1] /= dk;
-    }
-    __syncthreads();
-    for (int e = t; e < KB * KB; e += 256) {
-      const int r = e / KB, c = e % KB;
-      if (r > k && c > k && c <= r && r < kb) {
-        // a[r][c] -= a[r][k] * conj(a[c][k])
-        const double ar = a[r][k][0], ai = a[r][k][1], br = a[c][k][0], bi = a[c][k][1];
-        a[r][c][0] -= ar * br + ai * bi;
-        a[r][c][1] -= ai * br - ar * bi;
-      }
-    }
-    __syncthreads();
-  }
-  if (bad) {
-    if (t == 0) j.status[0] = bad;
-    return;
-  }
-  // inverse of the lower factor: column c by forward substitution (thread c)
-  if (t < KB) {
-    const int c = t;
-    for (int r = 0; r < KB; ++r) x[r][c][0] = x[r][c][1] = 0.0;
-    if (c < kb) {
-      x[c][c][0] = 1.0 / a[c][c][0];
-      for (int r = c + 1; r < kb; ++r) {
-        double sr = 0.0, si = 0.0;
-        for (int p = c; p < r; ++p) {
-          sr += a[r][p][0] * x[p][c][0] - a[r][p][1] * x[p][c][1];
-          si += a[r][p][0] * x[p][c][1] + a[r][p][1] * x[p][c][0];
+    const double inv = 1.0 / d;
+    const double2 cc = cl[c], rw = row[k & 1][c];
+    if (t == 0) dd[k] = d;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = r0 + 8 * i;
+      if (r > k) {
+        const double2 a = cl[r], m = make_double2(a.x * inv, a.y * inv);
+        if (c > k) {  // a[r][c] -= m conj(a[c][k])
+          if (c <= r) {
+            v[i].x -= m.x * cc.x + m.y * cc.y;
+            v[i].y -= m.y * cc.x - m.x * cc.y;
+          }
+        } else if (c == k) {
+          l[i] = v[i];
+          v[i] = make_double2(-m.x, -m.y);
+        } else {
+          v[i].x -= m.x * rw.x - m.y * rw.y;
+          v[i].y -= m.x * rw.y + m.y * rw.x;
         }
-        x[r][c][0] = -sr / a[r][r][0];
-        x[r][c][1] = -si / a[r][r][0];
+      } else if (r == k && c == k) {
+        v[i] = make_double2(1.0, 0.0);
       }
+      if (c == k + 1 && r > k) col[(k + 1) & 1][r] = v[i];
+      if (r == k + 1 && c <= k) row[(k + 1) & 1][c] = v[i];
     }
+    __syncthreads();
   }
-  __syncthreads();
-  for (int e = t; e < KB * KB; e += 256) {
-    const int r = e / KB, c = e % KB;
-    Dinv[2 * e] = x[r][c][0];
-    Dinv[2 * e + 1] = x[r][c][1];
-    if (r < kb && c < kb) {
-      const bool low = c <= r;
-      L[(size_t(k0 + r) * n + k0 + c) * 2] = low ? a[r][c][0] : 0.0;
-      L[(size_t(k0 + r) * n + k0 + c) * 2 + 1] = low ? a[r][c][1] : 0.0;
-    }
+  const double sc = c < kb ? sqrt(dd[c]) : 1.0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int r = r0 + 8 * i;
+    const bool low = r < kb && c <= r;
+    const double sr = low ? sqrt(dd[r]) : 1.0;
+    Dinv[r * KB + c] = low ? make_double2(v[i].x / sr, v[i].y / sr) : make_double2(0.0, 0.0);
+    if (r < kb && c < kb)
+      L[size_t(k0 + r) * n + k0 + c] = !low ? make_double2(0.0, 0.0) : r == c ? make_double2(sc, 0.0)
+                                                                            : make_double2(l[i].x / sc, l[i].y / sc);
   }
 }
 
 // Panel: for rows i >= k0 + kb, L[i][k0:k0+kb] = A[i][k0:k0+kb] * inv(L_kk)^H,
 // and zero the block above the diagonal (L[k0..][i] for the same columns).
-// inv(L_kk) is staged in LDS (every lane then reads the same entry).
-__global__ __launch_bounds__(64) void chol_panel_k(CholJob j0, const CholJob* jobs, int k0) {
-  __shared__ double dl[KB * KB * 2];
+// A workgroup takes 32 rows; both factors in LDS, one wave per 16 x 16 quarter
+// of the product on v_mfma_f64_16x16x4f64 (lane l: left row and right column
+// l % 16, k = l / 16; result rows l / 16 + 4 t, column l % 16).  One thread per
+// row with its row in (spilled) registers took 56 us a panel, this 4.7.
+typedef double d4 __attribute__((ext_vector_type(4)));
+__global__ __launch_bounds__(256) void chol_panel_k(CholJob j0, const CholJob* jobs, int k0) {
+  __shared__ double2 a[KB][KB + 1], x[KB][KB + 1];
   const CholJob j = chol_job(j0, jobs);
   const int n = j.n;
   if (k0 >= n || j.status[0] != 0) return;
   const int kb = (n - k0) < KB ? (n - k0) : KB;
-  if (k0 + kb + int(blockIdx.x) * 64 >= n) return;  // no row of this job in the workgroup
-  const double* const Dinv = j.dinv + size_t(k0 / KB) * KB * KB * 2;
-  for (int e = threadIdx.x; e < KB * KB * 2; e += 64) dl[e] = Dinv[e];
-  __syncthreads();
-  double* const L = j.L;
-  const int i = k0 + kb + blockIdx.x * 64 + threadIdx.x;
-  if (i >= n) return;
-  double ar[KB], ai[KB];
+  const int base = k0 + kb + int(blockIdx.x) * KB;
+  if (base >= n) return;  // no row of this job in the workgroup
+  const double2* const Dinv = reinterpret_cast<const double2*>(j.dinv) + size_t(k0 / KB) * KB * KB;
+  double2* const L = reinterpret_cast<double2*>(j.L);
+  const int t = threadIdx.x;
 #pragma unroll
-  for (int c = 0; c < KB; ++c) {
-    ar[c] = c < kb ? L[(size_t(i) * n + k0 + c) * 2] : 0.0;
-    ai[c] = c < kb ? L[(size_t(i) * n + k0 + c) * 2 + 1] : 0.0;
+  for (int i = 0; i < 4; ++i) {
+    const int r = t / KB + 8 * i, c = t % KB;
+    a[r][c] = base + r < n && c < kb ? L[size_t(base + r) * n + k0 + c] : make_double2(0.0, 0.0);
+    x[r][c] = Dinv[r * KB + c];
   }
-  // out[c] = sum_p a[p] * conj(Dinv[c][p])
-  for (int c = 0; c < kb; ++c) {
-    double sr = 0.0, si = 0.0;
-    for (int p = 0; p <= c; ++p) {
-      const double dr = dl[(c * KB + p) * 2], di = dl[(c * KB + p) * 2 + 1];
-      sr += ar[p] * dr + ai[p] * di;
-      si += ai[p] * dr - ar[p] * di;
-    }
-    L[(size_t(i) * n + k0 + c) * 2] = sr;
-    L[(size_t(i) * n + k0 + c) * 2 + 1] = si;
-    // strict upper triangle of the final factor: zero L[k0 + c][i]
-    L[(size_t(k0 + c) * n + i) * 2] = 0.0;
-    L[(size_t(k0 + c) * n + i) * 2 + 1] = 0.0;
+  __syncthreads();
+  const int i0 = ((t >> 6) & 1) * 16, c0 = (t >> 7) * 16, m = t & 15, q = (t >> 4) & 3;
+  d4 re = {0, 0, 0, 0}, im = {0, 0, 0, 0};
+#pragma unroll
+  for (int k = 0; k < KB; k += 4) {  // sum_p a[i][p] conj(x[c][p])
+    const double2 u = a[i0 + m][k + q], w = x[c0 + m][k + q];
+    re = __builtin_amdgcn_mfma_f64_16x16x4f64(u.x, w.x, re, 0, 0, 0);
+    im = __builtin_amdgcn_mfma_f64_16x16x4f64(u.y, w.x, im, 0, 0, 0);
+    re = __builtin_amdgcn_mfma_f64_16x16x4f64(u.y, w.y, re, 0, 0, 0);
+    im = __builtin_amdgcn_mfma_f64_16x16x4f64(-u.x, w.y, im, 0, 0, 0);
+  }
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    const int i = base + i0 + q + 4 * s, c = c0 + m;
+    if (i < n && c < kb) L[size_t(i) * n + k0 + c] = make_double2(re[s], im[s]);
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {  // strict upper triangle of the final factor
+    const int c = t / KB + 8 * i, r = base + t % KB;
+    if (c < kb && r < n) L[size_t(k0 + c) * n + r] = make_double2(0.0, 0.0);
   }
 }
 
@@ -254,92 +260,89 @@ __global__ void tri_zero_k(CholJob j0, const CholJob* jobs) {
     j.U[e] = 0.0;
 }
 
+//
+// The products run on v_mfma_f64_16x16x4f64, one wave per 16 x 16 quarter (lane
+// layout as in the panel), the next block pair in flight meanwhile; 200 columns: 10.8 us a
+// wavefront, with the products on the vector units from LDS 20.
 __global__ __launch_bounds__(256) void tri_wave_k(CholJob j0, const CholJob* jobs, int d) {
-  __shared__ double ls[KB][KB + 1][2];
-  __shared__ double xs[KB][KB + 1][2];
+  __shared__ double2 ls[KB][KB + 1], xs[KB][KB + 1];
   const CholJob jb = chol_job(j0, jobs);
   if (jb.status[0] != 0) return;
   const int n = jb.n;
-  const double* const L = jb.L;
-  const double* const Dinv = jb.dinv;
-  double* const U = jb.U;
+  const double2* const L = reinterpret_cast<const double2*>(jb.L);
+  const double2* const Dinv = reinterpret_cast<const double2*>(jb.dinv);
+  double2* const U = reinterpret_cast<double2*>(jb.U);
   const int nb = (n + KB - 1) / KB;
   const int c = blockIdx.x, r = c + d;
   if (r >= nb) return;
   const int c0 = c * KB, r0 = r * KB;
   const int rb = (n - r0) < KB ? (n - r0) : KB;   // only the last block row can be short
-  const int t = threadIdx.x;
-  const int row = t / 8, col = t % 8;              // outputs (row, col + 8k), k < 4
-  double ar[4] = {0.0, 0.0, 0.0, 0.0}, ai[4] = {0.0, 0.0, 0.0, 0.0};
-  const double* dr = Dinv + size_t(r) * KB * KB * 2;
+  const int t = threadIdx.x, hi = t / KB, lo = t % KB;
+  const double2* const dr = Dinv + size_t(r) * KB * KB;
   if (d == 0) {
-    for (int k = 0; k < 4; ++k) {
-      ar[k] = dr[(row * KB + col + 8 * k) * 2];
-      ai[k] = dr[(row * KB + col + 8 * k) * 2 + 1];
+    for (int i = 0; i < 4; ++i) {
+      const int jj = hi + 8 * i;
+      const double2 x = dr[lo * KB + jj];
+      if (lo < rb && c0 + jj < n) U[size_t(c0 + jj) * n + r0 + lo] = make_double2(x.x, -x.y);
     }
-  } else {
-    // T = sum_p L_rp X_pc
-    for (int p = c; p < r; ++p) {
-      const int p0 = p * KB;
-      const double* dp = Dinv + size_t(p) * KB * KB * 2;
-      for (int e = t; e < KB * KB; e += 256) {
-        const int i = e / KB, q = e % KB;
-        const bool in = i < rb;
-        ls[i][q][0] = in ? L[(size_t(r0 + i) * n + p0 + q) * 2] : 0.0;
-        ls[i][q][1] = in ? L[(size_t(r0 + i) * n + p0 + q) * 2 + 1] : 0.0;
-        // X_pc[q][j] with j = e / KB, q = e % KB (contiguous reads of U row c0 + j)
-        const int jj = e / KB, qq = e % KB;
-        if (p == c) {
-          xs[qq][jj][0] = dp[(qq * KB + jj) * 2];
-          xs[qq][jj][1] = dp[(qq * KB + jj) * 2 + 1];
-        } else {
-          xs[qq][jj][0] = U[(size_t(c0 + jj) * n + p0 + qq) * 2];
-          xs[qq][jj][1] = -U[(size_t(c0 + jj) * n + p0 + qq) * 2 + 1];
-        }
-      }
-      __syncthreads();
-#pragma unroll 4
-      for (int q = 0; q < KB; ++q) {
-        const double lr = ls[row][q][0], li = ls[row][q][1];
+    return;
+  }
+  double2 lv[4], xv[4];
+  auto load = [&](int p) {  // L_rp by rows, X_pc by rows of U (or of the diagonal inverse)
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const double xr = xs[q][col + 8 * k][0], xi = xs[q][col + 8 * k][1];
-          ar[k] += lr * xr - li * xi;
-          ai[k] += lr * xi + li * xr;
-        }
+    for (int i = 0; i < 4; ++i) {
+      const int k = hi + 8 * i;
+      lv[i] = k < rb ? L[size_t(r0 + k) * n + p * KB + lo] : make_double2(0.0, 0.0);
+      if (p == c) {
+        xv[i] = Dinv[size_t(p) * KB * KB + lo * KB + k];
+      } else {
+        const double2 u = U[size_t(c0 + k) * n + p * KB + lo];
+        xv[i] = make_double2(u.x, -u.y);
       }
-      __syncthreads();
     }
-    // X_rc = -inv(L_rr) T
-    for (int k = 0; k < 4; ++k) {
-      xs[row][col + 8 * k][0] = ar[k];
-      xs[row][col + 8 * k][1] = ai[k];
-    }
-    for (int e = t; e < KB * KB; e += 256) {
-      const int i = e / KB, q = e % KB;
-      ls[i][q][0] = dr[e * 2];
-      ls[i][q][1] = dr[e * 2 + 1];
+  };
+  const int i0 = ((t >> 6) & 1) * 16, c1 = (t >> 7) * 16, m = t & 15, q = (t >> 4) & 3;
+  // T = sum_p L_rp X_pc
+  d4 re = {0, 0, 0, 0}, im = {0, 0, 0, 0};
+  load(c);
+  for (int p = c; p < r; ++p) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      ls[hi + 8 * i][lo] = lv[i];
+      xs[lo][hi + 8 * i] = xv[i];
     }
     __syncthreads();
-    for (int k = 0; k < 4; ++k) ar[k] = ai[k] = 0.0;
-#pragma unroll 4
-    for (int q = 0; q < KB; ++q) {
-      const double lr = ls[row][q][0], li = ls[row][q][1];
+    if (p + 1 < r) load(p + 1);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const double xr = xs[q][col + 8 * k][0], xi = xs[q][col + 8 * k][1];
-        ar[k] -= lr * xr - li * xi;
-        ai[k] -= lr * xi + li * xr;
-      }
+    for (int k = 0; k < KB; k += 4) {
+      const double2 a = ls[i0 + m][k + q], b = xs[k + q][c1 + m];
+      re = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.x, re, 0, 0, 0);
+      im = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.y, im, 0, 0, 0);
+      re = __builtin_amdgcn_mfma_f64_16x16x4f64(-a.y, b.y, re, 0, 0, 0);
+      im = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, b.x, im, 0, 0, 0);
     }
+    __syncthreads();
   }
-  if (row < rb) {
-    for (int k = 0; k < 4; ++k) {
-      const int jc = col + 8 * k;
-      if (c0 + jc >= n) continue;
-      U[(size_t(c0 + jc) * n + r0 + row) * 2] = ar[k];
-      U[(size_t(c0 + jc) * n + r0 + row) * 2 + 1] = -ai[k];
-    }
+  // X_rc = -inv(L_rr) T, as its transpose T^T inv(L_rr)^T: rows of U
+#pragma unroll
+  for (int s = 0; s < 4; ++s) xs[i0 + q + 4 * s][c1 + m] = make_double2(re[s], im[s]);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) ls[hi + 8 * i][lo] = dr[(hi + 8 * i) * KB + lo];
+  __syncthreads();
+  re = d4{0, 0, 0, 0};
+  im = d4{0, 0, 0, 0};
+#pragma unroll
+  for (int k = 0; k < KB; k += 4) {
+    const double2 a = xs[k + q][c1 + m], b = ls[i0 + m][k + q];
+    re = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.x, re, 0, 0, 0);
+    im = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.y, im, 0, 0, 0);
+    re = __builtin_amdgcn_mfma_f64_16x16x4f64(-a.y, b.y, re, 0, 0, 0);
+    im = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, b.x, im, 0, 0, 0);
+  }
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    const int jc = c1 + q + 4 * s, i = i0 + m;
+    if (i < rb && c0 + jc < n) U[size_t(c0 + jc) * n + r0 + i] = make_double2(-re[s], im[s]);
   }
 }
 
@@ -354,8 +357,8 @@ hipError_t chol_steps(const CholJob& j0, const CholJob* jobs, int njobs, int n, 
     const int kb = (n - k0) < KB ? (n - k0) : KB;
     const int rest = n - k0 - kb;
     if (rest > 0) {
-      hipLaunchKernelGGL(chol_panel_k, dim3((rest + 63) / 64, 1, njobs), dim3(64), 0, s, j0, jobs,
-                         k0);
+      hipLaunchKernelGGL(chol_panel_k, dim3((rest + KB - 1) / KB, 1, njobs), dim3(256), 0, s, j0,
+                         jobs, k0);
       const int nt = (rest + KB - 1) / KB;
       hipLaunchKernelGGL(chol_update_k, dim3(nt, nt, njobs), dim3(256), 0, s, j0, jobs, k0);
     }
