@@ -208,7 +208,7 @@ hipError_t run_fine(const int* n, int norb, const void* phi_v, const double* occ
                        n1 * IB * sizeof(C<T>) + n1 * sizeof(T), s, n1, inner, P, Y, h + hstride, n2, b);
     // z, odd planes: O = H^T Y, one contraction over the n2 planes for the whole
     // chunk (each plane row holds the b orbitals' planes side by side; matrix cores)
-    e = launch_gemm_xc(sizeof(T) == 4, n2, n2, size_t(b) * plane, Y, H, n2, 1.0, O, false, s);
+    e = launch_gemm_xc_real(sizeof(T) == 4, n2, n2, size_t(b) * plane, Y, H, n2, O, s);
     if (e != hipSuccess) break;
     const size_t half = (size_t(2) * n2 * plane) / 2;
     hipLaunchKernelGGL(density_acc_k<T>, dim3(unsigned((half + 255) / 256)), dim3(256), 0, s, n2, plane, b, Y, O,

@@ -238,6 +238,10 @@ hipError_t launch_ptim_xc(bool fp32, int na, int nb, size_t ng, const void* X, c
 //   complex64 rounded from the FP64 matrix), Z: [nb][ng]; upper: C upper triangular
 hipError_t launch_gemm_xc(bool fp32, int na, int nb, size_t ng, const void* X, const void* C,
                           int ldc, double alpha, void* Z, bool upper, hipStream_t s);
+// The same with alpha = 1 for a C whose imaginary parts are zero (they are not
+// multiplied).
+hipError_t launch_gemm_xc_real(bool fp32, int na, int nb, size_t ng, const void* X, const void* C, int ldc,
+                               void* Z, hipStream_t s);
 
 // chol_kernels.hip: FP64 Hermitian tools on an n x n complex128 matrix (row-major)
 hipError_t launch_hermitize(double* M, int n, hipStream_t s);
