@@ -113,14 +113,20 @@ bool misaligned(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) !=
 size_t elem_bytes(px_precision p) { return p == PX_PREC_FP32 ? 8 : 16; }
 
 void default_tuning(const px_cell* cell, px_precision prec, int* ic, int* jc) {
-  // ic output orbitals x jc density orbitals per chunk.  Passes 1 and 3 launch
-  // ic workgroups per tile and loop over jc pairs each; larger chunks amortise
-  // the phi tiles and the output read-modify-write.  The pair buffer holds
-  // ic*jc slabs.
-  (void)cell;
+  // ic output orbitals x jc density orbitals per chunk; the Hermitian-pair mode
+  // takes square blocks of ic.  Larger chunks amortise the orbital tiles, the
+  // output read-modify-write and the launches; the pair buffer holds ic*jc
+  // slabs.  The block is the largest whose buffer stays near that of 32 x 32
+  // slabs at 96^3 (14.5 GB in FP64; both forms take the same block).  FP32 builds,
+  // ms, block 32 -> the rule's: 24^3 x 100 1.51 -> 1.21, 32^3 x 128 3.49 -> 3.04,
+  // 48^3 x 200 20.5 -> 19.3, 72^3 x 300 158.4 -> 154.9; at 96^3 x 203 blocks of 64
+  // would give 171 -> 168 for four times the memory.
+  constexpr double kPairBytes = 16.4e9;
   (void)prec;
   *ic = 32;
-  *jc = 16;
+  for (const int b : {48, 64, 96, 128})
+    if (double(b) * b * double(ngrid(cell)) * 16.0 <= kPairBytes) *ic = b;
+  *jc = *ic / 2;
 }
 
 void tuning_for(const px_context* c, const px_cell* cell, px_precision prec, int* ic, int* jc,
@@ -1227,7 +1233,11 @@ struct BatchPlan {
   std::vector<TailGroup> groups;
 };
 
+// Pair block of an instance in the batched form: the tuned one, else 32, whatever
+// the grid (a wave holds the chunks of many instances; with the single
+// form's larger default a batch of 12 took 75.1 ms instead of 72.7).
 int block_for(const px_context* c, const px_cell* cell, px_precision prec) {
+  if (!c->tuning.count({cell->n[0], cell->n[1], cell->n[2], int(prec)})) return 32;
   int ic, jc;
   tuning_for(c, cell, prec, &ic, &jc);
   return ic > jc ? ic : jc;
