@@ -36,11 +36,13 @@ __global__ __launch_bounds__(256) void pass4_rows(ChunkArgs a0, const ChunkArgs*
   const T* t = reinterpret_cast<const T*>(a.t) + 2 * (size_t(ii) * a.jc * ng + e);
   T* const o = reinterpret_cast<T*>(a.out) + 2 * (size_t(a.i0 + ii) * ng + e);
   // a triangular block's output was written by its pass 3 already
+  V prev = V{};
+  if (!a.first || a.tri) prev = *(const PX_GLOBAL V*)o;
+  // the chunk's sum first: one rounding at the output's magnitude per chunk
   V acc = V{};
-  if (!a.first || a.tri) acc = *(const PX_GLOBAL V*)o;
 #pragma unroll 8
-  for (int j = 0; j < jend; j += gj) acc -= __builtin_nontemporal_load((const PX_GLOBAL V*)(t + 2 * size_t(j) * ng));
-  *(PX_GLOBAL V*)o = acc;
+  for (int j = 0; j < jend; j += gj) acc += __builtin_nontemporal_load((const PX_GLOBAL V*)(t + 2 * size_t(j) * ng));
+  *(PX_GLOBAL V*)o = prev - acc;
 }
 
 hipError_t launch_pass4(bool fp32, const ChunkArgs& a, const ChunkDims& d, int gj, size_t ng,
