@@ -166,7 +166,7 @@ __device__ __forceinline__ double skip_factor(int n) { return 64.0 * DBL_EPSILON
 // (one workgroup per pair): U_P (32 x 32, row-major) into Ug[P].  Bound by the
 // chain rotation -> S -> rotation of the inner rounds (few workgroups, no
 // bandwidth): per round one phase of S on all four waves, and one in which wave
-// 0 forms the next rotations while the others apply this round's to U.  A
+// 0 forms the next rotations while the others apply the current ones to U.  A
 // launch took 66 us with both updates after the rotations and 2 x 2 complex
 // matrix products, now 30 (twelve waves, U beside S: 31; what is left is mostly
 // the LDS traffic of the rotations, S and U).

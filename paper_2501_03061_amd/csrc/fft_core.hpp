@@ -10,7 +10,7 @@
 // so that the result comes out in natural order with no bit reversal.  The
 // last stage (NS = N/R) writes positions j + r*N/R, the same set the first
 // stage of another transform with the same radix reads, which lets the
-// forward and inverse z transforms of the kernel-multiply pass meet in
+// forward and inverse x transforms of the kernel-multiply pass meet in
 // registers.
 //
 // Forward transforms use exp(-i...), inverse exp(+i...), both unnormalised.
@@ -245,8 +245,7 @@ PX_PLAN(120, 2, 10, 12, 1)
 #undef PX_PLAN
 
 // Radix and span of stage S of the plan's radix sequence (INV = false) or of
-// the reversed sequence (INV = true; the inverse transforms use it, and so
-// does the forward x transform of the pair product, see pass 1).
+// the reversed sequence (INV = true, the order of the inverse transforms).
 template <int N, int S, bool INV> struct StageOf {
   static constexpr int nst = Plan<N>::nst;
   static constexpr int idx = INV ? (nst - 1 - S) : S;

@@ -218,8 +218,8 @@ def summarize_hbm(fetch, write, copy_fetch, copy_write, out, commands, workload)
         lines.append(f"| `{name}` | {len(fb[k])} | {f:,.0f} | {w:,.0f} | {rb / 1e9:.3f} | "
                      f"{wbts / 1e9:.3f} | {(rb + wbts) / 1e9:.3f} |")
         if "float" in k and _short(k).startswith("pass"):
-            # instantiations of one pass (e.g. pass 3 with and without the kept
-            # v_ij) merge into a dispatch-weighted average per launch
+            # instantiations of one pass (e.g. pass 3 with and without the
+            # transposed sums) merge into a dispatch-weighted average per launch
             d = len(fb[k])
             prev = kernels.get(_short(k))
             if prev:
