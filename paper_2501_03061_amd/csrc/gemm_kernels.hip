@@ -109,7 +109,17 @@ template <class F> __device__ __forceinline__ void by_tiles(int ni, int nj, F&& 
 // registers with masks; 200 x 200 x 48^3 FP64 1.82 -> 1.34 ms, of which the
 // 16-wide tiles past 200 that are no longer computed are a third.
 struct XhyStage { static constexpr int ROW = 256, BYTES = 128 * ROW; };  // X rows, then Y rows
-template <typename T>
+// WIDE: lane offsets of 64 bits, formed at every transfer.  The 32-bit offsets
+// (kept in registers, added to a scalar base by the transfer itself) reach three
+// rows of N_g and a chunk with its last stage rounded up: N_g below about 89.5
+// million in FP64, 179 million in FP32.
+constexpr bool xhy_wide(size_t ng, size_t kchunk, size_t sz) {
+  return 3 * ng * sz + kchunk * sz + 2 * XhyStage::ROW > (size_t(1) << 32);
+}
+static_assert(!xhy_wide(size_t(447) * 447 * 447, 1 << 18, 16) && xhy_wide(size_t(448) * 448 * 448, 0, 16), "FP64 edge");
+static_assert(!xhy_wide(size_t(562) * 562 * 562, 1 << 19, 8) && xhy_wide(size_t(564) * 564 * 564, 0, 8), "FP32 edge");
+static_assert(xhy_wide(size_t(67200000), 67200000, 16), "the whole sum in one chunk");
+template <typename T, bool WIDE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void gemm_xhy_k(int na, int nb, size_t ng, const cpx<T>* X,
                                                   const cpx<T>* Y, double* part, size_t kchunk,
                                                   int tri) {
@@ -135,24 +145,31 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void g
   const int q = lane >> 4, m = lane & 15;
 
   // transfers: waves 0 and 1 move X's rows, 2 and 3 Y's, four rows each time
-  // (a wave-uniform row and a 32-bit lane offset of up to three rows more)
+  // (a wave-uniform row and a lane offset of up to three rows more)
+  using Off = typename std::conditional<WIDE, size_t, unsigned>::type;
   const bool isx = w < 2;
   const int row0 = (isx ? ta : tb) * 64 + (w & 1) * 32, rlim = (isx ? na : nb) - 1;
   const char* const src = reinterpret_cast<const char*>(isx ? X : Y) + r_begin * SZ;
-  unsigned off[8];
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
+  auto row_off = [&](int i, int ql) {
     const int r = row0 + 4 * i < rlim ? row0 + 4 * i : rlim;
-    off[i] = unsigned(r + q < rlim ? q : rlim - r) * unsigned(ng * SZ);
+    return Off(r + ql < rlim ? ql : rlim - r) * Off(ng * SZ);
+  };
+  unsigned off[WIDE ? 1 : 8];
+  if constexpr (!WIDE) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) off[i] = row_off(i, q);
   }
-  const unsigned last = unsigned((r_end - r_begin) * SZ) - 16;  // the chunk's last piece
+  const Off last = Off((r_end - r_begin) * SZ) - 16;  // the chunk's last piece
   auto stage_in = [&](int k, char* st) {
     char* const dst = st + w * 32 * XhyStage::ROW;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const int r = row0 + 4 * i < rlim ? row0 + 4 * i : rlim;
-      const unsigned c = unsigned(k) * XhyStage::ROW + unsigned((m ^ ((4 * i + q) & 7)) * 16);
-      dma16(src + size_t(r) * ng * SZ + (off[i] + (c < last ? c : last)), dst + i * 4 * XhyStage::ROW);
+      const Off c = Off(k) * XhyStage::ROW + Off((m ^ ((4 * i + q) & 7)) * 16);
+      int ql = q;
+      if constexpr (WIDE) __asm__("" : "+v"(ql));  // (not kept over the loop: spills)
+      const Off o = WIDE ? row_off(i, ql) : Off(off[WIDE ? 0 : i]);
+      dma16(src + size_t(r) * ng * SZ + (o + (c < last ? c : last)), dst + i * 4 * XhyStage::ROW);
     }
   };
 
@@ -388,14 +405,16 @@ static hipError_t xhy_launch(bool fp32, int na, int nb, size_t ng, const void* X
   const int ta = (na + 63) / 64, tb = (nb + 63) / 64;
   const int tri = herm ? ta : 0;
   dim3 grid(herm ? ta * (ta + 1) / 2 : ta, herm ? 1 : tb, nsplit);
-  if (fp32)
-    hipLaunchKernelGGL(gemm_xhy_k<float>, grid, dim3(256), 0, s, na, nb, ng,
-                       static_cast<const cpx<float>*>(X), static_cast<const cpx<float>*>(Y), part,
-                       kchunk, tri);
-  else
-    hipLaunchKernelGGL(gemm_xhy_k<double>, grid, dim3(256), 0, s, na, nb, ng,
-                       static_cast<const cpx<double>*>(X), static_cast<const cpx<double>*>(Y),
-                       part, kchunk, tri);
+  auto run = [&](auto t, auto wide) {
+    using T = decltype(t);
+    hipLaunchKernelGGL((gemm_xhy_k<T, decltype(wide)::value>), grid, dim3(256), 0, s, na, nb, ng,
+                       static_cast<const cpx<T>*>(X), static_cast<const cpx<T>*>(Y), part, kchunk, tri);
+  };
+  const bool wide = xhy_wide(ng, kchunk, fp32 ? 8 : 16);
+  if (fp32 && wide) run(float{}, std::true_type{});
+  else if (fp32) run(float{}, std::false_type{});
+  else if (wide) run(double{}, std::true_type{});
+  else run(double{}, std::false_type{});
   const size_t n = size_t(na) * nb;
   const bool many = nsplit >= 32;
   const size_t blocks = many ? (n + 15) / 16 : (n + 255) / 256;
@@ -463,7 +482,13 @@ template <typename T> struct Update {
 };
 // REAL: C has no imaginary part, two products instead of Gauss's three (the z
 // interpolation of the fine density, 16 orbitals, 72^3 FP64: 344 -> 262 us).
-template <typename T, bool UPD, bool REAL>
+// WIDE: the lane offset of X in 64 bits (FP32, where a transfer spans two rows,
+// from about 537 million N_g; an FP64 transfer stays within one).
+template <typename T> constexpr bool xc_wide(size_t ng) {
+  return sizeof(T) == 4 && (ng + 128) * sizeof(cpx<T>) > (size_t(1) << 32);
+}
+static_assert(!xc_wide<float>(size_t(812) * 812 * 812) && xc_wide<float>(size_t(1) << 29), "FP32 edge");
+template <typename T, bool UPD, bool REAL, bool WIDE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 3 : 2))) void gemm_xc_k(int na, int nb, size_t ng, const cpx<T>* X,
                                                  const T* C, int ldc, double alpha,
                                                  cpx<T>* Z, int upper, Update<T> u) {
@@ -496,7 +521,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
   // X: each transfer of a wave moves 1 KiB (two rows of complex64, one of
   // complex128); rows past a_end repeat the last, values past N_g the last piece
   constexpr int LPR = S::ROW / 16, RPT = 64 / LPR, NX = S::BYTES / 4096;
-  // (a wave-uniform row and a 32-bit lane offset of at most one row more)
+  // (a wave-uniform row and a lane offset of at most one row more)
+  using Off = typename std::conditional<WIDE, size_t, unsigned>::type;
   const int xrow = lane / LPR;
   const unsigned rmax = unsigned(ng - rt * 64 < 64 ? ng - rt * 64 : 64) - 16 / SZ;
   const cpx<T>* const xt = X + rt * 64;
@@ -508,7 +534,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
       const int ar = a + xrow < a_end ? xrow : 0;
       // the entry that belongs at this lane's slot (its piece's first)
       const unsigned c = unsigned(SZ == 8 ? (((lane % LPR) * 16) ^ (((al + xrow) & 3) << 7)) / SZ : lane % LPR);
-      dma16(reinterpret_cast<const char*>(xt + size_t(a) * ng) + (unsigned(ar) * unsigned(ng) + (c < rmax ? c : rmax)) * unsigned(SZ),
+      dma16(reinterpret_cast<const char*>(xt + size_t(a) * ng) + (Off(ar) * Off(ng) + (c < rmax ? c : rmax)) * Off(SZ),
             st + (w * NX + i) * 1024);
     }
   };
@@ -649,9 +675,15 @@ static dim3 xc_grid(int nb, size_t ng) { return dim3(unsigned((ng + 63) / 64) * 
 template <typename T, bool REAL>
 static void xc_run(int na, int nb, size_t ng, const void* X, const void* C, int ldc, double alpha, void* Z, bool upper,
                    hipStream_t s) {
-  hipLaunchKernelGGL((gemm_xc_k<T, false, REAL>), xc_grid(nb, ng), dim3(256), 0, s, na, nb, ng,
-                     static_cast<const cpx<T>*>(X), static_cast<const T*>(C), ldc, alpha,
-                     static_cast<cpx<T>*>(Z), int(upper), Update<T>{});
+  auto run = [&](auto wide) {
+    hipLaunchKernelGGL((gemm_xc_k<T, false, REAL, decltype(wide)::value>), xc_grid(nb, ng), dim3(256), 0, s, na, nb, ng,
+                       static_cast<const cpx<T>*>(X), static_cast<const T*>(C), ldc, alpha,
+                       static_cast<cpx<T>*>(Z), int(upper), Update<T>{});
+  };
+  if constexpr (sizeof(T) == 4 && !REAL) {
+    if (xc_wide<T>(ng)) return run(std::true_type{});
+  }
+  run(std::false_type{});
 }
 
 hipError_t launch_gemm_xc(bool fp32, int na, int nb, size_t ng, const void* X, const void* C,
@@ -663,6 +695,7 @@ hipError_t launch_gemm_xc(bool fp32, int na, int nb, size_t ng, const void* X, c
 
 hipError_t launch_gemm_xc_real(bool fp32, int na, int nb, size_t ng, const void* X, const void* C, int ldc,
                                void* Z, hipStream_t s) {
+  if (fp32 && xc_wide<float>(ng)) return hipErrorInvalidValue;
   if (fp32) xc_run<float, true>(na, nb, ng, X, C, ldc, 1.0, Z, false, s);
   else xc_run<double, true>(na, nb, ng, X, C, ldc, 1.0, Z, false, s);
   return hipGetLastError();
@@ -697,9 +730,15 @@ static void ptim_xc(int na, int nb, size_t ng, const void* X, const void* C, int
   const Update<T> u = {static_cast<const cpx<T>*>(p.phi_n), static_cast<const cpx<T>*>(p.y),
                        static_cast<const cpx<T>*>(p.cur), static_cast<cpx<T>*>(p.nxt),
                        static_cast<cpx<T>*>(p.mid), p.c, p.partial};
-  hipLaunchKernelGGL((gemm_xc_k<T, true, false>), xc_grid(nb, ng), dim3(256), 0, s, na, nb, ng,
-                     static_cast<const cpx<T>*>(X), static_cast<const T*>(C), ldc, -1.0,
-                     static_cast<cpx<T>*>(nullptr), 0, u);
+  auto run = [&](auto wide) {
+    hipLaunchKernelGGL((gemm_xc_k<T, true, false, decltype(wide)::value>), xc_grid(nb, ng), dim3(256), 0, s, na, nb, ng,
+                       static_cast<const cpx<T>*>(X), static_cast<const T*>(C), ldc, -1.0,
+                       static_cast<cpx<T>*>(nullptr), 0, u);
+  };
+  if constexpr (sizeof(T) == 4) {
+    if (xc_wide<T>(ng)) return run(std::true_type{});
+  }
+  run(std::false_type{});
 }
 
 hipError_t launch_ptim_xc(bool fp32, int na, int nb, size_t ng, const void* X, const void* C, int ldc,
