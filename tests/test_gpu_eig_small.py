@@ -1,0 +1,41 @@
+"""px_sigma_diagonalize where a single rotation, or none, decides the result: 2 x 2
+blocks, entries at the rounding level and scales at which squares leave the range of
+FP64.  Residual |sigma Q - Q D| against the matrix's own rounding, computed in
+extended precision."""
+import numpy as np
+import pytest
+
+from _gpu import banner, to_dev, to_host
+
+pytestmark = pytest.mark.gpu
+
+EPS = np.finfo(np.float64).eps
+
+
+def _residual(ctx, a):
+    import torch
+    Q, d, st = ctx.px_sigma_diagonalize(to_dev(a))
+    torch.cuda.synchronize()
+    assert int(st.item()) == 0
+    al, Q = a.astype(np.clongdouble), to_host(Q).astype(np.clongdouble)
+    r = np.sqrt((np.abs(al @ Q - Q * to_host(d)) ** 2).sum() / (np.abs(al) ** 2).sum())
+    o = np.sqrt((np.abs(Q.conj().T @ Q - np.eye(len(a))) ** 2).sum())
+    return float(r), float(o), to_host(d)
+
+
+@pytest.mark.parametrize("ratio", [0.5, 0.1, 0.02])
+def test_one_rotation(px_ctx, ratio):
+    """2 x 2: after one rotation what is left are the roundings (half an eps each, random
+    signs) of about six dependent operations, sqrt(6) eps at the most with all of them
+    at their bound: 2.5 eps.  Roots and reciprocals of 4e-15 leave up to 3.4."""
+    banner(f"eig one rotation, off-diagonal {ratio}")
+    rng = np.random.default_rng(17)
+    res = []
+    for _ in range(32):
+        z = ratio * np.exp(2j * np.pi * rng.random())
+        a = np.array([[0.3 + rng.random(), z], [np.conj(z), 0.2 * rng.random()]])
+        r, o, _ = _residual(px_ctx, a)
+        res.append(r)
+        assert o < 4 * EPS
+    print(f"mean {np.mean(res) / EPS:.2f} eps, largest {np.max(res) / EPS:.2f} eps", flush=True)
+    assert np.max(res) < 2.5 * EPS
