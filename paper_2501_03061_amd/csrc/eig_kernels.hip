@@ -165,7 +165,10 @@ __device__ __forceinline__ double norm2(const int* flags) { return reinterpret_c
 // arbitrary, and every sweep mixed the noise anew (256 and 500 indices with
 // Fermi-Dirac eigenvalues or a projector: not converged after 40 sweeps before,
 // now in 15 to 20).  All entries at that level leave an off-diagonal norm of
-// 8 eps sqrt(n) ||A||_F, an eighth of the convergence bound.
+// 8 eps sqrt(n) ||A||_F, an eighth of the convergence bound.  From the second sweep
+// on only: an input's own entries at that level (the identity plus 1e-15) are
+// rotated once, as all others (with the skip from the first on, the eigenvalues of
+// such matrices were off by twice as much, 2 x 2 by five times).
 __device__ __forceinline__ double skip_factor(int n) { return 64.0 * DBL_EPSILON * DBL_EPSILON / double(n); }
 
 // One inner sweep on the 32 x 32 subproblem of each block pair of round k
@@ -177,7 +180,7 @@ __device__ __forceinline__ double skip_factor(int n) { return 64.0 * DBL_EPSILON
 // matrix products, now 30 (twelve waves, U beside S: 31; what is left is mostly
 // the LDS traffic of the rotations, S and U).
 __global__ __launch_bounds__(256) void bj_solve_k(const double* A, int n, int nb, int k, double* Ug,
-                                                  const int* flags) {
+                                                  const int* flags, int first) {
   if (flags[0]) return;
   __shared__ double2 S[BJ2][BJ2 + 1];
   __shared__ double2 U[BJ2][BJ2 + 1];
@@ -192,7 +195,7 @@ __global__ __launch_bounds__(256) void bj_solve_k(const double* A, int n, int nb
     U[i][j] = make_double2(i == j ? 1.0 : 0.0, 0.0);
   }
   __syncthreads();
-  const double skip2 = skip_factor(n) * norm2(flags);
+  const double skip2 = first ? -1.0 : skip_factor(n) * norm2(flags);
   auto next_rot = [&](int kk) {
     int p, q;
     round_pair(BJ2, kk, tid, p, q);
@@ -450,7 +453,7 @@ hipError_t launch_eig_hermitian(const double* sigma, int n, double* Q, double* d
     const int tiles = m * m > rows * m ? m * m : rows * m;
     for (int sweep = 0; sweep < max_sweeps; ++sweep) {
       for (int k = 0; k < nb - 1; ++k) {
-        hipLaunchKernelGGL(bj_solve_k, dim3(m), dim3(256), 0, s, A, n, nb, k, Ug, flags);
+        hipLaunchKernelGGL(bj_solve_k, dim3(m), dim3(256), 0, s, A, n, nb, k, Ug, flags, int(sweep == 0));
         hipLaunchKernelGGL(bj_apply_k, dim3(tiles, 2), dim3(256), 0, s, A, V, n, nb, k, Ug, flags);
       }
       hipLaunchKernelGGL(eig_norm_part_k, dim3(kConvBlocks), dim3(256), 0, s, A, n, part, flags);

@@ -39,3 +39,25 @@ def test_one_rotation(px_ctx, ratio):
         assert o < 4 * EPS
     print(f"mean {np.mean(res) / EPS:.2f} eps, largest {np.max(res) / EPS:.2f} eps", flush=True)
     assert np.max(res) < 2.5 * EPS
+
+
+@pytest.mark.parametrize("n", [2, 3, 8, 17, 33])
+def test_entries_at_rounding_level(px_ctx, n):
+    """The identity plus entries of 4.5 eps: within the convergence bound at the start,
+    so one sweep rotates every entry and ends it.  The first rotations are by large
+    angles (the diagonal entries are equal), and one sweep then leaves about half of the
+    off-diagonal norm; entries that are not rotated at all would stay in the residual
+    whole.  Bound half way between."""
+    banner(f"eig entries at the rounding level n={n}")
+    rng = np.random.default_rng(5)
+    res = []
+    for _ in range(16):
+        h = rng.standard_normal((n, n)) + 1j * rng.standard_normal((n, n))
+        a = np.eye(n) + 1e-15 * (h + h.conj().T) / 2
+        np.fill_diagonal(a, 1.0)
+        r, o, _ = _residual(px_ctx, a)
+        res.append(r)
+        assert o < 2 * n * EPS
+    left = 1e-15 * np.sqrt(n - 1) / EPS  # norm of the entries over that of the matrix
+    print(f"mean {np.mean(res) / EPS:.2f} eps, not rotated {left:.2f}", flush=True)
+    assert np.mean(res) < 0.75 * left
