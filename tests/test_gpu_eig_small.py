@@ -61,3 +61,15 @@ def test_entries_at_rounding_level(px_ctx, n):
     left = 1e-15 * np.sqrt(n - 1) / EPS  # norm of the entries over that of the matrix
     print(f"mean {np.mean(res) / EPS:.2f} eps, not rotated {left:.2f}", flush=True)
     assert np.mean(res) < 0.75 * left
+
+
+@pytest.mark.parametrize("scale", [1e160, 1e-165])
+def test_norm_outside_fp64(px_ctx, scale):
+    """2 x 2 whose squared norm is infinite or zero in FP64: the first sweep rotates it
+    all the same (residual as for any 2 x 2 matrix)."""
+    banner(f"eig norm outside FP64, scale {scale}")
+    a = np.array([[0.7, 0.3 - 0.2j], [0.3 + 0.2j, 0.1]]) * scale
+    r, o, d = _residual(px_ctx, a)
+    ev = np.abs(d / scale - np.linalg.eigvalsh(a / scale)).max()
+    print(f"res {r / EPS:.2f} eps, ev {ev / EPS:.2f} eps", flush=True)
+    assert r < 2.5 * EPS and o < 4 * EPS and ev < 4 * EPS
