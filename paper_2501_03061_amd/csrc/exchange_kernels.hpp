@@ -431,7 +431,7 @@ void pass2_xy(ChunkArgs a0, const ChunkArgs* tasks, int pq) {
       // G = 0 from the FP64 tile sums of pass 1, one wave, fixed order
       double s0 = 0.0, s1 = 0.0;
       const G0Part* g = a.g0 + size_t(p) * NTILE;
-      for (int i = tid & 63; i < NTILE; i += 64) {
+      for (int i = t & 63; i < NTILE; i += 64) {  // (t: with tid the addresses were kept, and spilled at 96^3)
         s0 += gld(&g[i].re);
         s1 += gld(&g[i].im);
       }
