@@ -4,11 +4,15 @@
 
 Every .hip translation unit is compiled with hipcc for gfx950 only; the pair
 pipeline is compiled once per grid (-DPX_S0, PX_S1, PX_S2) so the grids build in
-parallel.  Packed FP32 instructions are disabled for all device code.
+parallel.  Packed FP32 instructions are disabled for all device code.  A kernel
+that keeps registers in scratch memory fails the build: pass 3 of the pair pipeline
+has given wrong sums now and then in builds that spilled, for a cause that reading
+its assembly has not shown, and spills cost time everywhere.
 """
 from __future__ import annotations
 
 import os
+import re
 import subprocess
 import sys
 from concurrent.futures import ThreadPoolExecutor
@@ -47,14 +51,31 @@ def _units():
     return units
 
 
+def scratch_users(remarks: str) -> dict:
+    """Kernels with scratch memory (name -> bytes per lane) in the compiler's
+    kernel-resource-usage remarks."""
+    users, name = {}, None
+    for line in remarks.splitlines():
+        m = re.search(r"remark:\s+Function Name: (\S+)", line)
+        if m:
+            name = m.group(1)
+        m = re.search(r"remark:\s+ScratchSize \[bytes/lane\]: (\d+)", line)
+        if m and int(m.group(1)) > 0:
+            users[name] = int(m.group(1))
+    return users
+
+
 def _compile(unit):
     src, obj, extra = unit
-    cmd = [_hipcc(), "-x", "hip", "-c", os.path.join(HERE, src), "-o",
-           os.path.join(BUILD_DIR, obj)] + COMMON + DEVICE + extra
+    cmd = [_hipcc(), "-x", "hip", "-c", os.path.join(HERE, src), "-o", os.path.join(BUILD_DIR, obj)] + \
+        COMMON + DEVICE + ["-Rpass-analysis=kernel-resource-usage"] + extra
     r = subprocess.run(cmd, capture_output=True, text=True)
-    msgs = "\n".join(l for l in (r.stderr or "").splitlines()
-                     if "packed-fp32-ops" not in l)
-    return src, obj, r.returncode, msgs
+    err = r.stderr or ""
+    users = scratch_users(err)
+    # the remarks (with the two lines of source that follow some) are not messages
+    err = re.sub(r"(^In file included from .*\n)*^.*\[-Rpass-analysis=kernel-resource-usage\]\n(\s+\d* \|.*\n)*", "", err + "\n", flags=re.M)
+    msgs = "\n".join(l for l in err.splitlines() if "packed-fp32-ops" not in l)
+    return src, obj, r.returncode, msgs, users
 
 
 def build(jobs: int | None = None, verbose: bool = False) -> str:
@@ -64,11 +85,14 @@ def build(jobs: int | None = None, verbose: bool = False) -> str:
     with ThreadPoolExecutor(jobs) as ex:
         results = list(ex.map(_compile, units))
     failed = [r for r in results if r[2] != 0]
-    for src, obj, rc, msgs in results:
+    for src, obj, rc, msgs, _ in results:
         if msgs.strip() and (verbose or rc != 0):
             print(f"--- {src} -> {obj}\n{msgs}", file=sys.stderr)
     if failed:
-        raise RuntimeError("hipcc failed for: " + ", ".join(f"{s} ({o})" for s, o, _, _ in failed))
+        raise RuntimeError("hipcc failed for: " + ", ".join(f"{r[0]} ({r[1]})" for r in failed))
+    spills = [f"{name} ({size} bytes a lane, {r[1]})" for r in results for name, size in r[4].items()]
+    if spills:
+        raise RuntimeError("kernels with scratch memory: " + ", ".join(spills))
     tmp = OUT + ".tmp"
     cmd = [_hipcc(), "-shared", "-fPIC", f"--offload-arch={ARCH}", "-o", tmp] + \
           [os.path.join(BUILD_DIR, o) for _, o, _ in units]

@@ -55,3 +55,30 @@ def test_no_kernel_uses_scratch():
     for part in ("pass1_z", "pass2_xyIfLi96ELi96ELi96E", "pass3_z", "pass4_rows", "gemm_xhy_k", "gemm_xc_k"):
         assert any(part in k for k in kernels), part
     assert {k: v for k, v in kernels.items() if v} == {}
+
+
+REMARKS = """a.hip:3:1: remark: Function Name: clean [-Rpass-analysis=kernel-resource-usage]
+    3 | __global__ void clean() {
+      | ^
+a.hip:3:1: remark:     VGPRs: 128 [-Rpass-analysis=kernel-resource-usage]
+a.hip:3:1: remark:     ScratchSize [bytes/lane]: 0 [-Rpass-analysis=kernel-resource-usage]
+a.hip:9:1: remark: Function Name: spills [-Rpass-analysis=kernel-resource-usage]
+a.hip:9:1: remark:     ScratchSize [bytes/lane]: 12 [-Rpass-analysis=kernel-resource-usage]
+"""
+
+
+def test_build_refuses_scratch(monkeypatch, tmp_path):
+    """The build fails, and links nothing, when the compiler reports scratch memory."""
+    from paper_2501_03061_amd.csrc import build as b
+    assert b.scratch_users(REMARKS) == {"spills": 12}
+
+    class Done:
+        returncode, stdout, stderr = 0, "", REMARKS
+
+    calls = []
+    monkeypatch.setattr(b.subprocess, "run", lambda cmd, **k: calls.append(cmd) or Done())
+    monkeypatch.setattr(b, "BUILD_DIR", str(tmp_path))
+    monkeypatch.setattr(b, "OUT", str(tmp_path / "lib.so"))
+    with pytest.raises(RuntimeError, match="scratch memory.*spills"):
+        b.build(jobs=2)
+    assert all("-shared" not in c for c in calls)
