@@ -385,8 +385,8 @@ static size_t xhy_kchunk(int na, int nb, size_t ng, int max_split, bool herm, in
   return kchunk;
 }
 
-size_t gemm_xhy_part_elems(int na, int nb, size_t ng, int* nsplit, bool herm) {
-  xhy_kchunk(na, nb, ng, 0, herm, nsplit);
+size_t gemm_xhy_part_elems(int na, int nb, size_t ng, int* nsplit, bool herm, int max_split) {
+  xhy_kchunk(na, nb, ng, max_split, herm, nsplit);
   return size_t(*nsplit) * na * nb;
 }
 

@@ -112,34 +112,68 @@ size_t ngrid(const px_cell* c) { return size_t(c->n[0]) * c->n[1] * c->n[2]; }
 bool misaligned(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) != 0; }
 size_t elem_bytes(px_precision p) { return p == PX_PREC_FP32 ? 8 : 16; }
 
-void default_tuning(const px_cell* cell, px_precision prec, int* ic, int* jc) {
-  // ic output orbitals x jc density orbitals per chunk; the Hermitian-pair mode
-  // takes square blocks of ic.  Larger chunks amortise the orbital tiles, the
-  // output read-modify-write and the launches; the pair buffer holds ic*jc
-  // slabs.  The block is the largest whose buffer stays near that of 32 x 32
-  // slabs at 96^3 (14.5 GB in FP64; both forms take the same block).  FP32 builds,
-  // ms, block 32 -> the rule's: 24^3 x 100 1.51 -> 1.21, 32^3 x 128 3.49 -> 3.04,
-  // 48^3 x 200 20.5 -> 19.3, 72^3 x 300 158.4 -> 154.9; at 96^3 x 203 blocks of 64
-  // would give 171 -> 168 for four times the memory.
+// A pair chunk: ic output orbitals x jc density orbitals (the Hermitian-pair mode
+// takes square blocks of the larger), and the z-tile configuration.
+struct Chunk {
+  int ic, jc, p2;
+};
+
+// Default pair blocks, largest first: the largest whose buffer of b x b slabs stays
+// near that of 32 x 32 slabs at 96^3 (14.5 GB in FP64; both forms take the same
+// block), and the smaller ones, for a workspace that does not hold it.  Larger
+// chunks amortise the orbital tiles, the output read-modify-write and the
+// launches.  FP32 builds, ms, block 32 -> the rule's: 24^3 x 100 1.51 -> 1.21,
+// 32^3 x 128 3.49 -> 3.04, 48^3 x 200 20.5 -> 19.3, 72^3 x 300 158.4 -> 154.9; at
+// 96^3 x 203 blocks of 64 would give 171 -> 168 for four times the memory.  Last a
+// block a quarter smaller than 32 or n: a workspace sized for the slabs of that block
+// has nothing to spare for the transposed kernel table.
+std::vector<int> default_blocks(const px_cell* cell, int n) {
   constexpr double kPairBytes = 16.4e9;
-  (void)prec;
-  *ic = 32;
-  for (const int b : {48, 64, 96, 128})
-    if (double(b) * b * double(ngrid(cell)) * 16.0 <= kPairBytes) *ic = b;
-  *jc = *ic / 2;
+  std::vector<int> v;
+  for (const int b : {128, 96, 64, 48, 32})
+    if (b == 32 || double(b) * b * double(ngrid(cell)) * 16.0 <= kPairBytes) v.push_back(b);
+  const int e = n < 32 ? n : 32;
+  v.push_back(e - (e > 4 ? e / 4 : e > 1 ? 1 : 0));
+  return v;
 }
 
-void tuning_for(const px_context* c, const px_cell* cell, px_precision prec, int* ic, int* jc,
-                int* p2 = nullptr) {
-  auto it = c->tuning.find({cell->n[0], cell->n[1], cell->n[2], int(prec)});
-  if (it != c->tuning.end()) {
-    *ic = std::get<0>(it->second);
-    *jc = std::get<1>(it->second);
-    if (p2) *p2 = std::get<2>(it->second);
-  } else {
-    default_tuning(cell, prec, ic, jc);
-    if (p2) *p2 = 0;
-  }
+// The chunks of an operation, the preferred first: the tuned one alone, or the
+// defaults.
+std::vector<Chunk> chunks(const px_context* c, const px_cell* cell, px_precision prec, bool symmetric, int n_psi,
+                          int n_phi) {
+  const auto it = c->tuning.find({cell->n[0], cell->n[1], cell->n[2], int(prec)});
+  if (it != c->tuning.end())
+    return {{std::get<0>(it->second), std::get<1>(it->second), std::get<2>(it->second)}};
+  std::vector<Chunk> v;
+  for (const int b : default_blocks(cell, n_psi > n_phi ? n_psi : n_phi))
+    v.push_back({b, symmetric || b == 1 ? b : b / 2, 0});
+  return v;
+}
+
+// Splits of the N_g sum of a contraction (0: the default's) for a workspace that
+// does not hold the partials of the default: at least 1,024 values each, 4,096,
+// one split.
+constexpr int kSplitSteps = 4;
+int split_step(int k, size_t ng) {
+  return k == 0 ? 0 : k == 1 ? int((ng + 1023) / 1024) : k == 2 ? int((ng + 4095) / 4096) : 1;
+}
+
+// The first chunk, then split step, whose bytes(chunk, split step) fit; the
+// smallest if none does.
+struct Fit {
+  Chunk ch;
+  int step;
+};
+template <class F> Fit fit_chunk(const std::vector<Chunk>& chs, size_t avail, F&& bytes) {
+  for (int k = 0; k < kSplitSteps; ++k)
+    for (const Chunk& ch : chs)
+      if (bytes(ch, k) <= avail) return {ch, k};
+  return {chs.back(), kSplitSteps - 1};
+}
+template <class F> int fit_splits(size_t avail, F&& bytes) {
+  for (int k = 0; k < kSplitSteps; ++k)
+    if (bytes(k) <= avail) return k;
+  return kSplitSteps - 1;
 }
 
 // Workspace layout of one exchange application.
@@ -147,17 +181,17 @@ struct ExLayout {
   size_t t, g0, expart, S, kt, end;
 };
 
-ExLayout ex_layout(const px_cell* cell, px_precision prec, int n_psi, int n_phi, int ic, int jc,
-                   bool energy, int p2 = 0) {
+ExLayout ex_layout(const px_cell* cell, px_precision prec, int n_psi, int n_phi, const Chunk& ch,
+                   bool energy) {
   ExLayout l{};
-  const int icc = ic < n_phi ? ic : n_phi, jcc = jc < n_psi ? jc : n_psi;
+  const int icc = ch.ic < n_phi ? ch.ic : n_phi, jcc = ch.jc < n_psi ? ch.jc : n_psi;
   const size_t pairs = size_t(icc) * jcc;
   size_t off = 0;
   l.t = off;
   off = align_up(off + pairs * ngrid(cell) * elem_bytes(prec));
   l.g0 = off;
   if (prec == PX_PREC_FP32)
-    off = align_up(off + pairs * px::ztile_count(true, cell->n, p2) * sizeof(px::G0Part));
+    off = align_up(off + pairs * px::ztile_count(true, cell->n, ch.p2) * sizeof(px::G0Part));
   l.expart = off;
   l.S = off;
   if (energy) {
@@ -174,13 +208,13 @@ ExLayout ex_layout(const px_cell* cell, px_precision prec, int n_psi, int n_phi,
 struct AceLayout {
   ExLayout ex;
   size_t W, M, L, U, dinv, part, end;
+  int nsplit;
 };
 
-AceLayout ace_layout(const px_cell* cell, px_precision prec, int n, int ic, int jc,
-                     bool symmetric, int p2 = 0) {
+AceLayout ace_layout(const px_cell* cell, px_precision prec, int n, Chunk ch, bool symmetric, int step) {
   AceLayout a{};
-  if (symmetric) ic = jc = (ic > jc ? ic : jc);
-  a.ex = ex_layout(cell, prec, n, n, ic, jc, true, p2);
+  if (symmetric) ch.ic = ch.jc = (ch.ic > ch.jc ? ch.ic : ch.jc);
+  a.ex = ex_layout(cell, prec, n, n, ch, true);
   size_t off = a.ex.end;
   a.W = off;
   off = align_up(off + size_t(n) * ngrid(cell) * elem_bytes(prec));
@@ -192,8 +226,7 @@ AceLayout ace_layout(const px_cell* cell, px_precision prec, int n, int ic, int 
   off = align_up(off + size_t(n) * n * 16);
   a.dinv = off;
   off = align_up(off + px::chol_dinv_bytes(n));
-  int nsplit = 0;
-  const size_t pe = px::gemm_xhy_part_elems(n, n, ngrid(cell), &nsplit, true);
+  const size_t pe = px::gemm_xhy_part_elems(n, n, ngrid(cell), &a.nsplit, true, split_step(step, ngrid(cell)));
   a.part = off;
   off = align_up(off + pe * 16);
   a.end = off;
@@ -202,17 +235,17 @@ AceLayout ace_layout(const px_cell* cell, px_precision prec, int n, int ic, int 
 
 struct ApplyLayout {
   size_t C, C32, part, end;
+  int nsplit;
 };
 
-ApplyLayout apply_layout(const px_cell* cell, int n, int n_phi) {
+ApplyLayout apply_layout(const px_cell* cell, int n, int n_phi, int step) {
   ApplyLayout a{};
   size_t off = 0;
   a.C = off;
   off = align_up(off + size_t(n) * n_phi * 16);
   a.C32 = off;  // C rounded to complex64, the operand of the FP32 form's xi C
   off = align_up(off + size_t(n) * n_phi * 8);
-  int nsplit = 0;
-  const size_t pe = px::gemm_xhy_part_elems(n, n_phi, ngrid(cell), &nsplit);
+  const size_t pe = px::gemm_xhy_part_elems(n, n_phi, ngrid(cell), &a.nsplit, false, split_step(step, ngrid(cell)));
   a.part = off;
   off = align_up(off + pe * 16);
   a.end = off;
@@ -224,12 +257,12 @@ struct LoopLayout {
   size_t mid, buf0, buf1, partial, end;
 };
 
-LoopLayout loop_layout(const px_cell* cell, px_precision prec, int n, int n_phi) {
+LoopLayout loop_layout(const px_cell* cell, px_precision prec, int n, int n_phi, int step) {
   LoopLayout l{};
-  l.ap = apply_layout(cell, n, n_phi);
+  l.ap = apply_layout(cell, n, n_phi, step);
   size_t off = l.ap.end;
   const size_t blk = size_t(n_phi) * ngrid(cell) * elem_bytes(prec);
-  l.mid = off;  // the midpoint, then V_ACE of it (xi^H mid is taken before it is overwritten)
+  l.mid = off;
   off = align_up(off + blk);
   l.buf0 = off;
   off = align_up(off + blk);
@@ -284,14 +317,15 @@ struct StepLayout {
   size_t part2, mid, Y, Z, buf0, buf1, partial;
   size_t S, Hm, Mneg, L, U, dinv, T, X, X32, smid, sbuf0, sbuf1, A1, A2, st;
   size_t end;
+  int nsplit2;
 };
 
-StepLayout step_layout(const px_cell* cell, px_precision prec, int n, int n_phi, int n_iter) {
+StepLayout step_layout(const px_cell* cell, px_precision prec, int n, int n_phi, int n_iter, int step) {
   StepLayout l{};
-  l.ap = apply_layout(cell, n, n_phi);
+  l.ap = apply_layout(cell, n, n_phi, step);
   size_t off = l.ap.end;
-  int nsplit = 0;
-  const size_t pe = px::gemm_xhy_part_elems(n_phi, n_phi, ngrid(cell), &nsplit, true);
+  const size_t pe =
+      px::gemm_xhy_part_elems(n_phi, n_phi, ngrid(cell), &l.nsplit2, true, split_step(step, ngrid(cell)));
   l.part2 = off;
   off = align_up(off + pe * 16);
   const size_t blk = size_t(n_phi) * ngrid(cell) * elem_bytes(prec);
@@ -369,9 +403,11 @@ px_status need_ws(px_context* c, size_t bytes) {
 // solved as its lower triangle j <= i, so every unordered pair is solved once.
 px_status run_exchange(px_context* c, const px_cell* cell, px_precision prec, int n_psi,
                        const void* psi, const double* occ, int n_phi, const void* phi,
-                       const double* kern, void* out, const ExLayout& l, bool energy, int ic,
-                       int jc, bool symmetric, hipStream_t s, int p2 = 0) {
+                       const double* kern, void* out, const ExLayout& l, bool energy, const Chunk& ch,
+                       bool symmetric, hipStream_t s) {
   const bool fp32 = prec == PX_PREC_FP32;
+  int ic = ch.ic, jc = ch.jc;
+  const int p2 = ch.p2;
   const size_t ng = ngrid(cell);
   px::ChunkArgs a{};
   a.psi = psi;
@@ -506,23 +542,23 @@ size_t px_workspace_bytes(const px_context* ctx, px_op op, const px_cell* cell, 
   const bool fft_op = op == PX_OP_EXCHANGE || op == PX_OP_ACE_BUILD || op == PX_OP_EXCHANGE_SIGMA ||
                       op == PX_OP_ACE_BUILD_SIGMA;
   if (fft_op ? !fft_grid : !gemm_grid) return 0;
-  int ic, jc, p2;
-  tuning_for(ctx, cell, prec, &ic, &jc, &p2);
+  const Chunk gen = chunks(ctx, cell, prec, false, n_psi, n_phi)[0];
+  const Chunk ace = chunks(ctx, cell, prec, ctx->symmetric_ace, n_psi, n_psi)[0];
   switch (op) {
     case PX_OP_EXCHANGE:
       if (n_phi <= 0) return 0;
-      return ex_layout(cell, prec, n_psi, n_phi, ic, jc, true, p2).end;
+      return ex_layout(cell, prec, n_psi, n_phi, gen, true).end;
     case PX_OP_ACE_BUILD:
-      return ace_layout(cell, prec, n_psi, ic, jc, ctx->symmetric_ace, p2).end;
+      return ace_layout(cell, prec, n_psi, ace, ctx->symmetric_ace, 0).end;
     case PX_OP_ACE_APPLY:
       if (n_phi <= 0) return 0;
-      return apply_layout(cell, n_psi, n_phi).end;
+      return apply_layout(cell, n_psi, n_phi, 0).end;
     case PX_OP_PTIM_LOOP:
       if (n_phi <= 0) return 0;
-      return loop_layout(cell, prec, n_psi, n_phi).end;
+      return loop_layout(cell, prec, n_psi, n_phi, 0).end;
     case PX_OP_EXCHANGE_SIGMA: {
       if (n_phi <= 0) return 0;
-      const ExLayout ex = ex_layout(cell, prec, n_psi, n_phi, ic, jc, false, p2);
+      const ExLayout ex = ex_layout(cell, prec, n_psi, n_phi, gen, false);
       return sigma_layout(ex.end, cell, prec, n_psi, false).end;
     }
     case PX_OP_SIGMA_DIAG:
@@ -531,14 +567,14 @@ size_t px_workspace_bytes(const px_context* ctx, px_op op, const px_cell* cell, 
       return sigma_layout(0, cell, prec, n_psi, false).end;
     case PX_OP_PTIM_STEP:
       if (n_phi <= 0) return 0;
-      return step_layout(cell, prec, n_psi, n_phi, kStepMaxIter).end;
+      return step_layout(cell, prec, n_psi, n_phi, kStepMaxIter, 0).end;
     case PX_OP_ROTATE:  // Q in complex64 (the FP64 form does not use it)
       return align_up(size_t(n_psi) * n_psi * 8);
     case PX_OP_DENSITY_FINE:
       if (!fine_grid_ok(cell)) return 0;
       return align_up(px::density_fine_work_bytes(prec == PX_PREC_FP32, cell->n, n_psi));
     case PX_OP_ACE_BUILD_SIGMA: {
-      const AceLayout a = ace_layout(cell, prec, n_psi, ic, jc, ctx->symmetric_ace, p2);
+      const AceLayout a = ace_layout(cell, prec, n_psi, ace, ctx->symmetric_ace, 0);
       return sigma_layout(a.end, cell, prec, n_psi, false).end;
     }
   }
@@ -616,15 +652,16 @@ px_status px_exchange_apply(px_context* ctx, const px_cell* cell, px_precision p
     return fail(ctx, PX_ERR_INVALID_ARG, "exchange_apply: orbital blocks must be 16-byte aligned");
   if (e_x && (phi != psi || n_phi != n_psi))
     return fail(ctx, PX_ERR_INVALID_ARG, "exchange_apply: e_x requires phi == psi and n_phi == n_psi");
-  int ic, jc, p2;
-  tuning_for(ctx, cell, prec, &ic, &jc, &p2);
-  const ExLayout l = ex_layout(cell, prec, n_psi, n_phi, ic, jc, e_x != nullptr, p2);
+  const Chunk ch = fit_chunk(chunks(ctx, cell, prec, false, n_psi, n_phi), ctx->ws_bytes, [&](const Chunk& x, int) {
+                     return ex_layout(cell, prec, n_psi, n_phi, x, e_x != nullptr).end;
+                   }).ch;
+  const ExLayout l = ex_layout(cell, prec, n_psi, n_phi, ch, e_x != nullptr);
   st = need_ws(ctx, l.end);
   if (st != PX_OK) return st;
   hipError_t he = hipSetDevice(ctx->device);
   if (he != hipSuccess) return hip_check(ctx, he, "hipSetDevice");
   st = run_exchange(ctx, cell, prec, n_psi, psi, occ, n_phi, phi, kernel_G, vx_phi, l,
-                    e_x != nullptr, ic, jc, false, stream, p2);
+                    e_x != nullptr, ch, false, stream);
   if (st != PX_OK) return st;
   if (e_x) {
     const double ng = double(ngrid(cell));
@@ -647,8 +684,8 @@ namespace {
 // Cholesky breakdown column goes to *status.
 px_status ace_build_run(px_context* ctx, const px_cell* cell, px_precision prec, int n,
                         const void* psi, const double* occ, const double* kernel_G, void* xi,
-                        double* M, double* e_x, int32_t* status, const AceLayout& l, int ic,
-                        int jc, int p2, hipStream_t stream) {
+                        double* M, double* e_x, int32_t* status, const AceLayout& l, const Chunk& ch,
+                        hipStream_t stream) {
   px_status st = PX_OK;
   hipError_t he = hipSuccess;
   const bool fp32 = prec == PX_PREC_FP32;
@@ -668,8 +705,8 @@ px_status ace_build_run(px_context* ctx, const px_cell* cell, px_precision prec,
   double* U = reinterpret_cast<double*>(ctx->ws + l.U);
   double* part = reinterpret_cast<double*>(ctx->ws + l.part);
   // W = Vx Psi (pair pipeline) and the energy sums
-  st = run_exchange(ctx, cell, prec, n, psi, occ, n, psi, kernel_G, W, l.ex, true, ic, jc,
-                    ctx->symmetric_ace, stream, p2);
+  st = run_exchange(ctx, cell, prec, n, psi, occ, n, psi, kernel_G, W, l.ex, true, ch,
+                    ctx->symmetric_ace, stream);
   if (st != PX_OK) return st;
   if (e_x) {
     st = hip_check(ctx,
@@ -678,12 +715,10 @@ px_status ace_build_run(px_context* ctx, const px_cell* cell, px_precision prec,
                    "energy");
     if (st != PX_OK) return st;
   }
-  int nsplit = 0;
-  px::gemm_xhy_part_elems(n, n, ng, &nsplit, true);
   if (ctx->profiling) (void)hipEventRecord(ev[1], stream);
   // M = dV Psi^H W, Hermitised; -M = L L^H; U = L^{-H}; xi = W U
   // M is Hermitian up to rounding: the tiles above the diagonal are mirrored
-  st = hip_check(ctx, px::launch_gemm_xhy_herm(fp32, n, ng, psi, W, dV, Mw, part, nsplit, stream),
+  st = hip_check(ctx, px::launch_gemm_xhy_herm(fp32, n, ng, psi, W, dV, Mw, part, l.nsplit, stream),
                  "M = dV Psi^H W");
   if (st != PX_OK) return st;
   if (ctx->profiling) (void)hipEventRecord(ev[2], stream);
@@ -741,14 +776,15 @@ px_status px_ace_build(px_context* ctx, const px_cell* cell, px_precision prec, 
   if (xi == psi) return fail(ctx, PX_ERR_INVALID_ARG, "ace_build: xi must not alias psi");
   if (misaligned(psi) || misaligned(xi))
     return fail(ctx, PX_ERR_INVALID_ARG, "ace_build: orbital blocks must be 16-byte aligned");
-  int ic, jc, p2;
-  tuning_for(ctx, cell, prec, &ic, &jc, &p2);
-  const AceLayout l = ace_layout(cell, prec, n, ic, jc, ctx->symmetric_ace, p2);
+  const bool sym = ctx->symmetric_ace;
+  const Fit f = fit_chunk(chunks(ctx, cell, prec, sym, n, n), ctx->ws_bytes,
+                          [&](const Chunk& x, int k) { return ace_layout(cell, prec, n, x, sym, k).end; });
+  const AceLayout l = ace_layout(cell, prec, n, f.ch, sym, f.step);
   st = need_ws(ctx, l.end);
   if (st != PX_OK) return st;
   hipError_t he = hipSetDevice(ctx->device);
   if (he != hipSuccess) return hip_check(ctx, he, "hipSetDevice");
-  st = ace_build_run(ctx, cell, prec, n, psi, occ, kernel_G, xi, M, e_x, status, l, ic, jc, p2, stream);
+  st = ace_build_run(ctx, cell, prec, n, psi, occ, kernel_G, xi, M, e_x, status, l, f.ch, stream);
   if (st == PX_OK) ctx->last_status.assign(1, {status, PX_ERR_NOT_POSITIVE_DEFINITE, "ace_build: -M"});
   return st;
 }
@@ -768,7 +804,9 @@ px_status px_ace_apply(px_context* ctx, const px_cell* cell, px_precision prec, 
     return fail(ctx, PX_ERR_INVALID_ARG, "ace_apply: out must not alias xi or phi");
   if (misaligned(xi) || misaligned(phi) || misaligned(out))
     return fail(ctx, PX_ERR_INVALID_ARG, "ace_apply: orbital blocks must be 16-byte aligned");
-  const ApplyLayout l = apply_layout(cell, n, n_phi);
+  const ApplyLayout l = apply_layout(cell, n, n_phi, fit_splits(ctx->ws_bytes, [&](int k) {
+                                       return apply_layout(cell, n, n_phi, k).end;
+                                     }));
   st = need_ws(ctx, l.end);
   if (st != PX_OK) return st;
   hipError_t he = hipSetDevice(ctx->device);
@@ -779,9 +817,7 @@ px_status px_ace_apply(px_context* ctx, const px_cell* cell, px_precision prec, 
   double* C = reinterpret_cast<double*>(ctx->ws + l.C);
   float* C32 = fp32 ? reinterpret_cast<float*>(ctx->ws + l.C32) : nullptr;
   double* part = reinterpret_cast<double*>(ctx->ws + l.part);
-  int nsplit = 0;
-  px::gemm_xhy_part_elems(n, n_phi, ng, &nsplit);
-  st = hip_check(ctx, px::launch_gemm_xhy(fp32, n, n_phi, ng, xi, phi, dV, C, n_phi, part, nsplit,
+  st = hip_check(ctx, px::launch_gemm_xhy(fp32, n, n_phi, ng, xi, phi, dV, C, n_phi, part, l.nsplit,
                                           C32, stream),
                  "C = dV xi^H phi");
   if (st != PX_OK) return st;
@@ -808,7 +844,9 @@ px_status px_ptim_exchange_loop(px_context* ctx, const px_cell* cell, px_precisi
   if (misaligned(xi) || misaligned(phi_n) || misaligned(phi_out))
     return fail(ctx, PX_ERR_INVALID_ARG,
                 "ptim_exchange_loop: orbital blocks must be 16-byte aligned");
-  const LoopLayout l = loop_layout(cell, prec, n, n_phi);
+  const LoopLayout l = loop_layout(cell, prec, n, n_phi, fit_splits(ctx->ws_bytes, [&](int k) {
+                                     return loop_layout(cell, prec, n, n_phi, k).end;
+                                   }));
   st = need_ws(ctx, l.end);
   if (st != PX_OK) return st;
   hipError_t he = hipSetDevice(ctx->device);
@@ -823,14 +861,12 @@ px_status px_ptim_exchange_loop(px_context* ctx, const px_cell* cell, px_precisi
   void* mid = ctx->ws + l.mid;
   void* bufs[2] = {ctx->ws + l.buf0, ctx->ws + l.buf1};
   double* partial = reinterpret_cast<double*>(ctx->ws + l.partial);
-  int nsplit = 0;
-  px::gemm_xhy_part_elems(n, n_phi, ng, &nsplit);
   const void* cur = phi_n;
   for (int k = 0; k < n_iter; ++k) {
     void* nxt = (k == n_iter - 1) ? phi_out : bufs[k & 1];
     // (the first midpoint is phi_n itself; the update leaves the next one)
     st = hip_check(ctx, px::launch_gemm_xhy(fp32, n, n_phi, ng, xi, k == 0 ? phi_n : mid, dV, C, n_phi,
-                                            part, nsplit, C32, stream),
+                                            part, l.ap.nsplit, C32, stream),
                    "C = dV xi^H mid");
     if (st != PX_OK) return st;
     st = hip_check(ctx, px::launch_ptim_xc(fp32, n, n_phi, ng, xi, Cc, n_phi,
@@ -912,9 +948,10 @@ px_status px_exchange_apply_sigma(px_context* ctx, const px_cell* cell, px_preci
   if (misaligned(phi_basis) || misaligned(tgt) || misaligned(vx_tgt) || misaligned(sigma))
     return fail(ctx, PX_ERR_INVALID_ARG,
                 "exchange_apply_sigma: orbital blocks and sigma must be 16-byte aligned");
-  int ic, jc, p2;
-  tuning_for(ctx, cell, prec, &ic, &jc, &p2);
-  const ExLayout ex = ex_layout(cell, prec, n, n_tgt, ic, jc, false, p2);
+  const Chunk ch = fit_chunk(chunks(ctx, cell, prec, false, n, n_tgt), ctx->ws_bytes, [&](const Chunk& x, int) {
+                     return sigma_layout(ex_layout(cell, prec, n, n_tgt, x, false).end, cell, prec, n, false).end;
+                   }).ch;
+  const ExLayout ex = ex_layout(cell, prec, n, n_tgt, ch, false);
   const SigmaLayout sl = sigma_layout(ex.end, cell, prec, n, false);
   st = need_ws(ctx, sl.end);
   if (st != PX_OK) return st;
@@ -924,7 +961,7 @@ px_status px_exchange_apply_sigma(px_context* ctx, const px_cell* cell, px_preci
   if (st != PX_OK) return st;
   // Eq. 13 on (phi, d): the double loop over the rotated orbitals
   st = run_exchange(ctx, cell, prec, n, ctx->ws + sl.phi, reinterpret_cast<double*>(ctx->ws + sl.d),
-                    n_tgt, tgt, kernel_G, vx_tgt, ex, false, ic, jc, false, stream, p2);
+                    n_tgt, tgt, kernel_G, vx_tgt, ex, false, ch, false, stream);
   if (st == PX_OK) ctx->last_status.assign(1, {status, PX_ERR_NOT_CONVERGED, "exchange_apply_sigma"});
   return st;
 }
@@ -1046,9 +1083,11 @@ px_status px_ace_build_sigma(px_context* ctx, const px_cell* cell, px_precision 
   if (misaligned(phi_basis) || misaligned(xi) || misaligned(sigma))
     return fail(ctx, PX_ERR_INVALID_ARG,
                 "ace_build_sigma: orbital blocks and sigma must be 16-byte aligned");
-  int ic, jc, p2;
-  tuning_for(ctx, cell, prec, &ic, &jc, &p2);
-  const AceLayout l = ace_layout(cell, prec, n, ic, jc, ctx->symmetric_ace, p2);
+  const bool sym = ctx->symmetric_ace;
+  const Fit f = fit_chunk(chunks(ctx, cell, prec, sym, n, n), ctx->ws_bytes, [&](const Chunk& x, int k) {
+    return sigma_layout(ace_layout(cell, prec, n, x, sym, k).end, cell, prec, n, false).end;
+  });
+  const AceLayout l = ace_layout(cell, prec, n, f.ch, sym, f.step);
   const SigmaLayout sl = sigma_layout(l.end, cell, prec, n, false);
   st = need_ws(ctx, sl.end);
   if (st != PX_OK) return st;
@@ -1059,7 +1098,7 @@ px_status px_ace_build_sigma(px_context* ctx, const px_cell* cell, px_precision 
   st = rotate_orbitals(ctx, sl, cell, prec, n, phi_basis, sigma, status, stream);
   if (st != PX_OK) return st;
   st = ace_build_run(ctx, cell, prec, n, ctx->ws + sl.phi, reinterpret_cast<double*>(ctx->ws + sl.d),
-                     kernel_G, xi, M, e_x, status + 1, l, ic, jc, p2, stream);
+                     kernel_G, xi, M, e_x, status + 1, l, f.ch, stream);
   if (st == PX_OK)
     ctx->last_status = {{status, PX_ERR_NOT_CONVERGED, "ace_build_sigma"},
                         {status + 1, PX_ERR_NOT_POSITIVE_DEFINITE, "ace_build_sigma: -M"}};
@@ -1084,7 +1123,9 @@ px_status px_ptim_step(px_context* ctx, const px_cell* cell, px_precision prec, 
   if (misaligned(xi) || misaligned(phi_n) || misaligned(phi_out) || misaligned(sigma_n) ||
       misaligned(sigma_out))
     return fail(ctx, PX_ERR_INVALID_ARG, "ptim_step: arrays must be 16-byte aligned");
-  const StepLayout l = step_layout(cell, prec, n, n_phi, kStepMaxIter);
+  const StepLayout l = step_layout(cell, prec, n, n_phi, kStepMaxIter, fit_splits(ctx->ws_bytes, [&](int k) {
+                                     return step_layout(cell, prec, n, n_phi, kStepMaxIter, k).end;
+                                   }));
   st = need_ws(ctx, l.end);
   if (st != PX_OK) return st;
   hipError_t he = hipSetDevice(ctx->device);
@@ -1100,9 +1141,7 @@ px_status px_ptim_step(px_context* ctx, const px_cell* cell, px_precision prec, 
   float* X32 = reinterpret_cast<float*>(w + l.X32);
   const void* Xc = fp32 ? static_cast<const void*>(X32) : D(l.X);
   int32_t* sts = reinterpret_cast<int32_t*>(w + l.st);
-  int ns1 = 0, ns2 = 0;
-  px::gemm_xhy_part_elems(n, n_phi, ng, &ns1);
-  px::gemm_xhy_part_elems(n_phi, n_phi, ng, &ns2, true);
+  const int ns1 = l.ap.nsplit, ns2 = l.nsplit2;
   void* pbufs[2] = {w + l.buf0, w + l.buf1};
   double* sbufs[2] = {D(l.sbuf0), D(l.sbuf1)};
   const void* cur_p = phi_n;
@@ -1231,21 +1270,19 @@ struct BatchPlan {
   std::vector<int> job_inst;       // instance of each job
   std::vector<BatchWave> waves;
   std::vector<TailGroup> groups;
+  int step = 0;                    // split step of the Gram matrices
 };
 
 // Pair block of an instance in the batched form: the tuned one, else 32, whatever
 // the grid (a wave holds the chunks of many instances; with the single
 // form's larger default a batch of 12 took 75.1 ms instead of 72.7).
-int block_for(const px_context* c, const px_cell* cell, px_precision prec) {
-  if (!c->tuning.count({cell->n[0], cell->n[1], cell->n[2], int(prec)})) return 32;
-  int ic, jc;
-  tuning_for(c, cell, prec, &ic, &jc);
-  return ic > jc ? ic : jc;
+int block_for(const px_context* c, const px_cell* cell, px_precision prec, int dflt = 32) {
+  const auto it = c->tuning.find({cell->n[0], cell->n[1], cell->n[2], int(prec)});
+  return it == c->tuning.end() ? dflt : std::max(std::get<0>(it->second), std::get<1>(it->second));
 }
 int tile_cfg_for(const px_context* c, const px_cell* cell, px_precision prec) {
-  int ic, jc, p2;
-  tuning_for(c, cell, prec, &ic, &jc, &p2);
-  return p2;
+  const auto it = c->tuning.find({cell->n[0], cell->n[1], cell->n[2], int(prec)});
+  return it == c->tuning.end() ? 0 : std::get<2>(it->second);
 }
 
 // Plan of one batched call.  Instances are grouped by grid (all three
@@ -1254,11 +1291,16 @@ int tile_cfg_for(const px_context* c, const px_cell* cell, px_precision prec) {
 // chunks writing the same output block (pass 3 writes block I, pass 4 block
 // J): d = 0 first (those chunks initialise the output), then d = 1, 2, ...  A
 // diagonal's chunks are packed into waves that fit the pair buffer.  In ACE
-// mode the instances completed by a wave form a tail group.  ws == nullptr:
-// sizes only.
+// mode the instances completed by a wave form a tail group.  sz.cap: the pair buffer
+// of a wave, in bytes.  ws == nullptr: sizes only.
+struct BatchSizes {
+  size_t cap;
+  int block, step;  // default pair block, split step of the Gram matrices
+};
 BatchPlan plan_batch(const px_context* c, int n_inst, const px_instance* in, px_precision prec,
-                     bool ace, char* ws) {
+                     bool ace, const BatchSizes& sz, char* ws) {
   BatchPlan P;
+  P.step = sz.step;
   const bool fp32 = prec == PX_PREC_FP32;
   const size_t b = elem_bytes(prec);
   size_t t_bytes = 0, g0_slots = 0, ex_slots = 0;  // sizes of the pair buffer and of the partials
@@ -1274,18 +1316,18 @@ BatchPlan plan_batch(const px_context* c, int n_inst, const px_instance* in, px_
   });
   struct Chunk { int inst, I, J, B; };
   for (const Grid& gr : grids) {
-    // pair-buffer capacity of the grid: batch_cap_bytes, at least its largest chunk
+    // pair-buffer capacity of the grid: sz.cap, at least its largest chunk
     int max_nb = 0;
     size_t min_pairs = 1;
     for (int k = 0; k < n_inst; ++k)
       if (grid_of(k) == gr) {
-        const int B = block_for(c, &in[k].cell, prec);
+        const int B = block_for(c, &in[k].cell, prec, sz.block);
         max_nb = std::max(max_nb, (int(in[k].n) + B - 1) / B);
         const size_t e = size_t(std::min(B, int(in[k].n)));
         min_pairs = std::max(min_pairs, e * e);
       }
     const size_t ng = size_t(gr[0]) * gr[1] * gr[2];
-    const size_t cap = std::max(min_pairs, c->batch_cap_bytes / (ng * b));
+    const size_t cap = std::max(min_pairs, sz.cap / (ng * b));
     t_bytes = std::max(t_bytes, cap * ng * b);
     // per pair: one G = 0 sum per z tile and n2 energy-partial slots
     int p2 = 0;  // the tuning of the grid (every instance of a grid shares it)
@@ -1297,7 +1339,7 @@ BatchPlan plan_batch(const px_context* c, int n_inst, const px_instance* in, px_
       std::vector<Chunk> diag;
       for (int k = 0; k < n_inst; ++k) {
         if (grid_of(k) != gr) continue;
-        const int B = block_for(c, &in[k].cell, prec);
+        const int B = block_for(c, &in[k].cell, prec, sz.block);
         const int nb = (int(in[k].n) + B - 1) / B;
         for (int J = 0; J + d < nb; ++J) diag.push_back({k, J + d, J, B});
       }
@@ -1404,7 +1446,8 @@ BatchPlan plan_batch(const px_context* c, int n_inst, const px_instance* in, px_
     size_t part = 0;
     for (int k = 0; k < n_inst; ++k) {
       int ns = 0;
-      part = std::max(part, px::gemm_xhy_part_elems(in[k].n, in[k].n, ngrid(&in[k].cell), &ns, true));
+      const size_t ng = ngrid(&in[k].cell);
+      part = std::max(part, px::gemm_xhy_part_elems(in[k].n, in[k].n, ng, &ns, true, split_step(sz.step, ng)));
     }
     P.part_off.resize(px_context::kTailLanes);
     for (int l = 0; l < px_context::kTailLanes; ++l) {
@@ -1494,7 +1537,7 @@ px_status enqueue_tail(px_context* c, const BatchPlan& P, const TailGroup& g, co
       if (st != PX_OK) return st;
     }
     int nsplit = 0;
-    px::gemm_xhy_part_elems(x.n, x.n, ng, &nsplit, true);
+    px::gemm_xhy_part_elems(x.n, x.n, ng, &nsplit, true, split_step(P.step, ng));
     st = hip_check(c, px::launch_gemm_xhy_herm(fp32, x.n, ng, x.psi, ws + P.W_off[k],
                                                omega / double(ng), P.jobs[q].M, part, nsplit, ls),
                    "batched M");
@@ -1640,7 +1683,7 @@ size_t px_workspace_bytes_batched(const px_context* ctx, int32_t n_inst, const p
     if (!cell_ok(&inst[k].cell) || inst[k].n <= 0 ||
         !px::grid_supported(inst[k].cell.n[0], inst[k].cell.n[1], inst[k].cell.n[2]))
       return 0;
-  return plan_batch(ctx, n_inst, inst, prec, ace != 0, nullptr).end;
+  return plan_batch(ctx, n_inst, inst, prec, ace != 0, {ctx->batch_cap_bytes, 32, 0}, nullptr).end;
 }
 
 px_status px_set_batch_capacity(px_context* ctx, size_t pair_buffer_bytes) {
@@ -1660,12 +1703,25 @@ px_status px_exchange_apply_batched(px_context* ctx, int32_t n_inst, const px_in
   if (!ctx) return PX_ERR_INVALID_ARG;
   px_status st = check_instances(ctx, n_inst, inst, prec, ace != 0);
   if (st != PX_OK) return st;
-  BatchPlan P = plan_batch(ctx, n_inst, inst, prec, ace != 0, nullptr);
+  // a workspace that does not hold the preferred plan: a smaller pair buffer (down
+  // to half), then smaller blocks, then longer splits
+  BatchSizes sz{ctx->batch_cap_bytes, 32, 0};
+  BatchPlan P = plan_batch(ctx, n_inst, inst, prec, ace != 0, sz, nullptr);
+  size_t slab = 0;
+  for (int k = 0; k < n_inst; ++k) slab = std::max(slab, ngrid(&inst[k].cell) * elem_bytes(prec));
+  for (int cuts = 0; P.end > ctx->ws_bytes;) {
+    const size_t less = (P.end - ctx->ws_bytes) / 4 * 5 + slab;
+    if (cuts < 3 && less < sz.cap / 4 && sz.cap - less >= ctx->batch_cap_bytes / 2) sz.cap -= less, ++cuts;
+    else if (sz.block == 32) sz.block = 24;
+    else if (sz.step + 1 < kSplitSteps) ++sz.step;
+    else break;
+    P = plan_batch(ctx, n_inst, inst, prec, ace != 0, sz, nullptr);
+  }
   st = need_ws(ctx, P.end);
   if (st != PX_OK) return st;
   hipError_t he = hipSetDevice(ctx->device);
   if (he != hipSuccess) return hip_check(ctx, he, "hipSetDevice");
-  P = plan_batch(ctx, n_inst, inst, prec, ace != 0, ctx->ws);
+  P = plan_batch(ctx, n_inst, inst, prec, ace != 0, sz, ctx->ws);
   std::vector<unsigned char> img;
   table_image(P, img);
   const size_t tbytes = img.size();
@@ -1757,13 +1813,14 @@ px_status px_autotune(px_context* ctx, const px_cell* cell, px_precision prec, i
     if (covered) break;
     covered = B >= n;
     for (int p2 = 0; p2 < px::kTileConfigs && st == PX_OK; ++p2) {
-      const ExLayout l = ex_layout(cell, prec, n, n, B, B, false, p2);
+      const Chunk ch{B, B, p2};
+      const ExLayout l = ex_layout(cell, prec, n, n, ch, false);
       if (ctx->ws == nullptr || ctx->ws_bytes < l.end) continue;
       float ms = 0.f, best_ms = 1e30f;
       for (int rep = 0; rep < 3; ++rep) {
         (void)hipEventRecord(e0, stream);
-        st = run_exchange(ctx, cell, prec, n, psi, occ, n, psi, kernel_G, out, l, false, B, B, true,
-                          stream, p2);
+        st = run_exchange(ctx, cell, prec, n, psi, occ, n, psi, kernel_G, out, l, false, ch, true,
+                          stream);
         (void)hipEventRecord(e1, stream);
         if (st != PX_OK) break;
         he = hipEventSynchronize(e1);

@@ -209,7 +209,8 @@ hipError_t launch_gemm_xhy(bool fp32, int na, int nb, size_t ng, const void* X, 
 hipError_t launch_gemm_xhy_herm(bool fp32, int n, size_t ng, const void* X, const void* Y,
                                 double scale, double* M, double* part, int nsplit,
                                 hipStream_t s);
-size_t gemm_xhy_part_elems(int na, int nb, size_t ng, int* nsplit, bool herm = false);
+// (max_split > 0: at most so many splits)
+size_t gemm_xhy_part_elems(int na, int nb, size_t ng, int* nsplit, bool herm = false, int max_split = 0);
 // Splits launch_gemm_xhy uses when at most max_split are available (fewer,
 // longer splits than the default when max_split is below it).
 int gemm_xhy_splits(int na, int nb, size_t ng, int max_split);
