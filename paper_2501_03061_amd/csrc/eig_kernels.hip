@@ -108,20 +108,21 @@ __device__ __forceinline__ int bj_index(int nb, int k, int slot, int t) {
   return t < BJ ? I * BJ + t : J * BJ + (t - BJ);
 }
 
-// 1/sqrt(x) and 1/x of a normal x: the hardware's approximation (5e-8) with one
-// Newton step (4e-15 at most, 3e-16 rms over 1 M values) or two (rounded: 1.4e-16).
+// 1/sqrt(x) of a normal x: the hardware's approximation (5e-8) with one Newton
+// step (4e-15 at most, 3e-16 rms over 1 M values).
 __device__ __forceinline__ double rsq1(double x) {
   const double y = __builtin_amdgcn_rsq(x);
   return fma(0.5 * y, fma(-x * y, y, 1.0), y);
 }
-__device__ __forceinline__ double rsq2(double x) {
-  const double y = rsq1(x);
-  return fma(0.5 * y, fma(-x * y, y, 1.0), y);
+// 1/sqrt(x) and 1/x with one step of third order (rounded): one dependent
+// operation more than a Newton step, two (one) fewer than a second one.
+__device__ __forceinline__ double rsq3(double x) {
+  const double y = __builtin_amdgcn_rsq(x), e = fma(-x * y, y, 1.0);
+  return fma(y * e, fma(e, 0.375, 0.5), y);
 }
-__device__ __forceinline__ double rcp2(double x) {
-  double y = __builtin_amdgcn_rcp(x);
-  y = fma(y, fma(-x, y, 1.0), y);
-  return fma(y, fma(-x, y, 1.0), y);
+__device__ __forceinline__ double rcp3(double x) {
+  const double y = __builtin_amdgcn_rcp(x), e = fma(-x, y, 1.0);
+  return fma(y, fma(e, e, e), y);
 }
 
 // Rotation of the 2 x 2 diagonal block (app, aqq real, apq).  With m = |apq|,
@@ -137,9 +138,9 @@ __device__ __forceinline__ Rot make_rot(double app, double aqq, double2 apq, dou
   if (m2 <= skip2 || (apq.x == 0.0 && apq.y == 0.0)) return r;
   double im, t;
   if (m2 > 1e-280 && m2 < 1e280 && fabs(d) < 1e140) {
-    im = rsq2(m2);
+    im = rsq3(m2);
     const double x = fma(d, d, 4.0 * m2);
-    t = (d >= 0.0 ? 2.0 : -2.0) * (m2 * im) * rcp2(fma(x, rsq2(x), fabs(d)));
+    t = (d >= 0.0 ? 2.0 : -2.0) * (m2 * im) * rcp3(fma(x, rsq3(x), fabs(d)));
   } else {
     const double m = hypot(apq.x, apq.y);
     im = 1.0 / m;
