@@ -118,8 +118,8 @@ int32_t px_grid_supported(const px_cell* cell, px_precision prec);
 /* Bytes of workspace that `op` uses for this problem with the context's current
  * tuning when it has them; 0 if the arguments are invalid.  n_phi is ignored for
  * PX_OP_ACE_BUILD (Phi = Psi).  A smaller workspace is accepted as long as it
- * holds a default pair chunk of at least 24 x 24 (general form 24 x 12) slabs, or
- * three quarters of n where n is smaller, and one split of every contraction: the
+ * holds a pair chunk of 24 x 24 (general form 24 x 12) slabs, or three quarters of n
+ * where n is smaller, and one split of every contraction: the
  * call then takes the largest default chunk, and the most of the split counts, that
  * fit (results differ by the summation order).  A chunk set by px_set_tuning,
  * px_autotune or px_load_tuning is not changed. */
@@ -134,9 +134,10 @@ px_status px_set_workspace(px_context* ctx, void* dev_ptr, size_t bytes);
 /* Pair-chunk tuning: a chunk is ic output orbitals x jc density orbitals whose
  * pair slabs are in flight together (Sec. III-B(b) batches 16 pairs on its
  * GPU).  0 restores the default: blocks of b x b slabs in the Hermitian-pair mode,
- * b x b/2 in the general form, with b the largest of 128, 96, 64, 48 and 32 whose
- * b x b slabs of N_g complex128 values stay below 16.4 GB (b = 128 to 32^3, 96 to
- * 48^3, 64 at 60^3, 48 to 72^3, else 32; the FP32 form takes half of the memory).
+ * with b the largest of 128, 96, 64, 48 and 32 whose b x b slabs of N_g complex128
+ * values stay below 16.4 GB (b = 128 to 32^3, 96 to 48^3, 64 at 60^3, 48 to 72^3, else
+ * 32; the FP32 form takes half of the memory); in the general form b x b/2, or 32 x 32
+ * and 16 x 32 where b is 48 and 32, evened out over n_phi and n_psi.
  * Against b = 32 everywhere that is 2 to 20 % of a build for up to 16 times the
  * memory; with a smaller workspace the call takes a smaller block (see
  * px_workspace_bytes).  Changes px_workspace_bytes.  The tile configuration that

@@ -357,9 +357,10 @@ template <class G, int R, int NA, class F> __device__ __forceinline__ void by_sl
 
 // One LDS -> LDS Stockham stage over all lines of geometry G, in place: every
 // thread loads its butterflies into registers, the block synchronises, then
-// each butterfly is transformed and written back.  Ends with a barrier.
-template <typename T, class G, int R, int NS, bool INV, int NA>
-__device__ __forceinline__ void stage_lds(cpx<T>* lds, const cpx<T>* tw, int t) {
+// each butterfly is transformed and written back.  tw(v, j) applies the stage's
+// twiddles to butterfly j.  Ends with a barrier.
+template <typename T, class G, int R, int NS, bool INV, int NA, class W>
+__device__ __forceinline__ void stage_lds(cpx<T>* lds, int t, W&& tw) {
   by_slots<G, R, NA>([&](auto sc) {
     constexpr int S = decltype(sc)::value;
     cpx<T> v[S > 0 ? S : 1][R];
@@ -375,7 +376,7 @@ __device__ __forceinline__ void stage_lds(cpx<T>* lds, const cpx<T>* tw, int t) 
     for (int k = 0; k < S; ++k) {
       int line, j;
       slot<G, R, NA>(t, k, line, j);
-      twiddle<T, G::n, R, NS, INV>(v[k], j, tw);
+      tw(v[k], j);
       dft<T, R, INV>(v[k]);
 #pragma unroll
       for (int r = 0; r < R; ++r) lds[line * G::ls + out_pos<R, NS>(j, r) * G::es] = v[k][r];

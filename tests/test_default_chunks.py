@@ -1,0 +1,56 @@
+"""Default pair chunks through px_workspace_bytes (CPU): the slabs of the general form
+(exchange) and of the Hermitian-pair mode (ACE construction) per grid, and their bound
+in memory."""
+import ctypes
+
+import pytest
+
+from paper_2501_03061_amd import px
+
+
+def _bytes(ctx, op, grid, prec, n, m):
+    cell = px.Cell(tuple(0.3 * k for k in grid), grid).c()
+    return px.load_library().px_workspace_bytes(ctx, op, ctypes.byref(cell), prec, n, m)
+
+
+@pytest.fixture()
+def ctx():
+    lib = px.load_library()
+    h = ctypes.c_void_p()
+    assert lib.px_create(0, ctypes.byref(h)) == px.PX_OK
+    yield h
+    lib.px_destroy(h)
+
+
+@pytest.mark.parametrize("grid,block,general", [((16,) * 3, 128, (128, 64)), ((24,) * 3, 128, (128, 64)),
+                                                ((48,) * 3, 96, (96, 48)), ((60,) * 3, 64, (64, 32)),
+                                                ((60, 60, 90), 48, (32, 32)), ((72,) * 3, 48, (32, 32)),
+                                                ((60, 90, 120), 32, (16, 32)), ((96,) * 3, 32, (16, 32))])
+def test_slabs(ctx, grid, block, general):
+    ng = grid[0] * grid[1] * grid[2]
+    for prec, b in ((0, 16), (1, 8)):
+        # 384 and 768 orbitals: multiples of every chunk, so that none is evened out
+        got = _bytes(ctx, px.PX_OP_EXCHANGE, grid, prec, 768, 384)
+        slabs = general[0] * general[1]
+        # beside the slabs: energy partials, tile sums and the kernel table (at most 3 %
+        # of a slab of 4,096 points each) and the energies of the pairs
+        assert slabs * ng * b <= got <= 1.05 * slabs * ng * b + ng * 8 + 768 * 384 * 8 + 4096
+        ace = _bytes(ctx, px.PX_OP_ACE_BUILD, grid, prec, 384, 0)
+        fixed = 384 * ng * b + 3 * 384 * 384 * 16
+        assert block * block * ng * b + fixed <= ace
+        assert block == 32 or block * block * ng * 16 <= 16.4e9
+
+
+@pytest.mark.parametrize("n_phi", [-1, 0, 1])
+def test_counts_that_are_ignored(ctx, n_phi):
+    """n_phi of the operations that do not take it, and a bad one of those that do."""
+    for op in (px.PX_OP_ACE_BUILD, px.PX_OP_SIGMA_DIAG, px.PX_OP_DENSITY_SIGMA, px.PX_OP_ROTATE):
+        assert _bytes(ctx, op, (72,) * 3, 0, 5, n_phi) > 0
+    assert (_bytes(ctx, px.PX_OP_EXCHANGE, (72,) * 3, 0, 5, n_phi) > 0) == (n_phi > 0)
+
+
+def test_chunks_of_equal_size(ctx):
+    """33 columns in two chunks take 17 each, not 32 and 1."""
+    ng = 96 ** 3
+    got = _bytes(ctx, px.PX_OP_EXCHANGE, (96,) * 3, 0, 33, 16)
+    assert 16 * 17 * ng * 16 <= got < 16 * 18 * ng * 16
