@@ -29,7 +29,7 @@ SHAPES = ((60, 60, 90), (60, 90, 120))
 ARCH = "gfx950"
 
 COMMON = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-I", HERE,
-          "-I", os.path.join(ROOT, "include"), "-Wall", "-Wno-unused-function"]
+          "-I", os.path.join(ROOT, "include"), "-Wall"]
 DEVICE = ["-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-munsafe-fp-atomics"]
 
 
@@ -72,6 +72,8 @@ def _compile(unit):
     r = subprocess.run(cmd, capture_output=True, text=True)
     err = r.stderr or ""
     users = scratch_users(err)
+    if r.returncode == 0 and src.endswith(".hip") and "ScratchSize" not in err:
+        return src, obj, 1, "no resource report from the compiler\n" + err, users
     # the remarks (with the two lines of source that follow some) are not messages
     err = re.sub(r"(^In file included from .*\n)*^.*\[-Rpass-analysis=kernel-resource-usage\]\n(\s+\d* \|.*\n)*", "", err + "\n", flags=re.M)
     msgs = "\n".join(l for l in err.splitlines() if "packed-fp32-ops" not in l)
