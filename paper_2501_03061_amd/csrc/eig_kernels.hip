@@ -53,12 +53,6 @@ __device__ __forceinline__ void round_pair(int np, int k, int slot, int& p, int&
   q = a < b ? b : a;
 }
 
-__device__ __forceinline__ double2 cmul2(double2 a, double2 b) {
-  return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
-}
-__device__ __forceinline__ double2 cconj2(double2 a) { return make_double2(a.x, -a.y); }
-__device__ __forceinline__ double2 cadd2(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
-
 // (x0, x1) <- (x0, x1) G
 __device__ __forceinline__ void rotate_cols(const Rot& g, double2& x0, double2& x1) {
   const double2 t = make_double2(x1.x * g.er - x1.y * g.ei, x1.x * g.ei + x1.y * g.er);

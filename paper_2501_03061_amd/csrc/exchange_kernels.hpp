@@ -165,7 +165,6 @@ template <typename T, int N0, int N1, int N2, int W, int RS_ = ztile_radix<N2>()
   static constexpr int PL = N0 * N1;
   static constexpr int NTILE = (PL + W - 1) / W;
   static constexpr bool RAG = PL % W != 0;
-  static_assert(Plan<N2>::nst == 2, "z tiles assume two-stage plans");
   static constexpr int RS = RS_, RB = N2 / RS;
   static constexpr bool FWD = Plan<N2>::rad[0] == RS;  // radix order of the forward transform
   using F0 = StageOf<N2, 0, !FWD>;
@@ -331,8 +330,6 @@ template <typename T, int N2, int CFG> constexpr int tile_width3() {
 // so the two meet in registers around the kernel multiply.
 template <typename T, int N0, int N1> struct Slab {
   static constexpr int P0 = N0 + 1;
-  static constexpr int NSX = 2, NSY = 2;
-  static_assert(Plan<N0>::nst == 2 && Plan<N1>::nst == 2, "slabs assume two-stage plans");
   using GX = Lines<N0, N1, P0, 1, true>;
   using GY = Lines<N1, N0, 1, P0, true>;
 };

@@ -35,7 +35,6 @@ template <typename T> __device__ __forceinline__ cpx<T> cmulc(cpx<T> a, cpx<T> b
 }
 template <typename T> __device__ __forceinline__ cpx<T> cadd(cpx<T> a, cpx<T> b) { return {a.x + b.x, a.y + b.y}; }
 template <typename T> __device__ __forceinline__ cpx<T> csub(cpx<T> a, cpx<T> b) { return {a.x - b.x, a.y - b.y}; }
-template <typename T> __device__ __forceinline__ cpx<T> cscale(cpx<T> a, T s) { return {a.x * s, a.y * s}; }
 // multiply by -i (forward) or +i (inverse)
 template <typename T, bool INV> __device__ __forceinline__ cpx<T> mul_mi(cpx<T> a) {
   if (INV) return {-a.y, a.x};
@@ -198,12 +197,6 @@ template <typename T, int A, int B, bool INV> __device__ __forceinline__ void df
   }
 }
 
-// Factor A of a composite length handled by dft_ct<A, R/A>.
-template <int R> constexpr int first_factor() {
-  return R % 8 == 0 && R > 8 ? 8 : R % 6 == 0 && R > 6 ? 6 : R % 4 == 0 && R > 4 ? 4
-       : R % 3 == 0 && R > 3 ? 3 : R % 2 == 0 && R > 2 ? 2 : R % 5 == 0 && R > 5 ? 5 : 1;
-}
-
 template <typename T, int R, bool INV> __device__ __forceinline__ void dft(cpx<T>* v) {
   if constexpr (R == 2) dft2<T, INV>(v);
   else if constexpr (R == 3) dft3<T, INV>(v);
@@ -213,12 +206,9 @@ template <typename T, int R, bool INV> __device__ __forceinline__ void dft(cpx<T
   else if constexpr (R == 9) dft_ct<T, 3, 3, INV>(v);
   else if constexpr (R == 10) dft_ct<T, 2, 5, INV>(v);
   else if constexpr (R == 12) dft_ct<T, 4, 3, INV>(v);
-  else if constexpr (R == 8) dft8<T, INV>(v);
   else {
-    // whole-line transforms (e.g. 72 = 8 x 9) for the register-resident pencils
-    constexpr int A = first_factor<R>();
-    static_assert(A > 1 && R % A == 0, "length must factor into 2, 3, 5");
-    dft_ct<T, A, R / A, INV>(v);
+    static_assert(R == 8, "radix without a kernel");
+    dft8<T, INV>(v);
   }
 }
 
@@ -228,33 +218,26 @@ template <typename T, int R, bool INV> __device__ __forceinline__ void dft(cpx<T
 // transform uses the reversed sequence so that its first radix equals the
 // forward's last.
 template <int N> struct Plan;
-#define PX_PLAN(N_, NST_, R0_, R1_, R2_) \
-  template <> struct Plan<N_> { static constexpr int nst = NST_; static constexpr int rad[3] = {R0_, R1_, R2_}; };
-PX_PLAN(16, 2, 4, 4, 1)
-PX_PLAN(24, 2, 8, 3, 1)
-PX_PLAN(32, 2, 8, 4, 1)
-PX_PLAN(40, 2, 8, 5, 1)
-PX_PLAN(48, 2, 8, 6, 1)
-PX_PLAN(60, 2, 6, 10, 1)
-PX_PLAN(64, 2, 8, 8, 1)
-PX_PLAN(72, 2, 8, 9, 1)
-PX_PLAN(80, 2, 8, 10, 1)
-PX_PLAN(90, 2, 9, 10, 1)
-PX_PLAN(96, 2, 8, 12, 1)
-PX_PLAN(120, 2, 10, 12, 1)
+#define PX_PLAN(N_, R0_, R1_) template <> struct Plan<N_> { static constexpr int rad[2] = {R0_, R1_}; };
+PX_PLAN(16, 4, 4)
+PX_PLAN(24, 8, 3)
+PX_PLAN(32, 8, 4)
+PX_PLAN(40, 8, 5)
+PX_PLAN(48, 8, 6)
+PX_PLAN(60, 6, 10)
+PX_PLAN(64, 8, 8)
+PX_PLAN(72, 8, 9)
+PX_PLAN(80, 8, 10)
+PX_PLAN(90, 9, 10)
+PX_PLAN(96, 8, 12)
+PX_PLAN(120, 10, 12)
 #undef PX_PLAN
 
 // Radix and span of stage S of the plan's radix sequence (INV = false) or of
 // the reversed sequence (INV = true, the order of the inverse transforms).
 template <int N, int S, bool INV> struct StageOf {
-  static constexpr int nst = Plan<N>::nst;
-  static constexpr int idx = INV ? (nst - 1 - S) : S;
-  static constexpr int R = Plan<N>::rad[idx];
-  static constexpr int NS = [] {
-    int p = 1;
-    for (int s = 0; s < S; ++s) p *= Plan<N>::rad[INV ? (Plan<N>::nst - 1 - s) : s];
-    return p;
-  }();
+  static constexpr int R = Plan<N>::rad[INV ? 1 - S : S];
+  static constexpr int NS = S == 0 ? 1 : Plan<N>::rad[INV ? 1 : 0];
 };
 
 // ---------------------------------------------------------------- line geometry

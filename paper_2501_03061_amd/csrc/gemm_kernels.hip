@@ -55,10 +55,6 @@ template <typename T> __device__ __forceinline__ cpx<T> load_c(const cpx<T>* p) 
 }
 
 typedef float vf4g __attribute__((ext_vector_type(4)));
-// Two consecutive complex64 values (16-byte aligned).
-__device__ __forceinline__ vf4g gload4(const cpx<float>* p) {
-  return *reinterpret_cast<const vf4g*>(p);
-}
 
 // Row of the 16x16 result held in item t of a lane with l/16 = q.
 template <typename T> __device__ __forceinline__ int drow(int q, int t) {

@@ -31,7 +31,7 @@ __global__ __launch_bounds__(256) void pass4_rows(ChunkArgs a0, const ChunkArgs*
   const ChunkArgs a = chunk_args(a0, tasks);
   const size_t e = (size_t(blockIdx.x) * 256 + threadIdx.x) * Lane<T>::EV;
   const int ii = blockIdx.y;
-  if (!a.store_v || ii >= a.ic || e >= ng) return;
+  if (ii >= a.ic || e >= ng) return;
   const int jend = a.tri ? ii + 1 : a.jc;  // a triangular block holds jj <= ii
   const T* t = reinterpret_cast<const T*>(a.t) + 2 * (size_t(ii) * a.jc * ng + e);
   T* const o = reinterpret_cast<T*>(a.out) + 2 * (size_t(a.i0 + ii) * ng + e);
