@@ -315,10 +315,6 @@ void pass1_z(ChunkArgs a0, const ChunkArgs* tasks) {
 }
 
 template <typename T, int CFG> constexpr int tile_width() { return ztile_width(sizeof(T) == 4, CFG); }
-// Pass 3 at 96 planes in FP64 takes 512-byte rows (with 256-byte rows 3% more).
-template <typename T, int N2, int CFG> constexpr int tile_width3() {
-  return N2 == 96 && sizeof(T) == 8 ? 32 : tile_width<T, CFG>();
-}
 
 // ============================================================== pass 2
 // Workgroup = the xy slab at kz = blockIdx.x of pq consecutive pairs; the
@@ -439,8 +435,8 @@ void pass2_xy(ChunkArgs a0, const ChunkArgs* tasks, int pq) {
   };
   // PF: the slab of the next pair is requested after the kernel multiply (its
   // registers are free then and the kernel loads done) and arrives during the
-  // inverse transforms.  Where LDS holds one workgroup per CU nothing else
-  // covers the latency.
+  // inverse transforms.  (Requested right after its predecessor's first stage, with
+  // the kernel values kept in registers: 72^3 FP64 2.95 ms per 1000 pairs against 2.88.)
   constexpr int S0 = slots<GY, Y0::R, NA>();
   static_assert(!PF || (N1 / Y0::R) % (NA / N0) == 0, "prefetch needs full slots");
   auto request = [&](__amdgpu_buffer_rsrc_t b, auto& v, int t, auto sc) {
@@ -888,17 +884,32 @@ void pass3_z(ChunkArgs a0, const ChunkArgs* tasks) {
 // ============================================================== host launcher
 // Threads of a pass-2 workgroup that take butterflies (the workgroup has whole
 // waves): a multiple of the line counts, so that a thread keeps its line, with
-// one to three butterflies in each stage.
+// one to four butterflies in each stage.  More threads hide less of the LDS round
+// trips by independent butterflies and fill ragged slots worse, fewer run out of
+// registers.  Pass 2 with the energy, ms per 1000 pairs, here against others:
+//   FP32  24^3 192: 0.065, 96: 0.061 (with 16 orbitals 0.127, 0.119); 48^3 192: 0.37, 288: 0.45,
+//         384: 0.42; 60^3 180: 0.85, 360: 0.97; 72^3 216: 1.58, 360: 1.66, 432: 1.66, 648: 2.09;
+//         80^3 320: 2.28, 640: 2.88; 96^3 384: 3.50, 576: 4.84, 768: 4.36; 60 x 90 180: 2.85, 360: 3.20,
+//         540: 4.19
+//   FP64  24^3 192: 0.097, 96: 0.094; 48^3 192: 0.70, 288: 0.90, 384: 0.72; 60^3 360: 1.60, 180: 1.72;
+//         72^3 648: 3.0, 360: 3.8; 80^3 640: 4.05, 320: 5.2; 96^3 768: 6.5, 384: 7.1; 60 x 90 540: 5.76,
+//         360: 6.6, 180: 7.5
 template <typename T, int N0, int N1> constexpr int slab_threads() {
   constexpr bool f = sizeof(T) == 4;
   if (N0 != N1) return f ? 180 : 540;  // 60 x 90
   return N0 == 16 ? 64 : N0 == 24 ? 192 : N0 == 32 ? 128 : N0 == 40 ? 320 : N0 == 48 ? 192
-       : N0 == 60 ? 360 : N0 == 64 ? (f ? 256 : 512) : N0 == 72 ? (f ? 216 : 648)
+       : N0 == 60 ? (f ? 180 : 360) : N0 == 64 ? (f ? 256 : 512) : N0 == 72 ? (f ? 216 : 648)
        : N0 == 80 ? (f ? 320 : 640) : f ? 384 : 768;
 }
-// Whether pass 2 requests the next pair's slab ahead (see PF).
+// Whether pass 2 requests the next pair's slab ahead (see PF): from 64^3 in FP32
+// and 60 points in FP64, where few workgroups fit a CU (FP64: one from 72^3 on).
+// Pass 2 with the energy, ms per 1000 pairs, without -> with: FP32 64^3 0.864 -> 0.850,
+// 72^3 1.573 -> 1.583 (without the energy 1.515 -> 1.474), 80^3 2.33 -> 2.28, 96^3 3.56 -> 3.50;
+// FP64 60^3 1.68 -> 1.63, 64^3 1.52 -> 1.47, 72^3 3.40 -> 3.00, 80^3 4.50 -> 4.05, 96^3 6.97 ->
+// 6.51, 60 x 90 x 120 6.29 -> 5.76.  FP32 at 60^3 would spill, 60 x 90 has no full slots; below
+// 60 points the threads' slots are not full either, and many workgroups fit.
 template <typename T, int N0, int N1> constexpr bool slab_prefetch() {
-  return sizeof(T) == 8 ? N0 >= 60 : N0 == N1 && N0 >= 60 && N0 != 80;
+  return sizeof(T) == 8 ? N0 >= 60 : N0 == N1 && N0 >= 64;
 }
 
 template <int N0, int N1, int N2, int CFG>
@@ -907,11 +918,10 @@ hipError_t launch_chunk_cfg(bool fp32, const ChunkArgs& a, const ChunkDims& d, b
   constexpr int WF = tile_width<float, CFG>(), WD = tile_width<double, CFG>();
   using ZF = ZTile<float, N0, N1, N2, WF>;
   using ZD = ZTile<double, N0, N1, N2, WD>;
-  // pass 3 tiles
-  constexpr int VF = tile_width3<float, N2, CFG>(), VD = tile_width3<double, N2, CFG>();
-  using YF = ZTile<float, N0, N1, N2, VF, ztile_radix3<float, N2>()>;
-  using YD = ZTile<double, N0, N1, N2, VD, ztile_radix3<double, N2>()>;
-  const int ntile = fp32 ? ZF::NTILE : ZD::NTILE, ntile3 = fp32 ? YF::NTILE : YD::NTILE;
+  // pass 3
+  using YF = ZTile<float, N0, N1, N2, WF, ztile_radix3<float, N2>()>;
+  using YD = ZTile<double, N0, N1, N2, WD, ztile_radix3<double, N2>()>;
+  const int ntile = fp32 ? ZF::NTILE : ZD::NTILE;
   if (ev) (void)hipEventRecord(ev[0], s);
   const dim3 g1(tile_grid(ntile), d.max_ic, d.ntasks);
   if (fp32) hipLaunchKernelGGL((pass1_z<float, N0, N1, N2, WF, true>), g1, dim3(ZF::NT), 0, s, a, tasks);
@@ -928,17 +938,17 @@ hipError_t launch_chunk_cfg(bool fp32, const ChunkArgs& a, const ChunkDims& d, b
   if (ev) (void)hipEventRecord(ev[2], s);
   int gj = 0;
   if (!d.store_v) {
-    if (fp32) hipLaunchKernelGGL((pass3_z<float, N0, N1, N2, VF, false, 1>), dim3(tile_grid(ntile3), d.max_ic, d.ntasks), dim3(YF::NT), 0, s, a, tasks);
-    else hipLaunchKernelGGL((pass3_z<double, N0, N1, N2, VD, false, 1>), dim3(tile_grid(ntile3), d.max_ic, d.ntasks), dim3(YD::NT), 0, s, a, tasks);
+    if (fp32) hipLaunchKernelGGL((pass3_z<float, N0, N1, N2, WF, false, 1>), dim3(tile_grid(ntile), d.max_ic, d.ntasks), dim3(YF::NT), 0, s, a, tasks);
+    else hipLaunchKernelGGL((pass3_z<double, N0, N1, N2, WD, false, 1>), dim3(tile_grid(ntile), d.max_ic, d.ntasks), dim3(YD::NT), 0, s, a, tasks);
   } else {
     constexpr int GF = col_group(true, YF::RS), GD = col_group(false, YD::RS);
     gj = fp32 ? GF : GD;
-    if (small_group(ntile3, d.max_jc, gj, d.ntasks)) gj = 1;
-    const dim3 g3(tile_grid(ntile3), (d.max_jc + gj - 1) / gj, d.ntasks);
-    if (fp32 && gj > 1) hipLaunchKernelGGL((pass3_z<float, N0, N1, N2, VF, true, GF>), g3, dim3(YF::NT), 0, s, a, tasks);
-    else if (fp32) hipLaunchKernelGGL((pass3_z<float, N0, N1, N2, VF, true, 1>), g3, dim3(YF::NT), 0, s, a, tasks);
-    else if (gj > 1) hipLaunchKernelGGL((pass3_z<double, N0, N1, N2, VD, true, GD>), g3, dim3(YD::NT), 0, s, a, tasks);
-    else hipLaunchKernelGGL((pass3_z<double, N0, N1, N2, VD, true, 1>), g3, dim3(YD::NT), 0, s, a, tasks);
+    if (small_group(ntile, d.max_jc, gj, d.ntasks)) gj = 1;
+    const dim3 g3(tile_grid(ntile), (d.max_jc + gj - 1) / gj, d.ntasks);
+    if (fp32 && gj > 1) hipLaunchKernelGGL((pass3_z<float, N0, N1, N2, WF, true, GF>), g3, dim3(YF::NT), 0, s, a, tasks);
+    else if (fp32) hipLaunchKernelGGL((pass3_z<float, N0, N1, N2, WF, true, 1>), g3, dim3(YF::NT), 0, s, a, tasks);
+    else if (gj > 1) hipLaunchKernelGGL((pass3_z<double, N0, N1, N2, WD, true, GD>), g3, dim3(YD::NT), 0, s, a, tasks);
+    else hipLaunchKernelGGL((pass3_z<double, N0, N1, N2, WD, true, 1>), g3, dim3(YD::NT), 0, s, a, tasks);
   }
   if (ev) (void)hipEventRecord(ev[3], s);
   hipError_t e = hipGetLastError();

@@ -127,12 +127,17 @@ struct ChunkDims {
   int store_v;    // of every chunk
 };
 // Whether pass 3 has too few workgroups with groups of gj columns to fill the
-// chip (256 CUs): then one column per workgroup.
+// chip (256 CUs): then one column per workgroup.  Passes 3 and 4 of builds, ms per
+// 1000 pairs, with groups always / below 384 workgroups / below 1536: 24^3 FP32 8
+// orbitals 1.36 / 0.65 / 0.65, 40 orbitals 0.37 / 0.12 / 0.12; 48^3 FP32 16 orbitals 0.90 /
+// 0.92 / 0.93, 40 orbitals 0.44 / 0.44 / 0.61, 128 orbitals 0.36 / 0.36 / 0.55.
 inline bool small_group(int ntile, int max_jc, int gj, int ntasks) {
   return size_t(ntile) * ((max_jc + gj - 1) / gj) * ntasks < 384;
 }
-// Pairs that a pass-2 workgroup takes (the kernel values of its slab are
-// loaded once for them), with at least 4096 workgroups left.
+// Pairs that a pass-2 workgroup takes one after the other (its twiddle tables are
+// made once for them), with at least 4096 workgroups left.  Pass 2, ms per 1000
+// pairs, with at least 1024 / 4096 / 16384 left: 48^3 x 16 FP32 0.54 / 0.40 / 0.41, FP64 0.98 /
+// 0.72 / 0.72; 24^3 x 16 FP32 0.153 / 0.127 / 0.126; 65536 at 72^3 x 96: FP32 1.58 -> 1.77.
 constexpr int kSlabPairs = 8;  // at most
 inline int pairs_per_slab_wg(int n2, int max_pairs, int ntasks) {
   const size_t wgs = size_t(n2) * max_pairs * ntasks;
