@@ -136,8 +136,8 @@ px_status px_set_workspace(px_context* ctx, void* dev_ptr, size_t bytes);
  * GPU).  0 restores the default: blocks of b x b slabs in the Hermitian-pair mode,
  * with b the largest of 128, 96, 64, 48 and 32 whose b x b slabs of N_g complex128
  * values stay below 16.4 GB (b = 128 to 32^3, 96 to 48^3, 64 at 60^3, 48 to 72^3, else
- * 32; the FP32 form takes half of the memory); in the general form b x b/2, or 32 x 32
- * and 16 x 32 where b is 48 and 32, evened out over n_phi and n_psi.
+ * 32; the FP32 form takes half of the memory); in the general form b x b/2, or 48 x 48
+ * and 16 x 32 where b is 48 and 32.
  * Against b = 32 everywhere that is 2 to 20 % of a build for up to 16 times the
  * memory; with a smaller workspace the call takes a smaller block (see
  * px_workspace_bytes).  Changes px_workspace_bytes.  The tile configuration that

@@ -150,21 +150,20 @@ std::vector<Chunk> chunks(const px_context* c, const px_cell* cell, px_precision
     for (const int b : blocks) v.push_back({b, b, 0});
     return v;
   }
-  // General form: b x b/2; where b is 48 or 32 fewer rows and more columns for the
-  // same slabs (pass 3 reads and writes an output once per chunk of columns, and 16
-  // rows of z tiles fill the chip there).  Per 1000 pairs, ms, b x b/2 -> this:
-  // 72^3 FP64 5.58 -> 5.46, FP32 3.01 -> 2.93, 64^3 3.36 -> 3.22 and 1.88 -> 1.84,
-  // 60 x 60 x 90 4.87 -> 5.00 and 2.72 -> 2.74 with 64 outputs, 4.80 -> 4.76 and 2.74 ->
-  // 2.73 with 30; 96^3 12.9 -> 12.7 and 6.88 -> 6.73, 80^3 7.69 -> 7.56 and 4.34 -> 4.33.
-  // At 24^3 and 48^3, where b is larger, 16 x 64 would take 0.18 against 0.14 and 0.79
-  // against 0.76.  Chunks of one call are of equal size.  Last the b x b/2 of 32 and of
-  // the smallest block (see default_blocks): for few outputs they are smaller.
-  auto even = [](int n, int c) { return (n + (n + c - 1) / c - 1) / ((n + c - 1) / c); };
+  // General form: b x b/2; where b is 48 or 32 more columns (pass 3 reads and writes an
+  // output once per chunk of columns): all slabs of the block at 48, half the rows at
+  // 32.  Per 1000 pairs with 128 x 64 orbitals, ms, b x b/2 -> this: 72^3 FP64 5.58 -> 5.40,
+  // FP32 2.97 -> 2.88, 64^3 3.35 -> 3.19 and 1.90 -> 1.83, 60 x 60 x 90 4.87 -> 4.79 and 2.68 ->
+  // 2.63 (32 x 32 there: 4.98 and 2.69, 16 x 64 4.96 and 2.75); with 96 x 32 orbitals 96^3 12.9 ->
+  // 12.7 and 6.88 -> 6.73, 80^3 7.69 -> 7.56 and 4.34 -> 4.33.  Where b is larger the outputs
+  // are read rarely enough: 24^3 FP32 with 64 x 32 0.131 and 16 x 64 0.183 against 0.138.
+  // (Chunks of equal size within a call, 2 x 32 rows for 64, are slower: 60 x 60 x 90 FP64
+  // 5.00, 72^3 5.46.)  Last the b x b/2 of 32 and of the smallest block (see
+  // default_blocks): for few outputs they are smaller.
   for (const int b : blocks)
     if (b >= 64) v.push_back({b, b / 2, 0});
-    else if (b == 48) v.push_back({32, 32, 0});
+    else if (b == 48) v.push_back({48, 48, 0});
     else if (b == 32) v.push_back({16, 32, 0});
-  for (Chunk& c : v) c = {even(n_phi, c.ic), even(n_psi, c.jc), 0};
   v.push_back({32, 16, 0});
   v.push_back({blocks.back(), blocks.back() > 1 ? blocks.back() / 2 : 1, 0});
   return v;
@@ -562,7 +561,7 @@ size_t px_workspace_bytes(const px_context* ctx, px_op op, const px_cell* cell, 
   const bool fft_op = op == PX_OP_EXCHANGE || op == PX_OP_ACE_BUILD || op == PX_OP_EXCHANGE_SIGMA ||
                       op == PX_OP_ACE_BUILD_SIGMA;
   if (fft_op ? !fft_grid : !gemm_grid) return 0;
-  const Chunk gen = chunks(ctx, cell, prec, false, n_psi, n_phi > 0 ? n_phi : 1)[0];
+  const Chunk gen = chunks(ctx, cell, prec, false, n_psi, n_phi)[0];
   const Chunk ace = chunks(ctx, cell, prec, ctx->symmetric_ace, n_psi, n_psi)[0];
   switch (op) {
     case PX_OP_EXCHANGE:

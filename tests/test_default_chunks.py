@@ -24,12 +24,11 @@ def ctx():
 
 @pytest.mark.parametrize("grid,block,general", [((16,) * 3, 128, (128, 64)), ((24,) * 3, 128, (128, 64)),
                                                 ((48,) * 3, 96, (96, 48)), ((60,) * 3, 64, (64, 32)),
-                                                ((60, 60, 90), 48, (32, 32)), ((72,) * 3, 48, (32, 32)),
+                                                ((60, 60, 90), 48, (48, 48)), ((72,) * 3, 48, (48, 48)),
                                                 ((60, 90, 120), 32, (16, 32)), ((96,) * 3, 32, (16, 32))])
 def test_slabs(ctx, grid, block, general):
     ng = grid[0] * grid[1] * grid[2]
     for prec, b in ((0, 16), (1, 8)):
-        # 384 and 768 orbitals: multiples of every chunk, so that none is evened out
         got = _bytes(ctx, px.PX_OP_EXCHANGE, grid, prec, 768, 384)
         slabs = general[0] * general[1]
         # beside the slabs: energy partials, tile sums and the kernel table (at most 3 %
@@ -47,10 +46,3 @@ def test_counts_that_are_ignored(ctx, n_phi):
     for op in (px.PX_OP_ACE_BUILD, px.PX_OP_SIGMA_DIAG, px.PX_OP_DENSITY_SIGMA, px.PX_OP_ROTATE):
         assert _bytes(ctx, op, (72,) * 3, 0, 5, n_phi) > 0
     assert (_bytes(ctx, px.PX_OP_EXCHANGE, (72,) * 3, 0, 5, n_phi) > 0) == (n_phi > 0)
-
-
-def test_chunks_of_equal_size(ctx):
-    """33 columns in two chunks take 17 each, not 32 and 1."""
-    ng = 96 ** 3
-    got = _bytes(ctx, px.PX_OP_EXCHANGE, (96,) * 3, 0, 33, 16)
-    assert 16 * 17 * ng * 16 <= got < 16 * 18 * ng * 16
