@@ -1307,8 +1307,8 @@ int tile_cfg_for(const px_context* c, const px_cell* cell, px_precision prec) {
 // Plan of one batched call.  Instances are grouped by grid (all three
 // lengths); within a grid the block pairs (I, J <= I) of every instance are
 // scheduled by block diagonal d = I - J, so that one launch never has two
-// chunks writing the same output block (pass 3 writes block I, pass 4 block
-// J): d = 0 first (those chunks initialise the output), then d = 1, 2, ...  A
+// chunks writing the same output block (pass 3 adds to block J, pass 4 to block
+// I): d = 0 first (those chunks initialise the output), then d = 1, 2, ...  A
 // diagonal's chunks are packed into waves that fit the pair buffer.  In ACE
 // mode the instances completed by a wave form a tail group.  sz.cap: the pair buffer
 // of a wave, in bytes.  ws == nullptr: sizes only.

@@ -7,7 +7,7 @@
 
 namespace px {
 
-// FP64 per-slab sums of one pair product (FP32 form): sum of rho, and sum
+// FP64 sums of one pair product over a z tile (FP32 form): sum of rho, and sum
 // of |rho|^2 of the values handed to the transform.
 struct G0Part {
   double re, im, en, pad;
