@@ -301,8 +301,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void g
 // sums in order.  R > 1 where the splits are many (small matrices): with one
 // thread per entry, 108 splits of a 16 x 16 matrix were one workgroup's serial
 // loop.  ACE application, us, R = 1 -> R = 16: 24^3 x 16 FP32 (108 splits) 36.7 -> 25.8, 48^3 x
-// 64 (494) 189 -> 78, 60^3 x 128 (128) 423 -> 397; at 16^3 x 16 (32 splits) 23.9 -> 25.9, below
-// that equal.
+// 64 (494) 189 -> 78, 60^3 x 128 (128) 423 -> 397; at 32 splits 16^3 x 16 23.9 -> 25.9, but
+// the time step at 48^3 x 200 8,780 -> 8,740; below that equal.
 template <int R>
 __global__ __launch_bounds__(256) void xhy_reduce_k(int na, int nb, const double* part, int nsplit, double scale,
                              double* M, int ldm, float* M32, int herm) {
@@ -414,7 +414,7 @@ static hipError_t xhy_launch(bool fp32, int na, int nb, size_t ng, const void* X
   else if (wide) run(double{}, std::true_type{});
   else run(double{}, std::false_type{});
   const size_t n = size_t(na) * nb;
-  const bool many = nsplit > 32;
+  const bool many = nsplit >= 32;
   const size_t blocks = many ? (n + 15) / 16 : (n + 255) / 256;
   const dim3 rg(unsigned(blocks < 4096 ? blocks : 4096));
   if (many)
